@@ -180,8 +180,9 @@ mcc_status mcc_device_error(mcc_ctx *ctx, int32_t *code);
  * as 10).  In relativistic mode 9, 12 and 13 run in
  * global scratch: as (256,4096), four waves, in the order-N step, and as
  * (64,4096), one wave, in its diagnostic, N x N and duplicity forms.  -1 restores the default, which depends on
- * the precision mode (built-in table, the fastest measured on lognormal
- * cell-size mixes).  The variant's capacity must hold the bucket's largest cell,
+ * the precision mode and on whether n_cells exceeds the device's compute
+ * units (built-in tables, the fastest measured on lognormal cell-size mixes
+ * and on few cells).  The variant's capacity must hold the bucket's largest cell,
  * else MCC_ERR_INVALID.  Results agree between variants to rounding (the
  * order of the per-cell sums depends on the threads per cell).
  */

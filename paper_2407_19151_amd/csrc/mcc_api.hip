@@ -32,16 +32,15 @@ const void *const *mcc_kernel_table_fp32_dup();
 const void *const *mcc_kernel_table_rel_dup();
 
 namespace mcc {
-hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_zero_stats(mcc_stats *st, hipStream_t s);
-hipError_t launch_check_weights(int64_t n, const double *w, int32_t *err, hipStream_t s);
 hipError_t launch_set_u64(uint64_t *p, uint64_t v, hipStream_t s);
 hipError_t launch_inc_u64(uint64_t *p, hipStream_t s);
 hipError_t launch_flag_nonzero(const uint32_t *count, int32_t code, int32_t *err,
                                hipStream_t s);
-hipError_t launch_bucket_cells(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n,
-                               int32_t *lists, uint32_t *counts, int32_t *cell_corr, int32_t *err,
-                               hipStream_t s);
+hipError_t launch_front(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n,
+                        const double *w, int32_t *lists, uint32_t *counts, int32_t *cell_corr,
+                        mcc_stats *stats, double *zero, int64_t nzero, int first_bucket,
+                        int32_t *err, hipStream_t s);
 int64_t scan_tiles_needed(int64_t m);
 int64_t bin_tiles(int64_t n);
 int64_t bin_hist_entries(int64_t n);
@@ -174,12 +173,31 @@ struct mcc_ctx {
   int variant[NBUCKET] = {};
 };
 
+namespace {
+// The kernel variant of every bucket for one call, and the first bucket that
+// takes cells (the ones below hand theirs to it).
+struct Variants {
+  int v[NBUCKET];
+  int first = 0;
+  // The most cells bucket b can hold of n particles in n_cells cells: each
+  // has more than the bucket below holds.  0: the bucket is empty whatever
+  // the offsets hold (a segment inside [0, n) cannot be that large), and its
+  // kernel need not be launched; otherwise a bound for its grid, exact for
+  // well-formed offsets (a longer list is still worked off).
+  int64_t most_cells(int64_t n, int32_t n_cells, int b) const {
+    if (b < first) return 0;
+    const int64_t least = b > first ? (int64_t)kBucketCap[b - 1] + 1 : 1;
+    return std::min<int64_t>(n_cells, n / least);
+  }
+};
+}  // namespace
+
 struct mcc_plan {
   mcc_ctx *ctx = nullptr;
   CollideArgs args{};
   int mode = 0;
   int32_t n_cells = 0;
-  int variant[NBUCKET] = {};
+  Variants pick;
   uint32_t hcount[NBUCKET] = {};  // cells per bucket (fixed for the plan)
   DevBuf lists, counts, step;
   BigScratch big;          // large-cell scratch of this plan's kernels (its graph holds it)
@@ -344,10 +362,26 @@ void set_big_args(const BigScratch &B, CollideArgs &A, int mode, int v) {
 unsigned long long *g_phase = nullptr;
 #endif
 
-// enqueue the collide kernel of one bucket, reading its device work list
+// The caller's variants (mcc_set_variant) or the defaults, which depend on
+// n_cells alone, so a plan and a call of the same cells take the same ones
+// and give the same bits.
+Variants pick_variants(const mcc_ctx *ctx, int mode, int32_t n_cells) {
+  Variants r;
+  const bool few = n_cells <= ctx->n_cu;
+  bool merge = few;
+  for (int b = 0; b < NBUCKET; ++b) {
+    r.v[b] = ctx->variant[b] >= 0 ? ctx->variant[b] : default_variant(mode, b, few);
+    if (b <= kFewBucket && ctx->variant[b] >= 0) merge = false;
+  }
+  r.first = merge ? kFewBucket : 0;
+  return r;
+}
+
+// enqueue the collide kernel of one bucket, reading its device work list;
+// most: no more workgroups than this (cells known or bounded on the host)
 mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base, int mode,
                          int32_t n_cells, const int32_t *lists, const uint32_t *counts, int b,
-                         int v, hipStream_t stream) {
+                         int v, int64_t most, hipStream_t stream) {
   const void *const *tab = kernel_table(mode);
   if (!ensure_big(ctx, big, mode, v)) return MCC_ERR_OOM;
   CollideArgs A = base;
@@ -359,8 +393,9 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
   A.work = ctx->work.as<uint32_t>() + WORK_QUEUES * WORK_STRIDE * b;
   set_big_args(big, A, mode, v);
   void *kargs[] = {&A};
-  HIP_TRY(hipLaunchKernel(tab[v], dim3(grid_of(ctx, mode, v)), dim3(variant_of(mode, v).tpc),
-                          kargs, 0, stream));
+  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(grid_of(ctx, mode, v), most));
+  HIP_TRY(hipLaunchKernel(tab[v], dim3((unsigned)grid), dim3(variant_of(mode, v).tpc), kargs, 0,
+                          stream));
   return MCC_OK;
 }
 
@@ -375,21 +410,23 @@ static_assert(kBucketCap[kSideBucket] == 4096 && kBucketCap[kBesideBucket] == 20
 // large-cell buffer).
 mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base, int mode,
                           int32_t n_cells, const int32_t *lists, const uint32_t *counts,
-                          const int *variant, hipStream_t stream,
+                          const Variants &pick, hipStream_t stream,
                           const uint32_t *host_counts = nullptr, const Branch *br = nullptr) {
-  auto pick = [&](int b) { return variant[b] >= 0 ? variant[b] : default_variant(mode, b); };
+  auto most = [&](int b) {
+    return host_counts ? (int64_t)host_counts[b] : pick.most_cells(base.n, n_cells, b);
+  };
   const bool branch =
-      br && (!host_counts || (host_counts[kSideBucket] > 0 && host_counts[kBesideBucket] > 0)) &&
-      !(variant_of(mode, pick(kSideBucket)).layout == 2 &&
-        variant_of(mode, pick(kBesideBucket)).layout == 2);
+      br && most(kSideBucket) > 0 && most(kBesideBucket) > 0 &&
+      !(variant_of(mode, pick.v[kSideBucket]).layout == 2 &&
+        variant_of(mode, pick.v[kBesideBucket]).layout == 2);
   if (branch) {
     HIP_TRY(hipEventRecord(br->fork, stream));
     HIP_TRY(hipStreamWaitEvent(br->side, br->fork, 0));
   }
   for (int b = NBUCKET - 1; b >= 0; --b) {
-    if (host_counts && host_counts[b] == 0) continue;
-    const mcc_status st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick(b),
-                                        (branch && b == kSideBucket) ? br->side : stream);
+    if (most(b) == 0) continue;
+    const mcc_status st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick.v[b],
+                                        most(b), (branch && b == kSideBucket) ? br->side : stream);
     if (st != MCC_OK) return st;
     if (branch && b == kBesideBucket) {
       HIP_TRY(hipEventRecord(br->join, br->side));
@@ -622,14 +659,20 @@ mcc_status mcc_collide_sorted(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t 
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, step, p, stats,
             cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
   hipStream_t s = ctx->stream;
-  HIP_TRY(launch_fill_u32(ctx->counts.as<uint32_t>(), 0u, NBUCKET, s));
-  if (stats) HIP_TRY(launch_zero_stats(stats, s));
-  if (n_cells == 0) return finish(ctx);
-  HIP_TRY(launch_check_weights(n, weights, ctx->err, s));
-  HIP_TRY(launch_bucket_cells(offsets, n_cells, n_species, n, ctx->lists.as<int32_t>(),
-                              ctx->counts.as<uint32_t>(), cell_corr_pairs, ctx->err, s));
-  st = launch_buckets(ctx, ctx->big, A, mode_of(p, A), n_cells, ctx->lists.as<int32_t>(),
-                      ctx->counts.as<uint32_t>(), ctx->variant, s, nullptr, &ctx->branch);
+  if (n_cells == 0) {
+    if (stats) HIP_TRY(launch_zero_stats(stats, s));
+    return finish(ctx);
+  }
+  const int mode = mode_of(p, A);
+  const Variants pick = pick_variants(ctx, mode, n_cells);
+  HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, ctx->lists.as<int32_t>(),
+                       ctx->counts.as<uint32_t>(), cell_corr_pairs, stats, nullptr, 0, pick.first,
+                       ctx->err, s));
+  // (the branch's event calls cost the host more than the overlap gains when
+  // every cell has a CU to itself)
+  st = launch_buckets(ctx, ctx->big, A, mode, n_cells, ctx->lists.as<int32_t>(),
+                      ctx->counts.as<uint32_t>(), pick, s, nullptr,
+                      n_cells > ctx->n_cu ? &ctx->branch : nullptr);
   if (st != MCC_OK) return st;
   return finish(ctx);
 }
@@ -659,20 +702,24 @@ mcc_status mcc_collide_sorted_noalloc(mcc_ctx *ctx, int64_t n, int32_t n_cells,
             cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
   const int mode = mode_of(p, A);
   hipStream_t s = ctx->stream;
-  HIP_TRY(launch_fill_u32(counts, 0u, NBUCKET, s));
-  if (stats) HIP_TRY(launch_zero_stats(stats, s));
-  if (n_cells == 0) return finish(ctx);
-  HIP_TRY(launch_check_weights(n, weights, ctx->err, s));
-  HIP_TRY(launch_bucket_cells(offsets, n_cells, n_species, n, lists, counts, cell_corr_pairs,
-                              ctx->err, s));
+  if (n_cells == 0) {
+    if (stats) HIP_TRY(launch_zero_stats(stats, s));
+    return finish(ctx);
+  }
+  Variants pick = pick_variants(ctx, mode, n_cells);
+  HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, lists, counts, cell_corr_pairs,
+                       stats, nullptr, 0, pick.first, ctx->err, s));
   // cells above 4096 particles need the global-scratch kernels: not stepped
-  HIP_TRY(launch_flag_nonzero(counts + (NBUCKET - 1), 2, ctx->err, s));
+  if (pick.most_cells(n, n_cells, NBUCKET - 1) > 0)
+    HIP_TRY(launch_flag_nonzero(counts + (NBUCKET - 1), 2, ctx->err, s));
   BigScratch none;  // (the variants below never use it)
   for (int b = NBUCKET - 2; b >= 0; --b) {
-    int v = ctx->variant[b] >= 0 ? ctx->variant[b] : default_variant(mode, b);
-    if (variant_of(mode, v).layout == 2) v = default_variant(mode, b);
+    int v = pick.v[b];
+    if (variant_of(mode, v).layout == 2) v = default_variant(mode, b, n_cells <= ctx->n_cu);
     if (variant_of(mode, v).layout == 2) return MCC_ERR_UNSUPPORTED;
-    st = launch_bucket(ctx, none, A, mode, n_cells, lists, counts, b, v, s);
+    const int64_t most = pick.most_cells(n, n_cells, b);
+    if (most == 0) continue;
+    st = launch_bucket(ctx, none, A, mode, n_cells, lists, counts, b, v, most, s);
     if (st != MCC_OK) return st;
   }
   return finish(ctx);
@@ -711,14 +758,13 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells, int3
   A.dlnl = coulomb_log_tangent != 0.0 ? coulomb_log_tangent / coulomb_log : 0.0;
   A.write_primal = update_primal ? 1 : 0;
   hipStream_t s = ctx->stream;
-  HIP_TRY(launch_check_weights(n, weights, ctx->err, s));
-  HIP_TRY(launch_fill_u32(ctx->counts.as<uint32_t>(), 0u, NBUCKET, s));
-  if (stats) HIP_TRY(launch_zero_stats(stats, s));
+  const Variants pick = pick_variants(ctx, MODE_TAN, n_cells);
+  HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, ctx->lists.as<int32_t>(),
+                       ctx->counts.as<uint32_t>(), nullptr, stats, nullptr, 0, pick.first,
+                       ctx->err, s));
   if (n_cells == 0) return finish(ctx);
-  HIP_TRY(launch_bucket_cells(offsets, n_cells, n_species, n, ctx->lists.as<int32_t>(),
-                              ctx->counts.as<uint32_t>(), nullptr, ctx->err, s));
   st = launch_buckets(ctx, ctx->big, A, MODE_TAN, n_cells, ctx->lists.as<int32_t>(),
-                      ctx->counts.as<uint32_t>(), ctx->variant, s);
+                      ctx->counts.as<uint32_t>(), pick, s);
   if (st != MCC_OK) return st;
   return finish(ctx);
 }
@@ -778,13 +824,11 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
   A.err = ctx->err;
   A.n97 = ctx->n97.as<double2>();
   hipStream_t s = ctx->stream;
-  HIP_TRY(launch_check_weights(n, weights, ctx->err, s));
-  HIP_TRY(launch_fill_u32(ctx->counts.as<uint32_t>(), 0u, NBUCKET, s));
-  HIP_TRY(launch_fill_u32(reinterpret_cast<uint32_t *>(ctx->adj_part.p), 0u,
-                          2 * (int64_t)std::max(n_cells, 1), s));
+  const Variants pick = pick_variants(ctx, MODE_TAN, n_cells);
+  HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, ctx->lists.as<int32_t>(),
+                       ctx->counts.as<uint32_t>(), nullptr, nullptr, ctx->adj_part.as<double>(),
+                       n_cells, pick.first, ctx->err, s));
   if (n_cells > 0) {
-    HIP_TRY(launch_bucket_cells(offsets, n_cells, n_species, n, ctx->lists.as<int32_t>(),
-                                ctx->counts.as<uint32_t>(), nullptr, ctx->err, s));
     // the cell counts per size bucket size the scratch (one wait on the stream)
     uint32_t hc[NBUCKET];
     HIP_TRY(hipMemcpyAsync(hc, ctx->counts.p, sizeof(hc), hipMemcpyDeviceToHost, s));
@@ -793,8 +837,7 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
       if (hc[b] == 0) continue;
       // threads per cell of the forward-mode variant of the bucket, so the
       // per-cell sums (and the choices they decide) round as there
-      const int v = ctx->variant[b] >= 0 ? ctx->variant[b] : default_variant(MODE_TAN, b);
-      const Variant V = variant_of(MODE_TAN, v);
+      const Variant V = variant_of(MODE_TAN, pick.v[b]);
       const bool big = kBucketCap[b] > 4096;
       const int tpc = big ? 64 : V.tpc;
       const int cap = big ? MCC_MAX_CELL : 4096;
@@ -964,7 +1007,7 @@ static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s, const Branch &b
   if (pl->stats) HIP_TRY(launch_zero_stats(pl->stats, s));
   const mcc_status st =
       launch_buckets(pl->ctx, pl->big, pl->args, pl->mode, pl->n_cells, pl->lists.as<int32_t>(),
-                     pl->counts.as<uint32_t>(), pl->variant, s, pl->hcount, &br);
+                     pl->counts.as<uint32_t>(), pl->pick, s, pl->hcount, &br);
   if (st != MCC_OK) return st;
   HIP_TRY(launch_inc_u64(pl->step.as<uint64_t>(), s));
   return MCC_OK;
@@ -1018,7 +1061,6 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   pl->n_cells = n_cells;
   pl->stats = stats;
   pl->cell_corr = cell_corr_pairs;
-  for (int b = 0; b < NBUCKET; ++b) pl->variant[b] = -1;
   if (!ensure_lists(ctx, pl->lists, pl->counts, n_cells) || !pl->step.ensure(64)) {
     mcc_plan_destroy(pl);
     return MCC_ERR_OOM;
@@ -1027,14 +1069,16 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, 0, p, stats,
             cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
   pl->mode = mode_of(p, pl->args);
-  for (int b = 0; b < NBUCKET; ++b) pl->variant[b] = default_variant(pl->mode, b);
+  for (int b = 0; b < NBUCKET; ++b)  // (a plan keeps every bucket's own list)
+    pl->pick.v[b] = default_variant(pl->mode, b, n_cells <= ctx->n_cu);
   pl->args.step_dev = pl->step.as<uint64_t>();
   hipStream_t s = ctx->stream;
-  // device work lists, built once (offsets are fixed for the plan)
-  hipError_t e = launch_fill_u32(pl->counts.as<uint32_t>(), 0u, NBUCKET, s);
-  if (e == hipSuccess && n_cells > 0)
-    e = launch_bucket_cells(offsets, n_cells, n_species, n, pl->lists.as<int32_t>(),
-                            pl->counts.as<uint32_t>(), cell_corr_pairs, ctx->err, s);
+  // device work lists, built once (offsets are fixed for the plan); the
+  // weights are bound to the plan too: checked here (positive and finite; a
+  // violation is latched as data error 4) and never again per step
+  hipError_t e = launch_front(offsets, n_cells, n_species, n, weights, pl->lists.as<int32_t>(),
+                              pl->counts.as<uint32_t>(), cell_corr_pairs, nullptr, nullptr, 0,
+                              pl->pick.first, ctx->err, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess)
     e = hipMemcpy(pl->hcount, pl->counts.p, sizeof(pl->hcount), hipMemcpyDeviceToHost);
@@ -1097,7 +1141,7 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
         pl->tuned_ms[b][v] = ms_best;
         if (ms_best < best) {
           best = ms_best;
-          pl->variant[b] = v;
+          pl->pick.v[b] = v;
         }
       }
     }
@@ -1112,17 +1156,10 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   // workspace of every chosen variant exists before capture (no allocation
   // while capturing)
   for (int b = 0; b < NBUCKET; ++b)
-    if (!ensure_big(ctx, pl->big, pl->mode, pl->variant[b])) {
+    if (!ensure_big(ctx, pl->big, pl->mode, pl->pick.v[b])) {
       mcc_plan_destroy(pl);
       return MCC_ERR_OOM;
     }
-  // the weights are bound to the plan: checked once here (positive and
-  // finite; a violation is latched as data error 4) and never again per step
-  e = launch_check_weights(n, weights, ctx->err, s);
-  if (e != hipSuccess) {
-    mcc_plan_destroy(pl);
-    return from_hip(e);
-  }
   // the weights are bound to the plan: their per-(cell, species) sums, range
   // and class, and the descending-weight order, are computed once here (with
   // the chosen variants, so the sums round as in a step) and read by every
@@ -1142,7 +1179,7 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
     W.stats = nullptr;
     W.cell_corr = nullptr;
     st = launch_buckets(ctx, pl->big, W, pl->mode, n_cells, pl->lists.as<int32_t>(),
-                        pl->counts.as<uint32_t>(), pl->variant, s, pl->hcount);
+                        pl->counts.as<uint32_t>(), pl->pick, s, pl->hcount);
     if (st == MCC_OK) st = from_hip(hipStreamSynchronize(s));
     if (st != MCC_OK) {
       mcc_plan_destroy(pl);
@@ -1195,8 +1232,8 @@ mcc_status mcc_plan_run_bucket(mcc_plan *pl, int32_t bucket, uint64_t step) {
   A.step_dev = nullptr;
   A.step = step;
   const mcc_status st = launch_bucket(pl->ctx, pl->big, A, pl->mode, pl->n_cells, pl->lists.as<int32_t>(),
-                                      pl->counts.as<uint32_t>(), bucket, pl->variant[bucket],
-                                      pl->ctx->stream);
+                                      pl->counts.as<uint32_t>(), bucket, pl->pick.v[bucket],
+                                      pl->hcount[bucket], pl->ctx->stream);
   if (st != MCC_OK) return st;
   return finish(pl->ctx);
 }
@@ -1208,13 +1245,13 @@ mcc_status mcc_plan_describe(mcc_plan *pl, char *buf, size_t len) {
   HIP_TRY(hipMemcpy(hc, pl->counts.p, sizeof(hc), hipMemcpyDeviceToHost));
   std::string out = "{\"buckets\": [";
   for (int b = 0; b < NBUCKET; ++b) {
-    const Variant V = variant_of(pl->mode, pl->variant[b]);
+    const Variant V = variant_of(pl->mode, pl->pick.v[b]);
     char tmp[512];
     std::snprintf(tmp, sizeof(tmp),
                   "%s{\"max_cell\": %d, \"cells\": %u, \"tpc\": %d, \"cap\": %d, \"layout\": %d, "
                   "\"grid\": %d, \"timed_ms\": {",
                   b ? ", " : "", kBucketCap[b], hc[b], V.tpc, V.cap, V.layout,
-                  grid_of(pl->ctx, pl->mode, pl->variant[b]));
+                  grid_of(pl->ctx, pl->mode, pl->pick.v[b]));
     out += tmp;
     bool first = true;
     for (int u = 0; u < NVARIANT; ++u) {

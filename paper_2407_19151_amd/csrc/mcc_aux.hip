@@ -11,24 +11,6 @@
 
 namespace mcc {
 
-__global__ void k_fill_u32(uint32_t *p, uint32_t v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-// weights must be positive and finite (a species' density is sum w / dV)
-__global__ void k_check_weights(int64_t n, const double *w, int32_t *err) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const double x = w[i];
-    if (!(x > 0.0) || x == __builtin_inf()) {
-      atomicCAS(err, 0, 4);
-      return;
-    }
-  }
-}
-
 __global__ void k_zero_stats(mcc_stats *s) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     s->pairs = s->corr_pairs = s->failed = s->collisions = 0ull;
@@ -53,49 +35,125 @@ __global__ void k_inc_u64(uint64_t *p) {
 
 // Work lists: cell c of size n goes to the first bucket whose capacity holds
 // it.  lists[b * n_cells + i], counts[b].  Empty cells get cell_corr = 0.
-// A workgroup counts its cells per bucket in LDS (one LDS atomic per wave and
-// bucket), reserves its slots with one global atomic per bucket, and each
-// wave writes its cells after its own slots: per-wave global atomics on the
-// seven counters would serialize the grid on them.
-__global__ void __launch_bounds__(256)
-    k_bucket_cells(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n,
-                   int32_t *lists, uint32_t *counts, int32_t *cell_corr, int32_t *err) {
-  __shared__ uint32_t lcount[NBUCKET], lbase[NBUCKET];
+// The bucket of cell c (none below `first`), or -1 where it takes no list entry.
+__device__ __forceinline__ int bucket_of_cell(const int64_t *offsets, int64_t c, int32_t S,
+                                              int64_t n, int first, int32_t *cell_corr,
+                                              int32_t *err) {
+  const int64_t b0 = offsets[c * S], b1 = offsets[(c + 1) * S];
+  const int64_t sz = b1 - b0;
+  if (b0 < 0 || b1 < b0 || b1 > n) {
+    atomicCAS(err, 0, 1);
+    return -1;
+  }
+  if (sz == 0) {
+    if (cell_corr) cell_corr[c] = 0;
+    return -1;
+  }
+  int b = first;
+  while (b < NBUCKET && sz > kBucketCap[b]) ++b;
+  if (b == NBUCKET) {
+    atomicCAS(err, 0, 2);
+    if (cell_corr) cell_corr[c] = 0;
+    return -1;
+  }
+  return b;
+}
+
+// the lane's slot among its workgroup's cells of bucket b: one LDS atomic per
+// wave and bucket, the lanes of a wave in order
+__device__ __forceinline__ uint32_t bucket_slot(int b, uint32_t *lcount) {
   const int lane = threadIdx.x & (WAVE - 1);
   const uint64_t below = (1ull << lane) - 1ull;
-  for (int64_t c0 = blockIdx.x * (int64_t)blockDim.x; c0 < n_cells;
-       c0 += (int64_t)gridDim.x * blockDim.x) {
+  uint32_t slot = 0;
+  for (int k = 0; k < NBUCKET; ++k) {
+    const uint64_t m = __ballot(b == k);
+    if (m == 0) continue;  // (uniform over the wave)
+    const int leader = __ffsll((unsigned long long)m) - 1;
+    uint32_t base = 0;
+    if (lane == leader) base = atomicAdd(&lcount[k], (uint32_t)__popcll(m));
+    base = __shfl(base, leader);
+    if (b == k) slot = base + (uint32_t)__popcll(m & below);
+  }
+  return slot;
+}
+
+// whether any of the weights w[i], i = i0, i0 + stride, ... < n is not
+// positive and finite: eight loads in flight per thread
+__device__ __forceinline__ bool bad_weights(int64_t n, const double *w, int64_t i0,
+                                            int64_t stride) {
+  bool bad = false;
+  int64_t i = i0;
+  for (; i + 7 * stride < n; i += 8 * stride) {
+    double x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = w[i + j * stride];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) bad |= !(x[j] > 0.0) || x[j] == __builtin_inf();
+  }
+  for (; i < n; i += stride) {
+    const double x = w[i];
+    bad |= !(x > 0.0) || x == __builtin_inf();
+  }
+  return bad;
+}
+
+// What every call without a plan does before its collide kernels: the
+// caller's statistics and `zero` cleared, the weights checked, and the cells
+// put on the work lists.  Three forms of the same work:
+//  - k_front_one: all of it in one workgroup, which needs no cleared counters
+//    and so no launch before it (a launch costs the host 4-5 us; this kernel
+//    takes 3 us at 3 200 particles, the four it replaces 12);
+//  - k_front_clear, then k_front over the grid, where one workgroup would
+//    take longer than the launch it saves.  The first cell_blocks workgroups
+//    of k_front list the cells (each counts its cells per bucket in LDS and
+//    reserves its slots with one global atomic per bucket), the others read
+//    the weights (HBM bound: 8 B per particle).
+constexpr int FRONT_TPB = 1024;
+__global__ void __launch_bounds__(FRONT_TPB)
+    k_front_one(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n, const double *w,
+                int32_t *lists, uint32_t *counts, int32_t *cell_corr, mcc_stats *stats,
+                double *zero, int64_t nzero, int first, int32_t *err) {
+  __shared__ uint32_t lcount[NBUCKET];
+  const int t = threadIdx.x;
+  if (t < NBUCKET) lcount[t] = 0u;
+  if (stats && t < (int)(sizeof(mcc_stats) / 8)) reinterpret_cast<uint64_t *>(stats)[t] = 0ull;
+  for (int64_t i = t; i < nzero; i += FRONT_TPB) zero[i] = 0.0;
+  __syncthreads();
+  for (int64_t c0 = 0; c0 < n_cells; c0 += FRONT_TPB) {
+    const int64_t c = c0 + t;
+    const int b = c < n_cells ? bucket_of_cell(offsets, c, S, n, first, cell_corr, err) : -1;
+    const uint32_t slot = bucket_slot(b, lcount);
+    if (b >= 0) lists[(int64_t)b * n_cells + slot] = (int32_t)c;
+  }
+  if (bad_weights(n, w, t, FRONT_TPB)) atomicCAS(err, 0, 4);
+  __syncthreads();
+  if (t < NBUCKET) counts[t] = lcount[t];
+}
+
+__global__ void k_front_clear(uint32_t *counts, mcc_stats *stats, double *zero, int64_t nzero) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i0 < NBUCKET) counts[i0] = 0u;
+  if (stats && i0 < (int64_t)(sizeof(mcc_stats) / 8))
+    reinterpret_cast<uint64_t *>(stats)[i0] = 0ull;
+  for (int64_t i = i0; i < nzero; i += (int64_t)gridDim.x * blockDim.x) zero[i] = 0.0;
+}
+
+__global__ void __launch_bounds__(256)
+    k_front(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n, const double *w,
+            int cell_blocks, int32_t *lists, uint32_t *counts, int32_t *cell_corr, int first,
+            int32_t *err) {
+  if ((int)blockIdx.x >= cell_blocks) {
+    const int64_t wb = blockIdx.x - cell_blocks, nb = gridDim.x - cell_blocks;
+    if (bad_weights(n, w, wb * 256 + threadIdx.x, nb * 256)) atomicCAS(err, 0, 4);
+    return;
+  }
+  __shared__ uint32_t lcount[NBUCKET], lbase[NBUCKET];
+  for (int64_t c0 = blockIdx.x * 256ll; c0 < n_cells; c0 += (int64_t)cell_blocks * 256) {
     if (threadIdx.x < NBUCKET) lcount[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t c = c0 + threadIdx.x;
-    int b = -1;  // this lane's bucket, or -1: no list entry
-    if (c < n_cells) {
-      const int64_t b0 = offsets[c * S], b1 = offsets[(c + 1) * S];
-      const int64_t sz = b1 - b0;
-      if (b0 < 0 || b1 < b0 || b1 > n) {
-        atomicCAS(err, 0, 1);
-      } else if (sz == 0) {
-        if (cell_corr) cell_corr[c] = 0;
-      } else {
-        b = 0;
-        while (b < NBUCKET && sz > kBucketCap[b]) ++b;
-        if (b == NBUCKET) {
-          atomicCAS(err, 0, 2);
-          if (cell_corr) cell_corr[c] = 0;
-          b = -1;
-        }
-      }
-    }
-    uint32_t slot = 0;  // the lane's slot among the workgroup's cells of bucket b
-    for (int k = 0; k < NBUCKET; ++k) {
-      const uint64_t m = __ballot(b == k);
-      if (m == 0) continue;  // (uniform over the wave)
-      const int leader = __ffsll((unsigned long long)m) - 1;
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(&lcount[k], (uint32_t)__popcll(m));
-      base = __shfl(base, leader);
-      if (b == k) slot = base + (uint32_t)__popcll(m & below);
-    }
+    const int b = c < n_cells ? bucket_of_cell(offsets, c, S, n, first, cell_corr, err) : -1;
+    const uint32_t slot = bucket_slot(b, lcount);
     __syncthreads();
     if (threadIdx.x < NBUCKET)
       lbase[threadIdx.x] =
@@ -476,18 +534,6 @@ static inline int grid_for(int64_t n, int tpb) {
   return (int)g;
 }
 
-hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n, 256)), dim3(256), 0, s, p, v, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_check_weights(int64_t n, const double *w, int32_t *err, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_check_weights, dim3(grid_for(n, 256)), dim3(256), 0, s, n, w, err);
-  return hipGetLastError();
-}
-
 hipError_t launch_zero_stats(mcc_stats *st, hipStream_t s) {
   hipLaunchKernelGGL(k_zero_stats, dim3(1), dim3(64), 0, s, st);
   return hipGetLastError();
@@ -509,12 +555,26 @@ hipError_t launch_inc_u64(uint64_t *p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_bucket_cells(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n,
-                               int32_t *lists, uint32_t *counts, int32_t *cell_corr, int32_t *err,
-                               hipStream_t s) {
-  if (n_cells <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bucket_cells, dim3(grid_for(n_cells, 256)), dim3(256), 0, s, offsets,
-                     n_cells, S, n, lists, counts, cell_corr, err);
+// one workgroup up to these sizes: 16 cells or 16 weights per thread, the
+// most whose passes stay under the cost of a second launch
+constexpr int64_t FRONT_ONE_CELLS = 16 * FRONT_TPB, FRONT_ONE_WEIGHTS = 16 * FRONT_TPB;
+
+hipError_t launch_front(const int64_t *offsets, int32_t n_cells, int32_t S, int64_t n,
+                        const double *w, int32_t *lists, uint32_t *counts, int32_t *cell_corr,
+                        mcc_stats *stats, double *zero, int64_t nzero, int first,
+                        int32_t *err, hipStream_t s) {
+  if (n_cells <= FRONT_ONE_CELLS && n <= FRONT_ONE_WEIGHTS) {
+    hipLaunchKernelGGL(k_front_one, dim3(1), dim3(FRONT_TPB), 0, s, offsets, n_cells, S, n, w,
+                       lists, counts, cell_corr, stats, zero, nzero, first, err);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(k_front_clear, dim3(grid_for(nzero / 4 + 1, 256)), dim3(256), 0, s, counts,
+                     stats, zero, nzero);
+  const int cb = n_cells > 0 ? grid_for(n_cells, 256) : 0;
+  const int wb = n > 0 ? (int)(n / 2048 + 1 < 8192 ? n / 2048 + 1 : 8192) : 0;
+  if (cb + wb > 0)
+    hipLaunchKernelGGL(k_front, dim3(cb + wb), dim3(256), 0, s, offsets, n_cells, S, n, w, cb,
+                       lists, counts, cell_corr, first, err);
   return hipGetLastError();
 }
 

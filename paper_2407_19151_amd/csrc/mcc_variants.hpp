@@ -74,9 +74,22 @@ constexpr int kBucketCap[NBUCKET] = {128, 256, 512, 1024, 2048, 4096, 32768};
 // one-wave variant, 1.5x the 4-wave)
 constexpr int kDefaultVariant[NBUCKET] = {0, 1, 3, 5, 7, 12, 15};
 constexpr int kDefaultVariantFP[NBUCKET] = {0, 1, 3, 5, 11, 12, 15};
+// With at most as many cells as the device has compute units, every cell has
+// a CU to itself: resident cells per CU no longer matter, the latency of one
+// cell does, and four waves per cell shorten it (16 cells, FP64 N97, kernel
+// time against the table above: 200 particles 35 against 45 us, 400 37
+// against 47, 60 35 against 31; eight waves for 1500: 63 against 81).  One
+// variant up to 1024 particles also lets a call without a plan launch one
+// kernel for the first four buckets (kFewBucket takes their cells).
+constexpr int kFewVariant[NBUCKET] = {5, 5, 5, 5, 7, 12, 15};
+constexpr int kFewBucket = 3;
+static_assert(kFewVariant[0] == kFewVariant[kFewBucket] &&
+                  kFewVariant[1] == kFewVariant[kFewBucket] &&
+                  kFewVariant[2] == kFewVariant[kFewBucket],
+              "the merged buckets share a variant");
 // candidates the autotuner times per bucket (-1 terminated)
 constexpr int kCandidates[NBUCKET][5] = {
-    {0, 1, 2, -1, -1}, {1, 2, 3, 4, -1}, {3, 4, 5, 6, -1}, {5, 6, 7, 11, -1},
+    {0, 1, 2, 5, -1}, {1, 2, 3, 4, 5}, {3, 4, 5, 6, -1}, {5, 6, 7, 11, -1},
     {7, 11, 8, -1, -1}, {12, 13, 9, -1, -1}, {15, 14, 10, -1, -1}};
 
 // the tangent form keeps six more doubles per particle and one per pair: in
@@ -91,8 +104,10 @@ inline constexpr Variant compact_of(Variant V) {
   return V.layout == 0 ? Variant{V.tpc, V.cap, 1} : V;
 }
 
-inline constexpr int default_variant(int mode, int bucket) {
-  return (base_mode(mode) == MODE_FP32 || mode == MODE_FP32_DIAG || base_mode(mode) == MODE_FP64 ||
+// few: no more cells than compute units
+inline constexpr int default_variant(int mode, int bucket, bool few) {
+  return few ? kFewVariant[bucket]
+         : (base_mode(mode) == MODE_FP32 || mode == MODE_FP32_DIAG || base_mode(mode) == MODE_FP64 ||
           mode == MODE_FP64_DIAG)
              ? kDefaultVariantFP[bucket]
              : kDefaultVariant[bucket];
