@@ -320,11 +320,13 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells,
  * is taken at its states and with its discrete choices and 23-bit uniforms;
  * the pair Jacobians are evaluated in FP64.  A reset (Sec. 6.2) collision
  * passes the adjoint through unchanged.
- * Scratch: per workgroup, 228 B per particle of capacity (4096, or
- * MCC_MAX_CELL for the cells above 4096): about 0.5 GB on 256 compute units
- * for cells up to 4096, 1.9 GB more once a cell above 4096 occurs; owned by
- * the context.  The call waits once on the context's stream (to read the
- * cell counts per size bucket) before it enqueues the kernels.
+ * Scratch: per workgroup, the records of up to six collisions (three above
+ * 1024 particles per cell) at 80 B per particle of capacity each, longer
+ * collision lists being taken in groups: at most 0.5 GB on 256 compute units
+ * for cells up to 1024, 0.7 GB for cells up to 4096, 2.7 GB more once a cell
+ * above 4096 occurs; owned by the context.  The call waits once on the
+ * context's stream (to read the cell counts per size bucket) before it
+ * enqueues the kernels.
  * Errors: MCC_ERR_UNSUPPORTED for the relativistic form, a pairing other
  * than ORDER_N, hard spheres or max_passes > 1.
  */

@@ -10,57 +10,83 @@
 // For an adjoint g of the step's output, this kernel returns g J (the
 // adjoint of the step's input) and g dv'/dlnL, cell by cell:
 //
-//   for each collision k, last to first:
-//     recompute the state at the start of collision k (collisions 0..k-1
-//     from the step's input), then collision k itself while recording the
-//     state before every scatter pair, the state after the momentum restore,
-//     and the correction's pair energies, cut pair and failure decision;
-//     sweep back: the pair corrections (disjoint pairs; the cut pair's U
-//     depends on Delta E_s and on the K of the pairs before it), the energy
-//     partition, the momentum restore, then the scatter chains in reverse.
+//   run the collisions forward, recording of each: the state at its start,
+//     after its momentum restore, and (where a chain changes it) before each
+//     scatter pair; its pairing; its correction pairs, their energies and the
+//     cut pair; and its failure decision;
+//   sweep back, last collision first: the pair corrections (disjoint pairs;
+//     the cut pair's U depends on Delta E_s and on the K of the pairs before
+//     it), the energy partition, the momentum restore, then the scatter
+//     chains in reverse.
 //
-// A pair's Jacobian d(du)/d(u, s) is built from the same tangent arithmetic
-// as the forward-mode form (rot_tangent), one column per basis direction.
-// The recomputed forward runs in the step's own precision form (FP32
-// kinematics or FP64) so that it takes the same discrete choices; the
-// Jacobians are evaluated in FP64 with that form's uniforms.  One workgroup
-// per cell, with the cell and its records in per-workgroup global scratch;
-// threads per cell as in the forward-mode kernels, so the per-cell sums
-// round, and the cut pair falls, as there.
+// A workgroup holds the records of up to `slots` collisions; a longer list is
+// taken in groups from its end, each group's start recomputed from the
+// step's input.  The forward runs in the step's own precision form (FP32
+// kinematics or FP64) so that it takes the same discrete choices; the pair
+// adjoints are evaluated in FP64 with that form's uniforms.  One workgroup
+// per cell, with the threads per cell of the forward-mode kernels, so the
+// per-cell sums round, and the cut pair falls, as there.
+//
+// Bound by the latency of the cell's phases.  Cells of up to 1024 particles
+// keep what is accessed through the lists (velocities, weights, adjoints) in
+// LDS, 70 B per particle of capacity, so that eight waves are resident per CU
+// (the registers allow no more), and only stream the records through the
+// per-workgroup global scratch: 1024 cells of 256 + 256, FP64, 136 us, against
+// 478 us with everything in global scratch, 512 two-wave workgroups, and the
+// collisions before k recomputed for each k.
 #include "mcc_adjoint_args.hpp"
 #include "mcc_collide.hpp"
 
 namespace mcc {
 
-// The adjoint of one scatter pair, given the pair's input velocities (pi, pj)
-// and the adjoints (gI, gJ) of its output, in place: gI, gJ become the
-// adjoints of its input; lbar gains the pair's part of the lnL adjoint.
+// Adjoint of a scatter pair: with u = v_I - v_J, the pair's update is
+// v_I += fa du (if accepted), v_J -= fb du (if accepted), du = du(u, s) the
+// rotation of u by the sampled angle and s = cf w_max / |u|^3.  Given the
+// adjoints (gI, gJ) of its output, returns the adjoint of u through du: the
+// input's adjoints are gI + it and gJ - it.  lbar gains the pair's part of
+// the lnL adjoint (s is proportional to lnL).
+struct PairBar {
+  double x, y, z;
+};
 template <typename KR>
-__device__ __attribute__((noinline)) void pair_adjoint(
-    double pix, double piy, double piz, double pjx, double pjy, double pjz, double wi, double wj,
-    uint32_t kp, double cf, double fa, double fb, int method, uint32_t cell, uint32_t step_lo,
-    uint32_t c3, uint32_t k0, uint32_t k1, const double2 *n97tab, double inv_lnl, double *gx,
-    double *gy, double *gz, int I, int J, double &lbar) {
+__device__ __forceinline__ PairBar pair_adjoint(
+    double ux, double uy, double uz, double wi, double wj, uint32_t kp, double cf, double fa,
+    double fb, int method, uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
+    const double2 *n97tab, double inv_lnl, double gIx, double gIy, double gIz, double gJx,
+    double gJy, double gJz, double &lbar) {
   using K = KMath<double>;
-  const double ux = pix - pjx, uy = piy - pjy, uz = piz - pjz;
   const double wmax = wi > wj ? wi : wj;
   // the primal's skips, in its own precision
   {
     const KR fx = (KR)ux, fy = (KR)uy, fz = (KR)uz;
     const KR f2 = fx * fx + fy * fy + fz * fz;
-    if (f2 == KR(0)) return;
+    if (f2 == KR(0)) return PairBar{0.0, 0.0, 0.0};
     const KR fs = KMath<KR>::div((KR)(cf * wmax), f2 * KMath<KR>::sqrt_(f2));
-    if (!(fs > KR(0))) return;
+    if (!(fs > KR(0))) return PairBar{0.0, 0.0, 0.0};
   }
-  const double um2 = ux * ux + uy * uy + uz * uz;
+  const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
+  const double u3 = unif64(r.w);
+  const double wratio = (wi < wj ? wi : wj) / wmax;
+  bool ai = true, aj = true;
+  if (wi < wj)
+    aj = u3 <= wratio;
+  else if (wj < wi)
+    ai = u3 <= wratio;
+  // adjoint of du
+  const double bx = (ai ? fa * gIx : 0.0) - (aj ? fb * gJx : 0.0);
+  const double by = (ai ? fa * gIy : 0.0) - (aj ? fb * gJy : 0.0);
+  const double bz = (ai ? fa * gIz : 0.0) - (aj ? fb * gJz : 0.0);
+  if (bx == 0.0 && by == 0.0 && bz == 0.0) return PairBar{0.0, 0.0, 0.0};
+  const double up2 = ux * ux + uy * uy;
+  const double um2 = up2 + uz * uz;
   const double um = K::sqrt_(um2);
   const double s = (cf * wmax) / (um2 * um);
-  const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
   // the form's uniforms (the FP32 form draws 23-bit ones)
   const double u0 = (double)KMath<KR>::u(r.x), u1 = (double)KMath<KR>::u(r.y);
   const double u2 = (double)KMath<KR>::u(r.z);
-  double oc, st, A = 0.0;
-  if (method == 0) {
+  // the angle and d(1 - cos)/ds
+  double oc, st, ocs = 0.0;
+  if (method == 0) {  // TA77: delta = tan(theta/2) scales as sqrt(s)
     const double z = sqrt(-2.0 * log(u0)) * cospi(2.0 * u1);
     const double delta = sqrt(0.5 * s) * z;
     const double d2 = delta * delta;
@@ -71,59 +97,67 @@ __device__ __attribute__((noinline)) void pair_adjoint(
       const double q = 1.0 / (1.0 + d2);
       st = 2.0 * delta * q;
       oc = 2.0 * d2 * q;
+      ocs = oc * q / s;  // 2 q^2 d(delta^2)/ds, d(delta^2)/ds = delta^2 / s
     }
-  } else {
-    A = n97_A_fast<double>(s, n97tab);
+  } else {  // N97: dA/ds = -exp(-s) / L'(A)
+    const double A = n97_A_fast<double>(s, n97tab);
+    const double e = expm1(-2.0 * A), den = 1.0 + u0 * e;
     if (__builtin_isinf(A))
       oc = 0.0;
     else if (A == 0.0)
       oc = 2.0 * u0;
     else
-      oc = -log1p(u0 * expm1(-2.0 * A)) / A;
+      oc = -log1p(u0 * e) / A;
     oc = oc < 0.0 ? 0.0 : (oc > 2.0 ? 2.0 : oc);
     st = sqrt(oc * (2.0 - oc));
+    if (A > 0.0 && !__builtin_isinf(A) && oc > 0.0 && oc < 2.0)
+      ocs = (2.0 * u0 * (e + 1.0) / den - oc) / A * (-exp(-s) / langevin_prime(A));
   }
   double sp, cp;
   sincospi(2.0 * u2, &sp, &cp);
-  const double u3 = unif64(r.w);
-  const double wratio = (wi < wj ? wi : wj) / wmax;
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wratio;
-  else if (wj < wi)
-    ai = u3 <= wratio;
-  // v_I' = v_I + fa du (if accepted), v_J' = v_J - fb du: adjoint of du
-  const double dbx = (ai ? fa * gx[I] : 0.0) - (aj ? fb * gx[J] : 0.0);
-  const double dby = (ai ? fa * gy[I] : 0.0) - (aj ? fb * gy[J] : 0.0);
-  const double dbz = (ai ? fa * gz[I] : 0.0) - (aj ? fb * gz[J] : 0.0);
-  if (dbx == 0.0 && dby == 0.0 && dbz == 0.0) return;
-  // columns of d(du)/du (s follows |u|: ds = -3 s (u . du) / |u|^2), then
-  // d(du)/dlnL (ds = s / lnL)
-  double ub[3];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const double ui = i == 0 ? ux : (i == 1 ? uy : uz);
-    double tx, ty, tz;
-    rot_tangent(method, ux, uy, uz, um, s, oc, st, sp, cp, u0, A, i == 0 ? 1.0 : 0.0,
-                i == 1 ? 1.0 : 0.0, i == 2 ? 1.0 : 0.0, -3.0 * s * ui / um2, tx, ty, tz);
-    ub[i] = tx * dbx + ty * dby + tz * dbz;
+  // du (rotate_delta) in reverse: adjoints of 1 - cos, sin, |u| and u
+  const double stc = st * cp, sts = st * sp;
+  double ocb, stb, umb, vx, vy, vz;
+  if (up2 > 0.0) {
+    const double up = K::sqrt_(up2), iup = 1.0 / up;
+    const double ax = ux * iup, ay = uy * iup;
+    const double al = ax * bx + ay * by, cr = ax * by - ay * bx;
+    ocb = -(ux * bx + uy * by + uz * bz);
+    stb = cp * (uz * al - up * bz) + sp * um * cr;
+    umb = sts * cr;
+    const double axb = uz * stc * bx + um * sts * by, ayb = uz * stc * by - um * sts * bx;
+    const double upb = -stc * bz - (axb * ax + ayb * ay) * iup;
+    vx = axb * iup - oc * bx + upb * ax;
+    vy = ayb * iup - oc * by + upb * ay;
+    vz = stc * al - oc * bz;
+  } else {
+    const double al = cp * bx + sp * by;
+    ocb = -uz * bz;
+    stb = um * al;
+    umb = st * al;
+    vx = 0.0;
+    vy = 0.0;
+    vz = -oc * bz;
   }
-  if (inv_lnl != 0.0) {
-    double tx, ty, tz;
-    rot_tangent(method, ux, uy, uz, um, s, oc, st, sp, cp, u0, A, 0.0, 0.0, 0.0, s * inv_lnl, tx,
-                ty, tz);
-    lbar += tx * dbx + ty * dby + tz * dbz;
-  }
-  gx[I] += ub[0];
-  gy[I] += ub[1];
-  gz[I] += ub[2];
-  gx[J] -= ub[0];
-  gy[J] -= ub[1];
-  gz[J] -= ub[2];
+  if (st != 0.0) ocb += stb * (1.0 - oc) / st;  // st^2 = oc (2 - oc), either sign of st
+  const double sb = ocb * ocs;                  // adjoint of s
+  lbar += sb * s * inv_lnl;
+  // |u| through the rotation and through s: ds = -3 s (u . du) / |u|^2
+  const double c = umb / um - 3.0 * s * sb / um2;
+  return PairBar{vx + c * ux, vy + c * uy, vz + c * uz};
 }
 
-template <int TPC, int CAP, typename KR>
-__global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
+// What a recorded collision leaves for its reverse sweep beside its slot's
+// arrays
+struct AdjRec {
+  double dE, ea, eb, D, res0, res1;
+  int nc0, nc1, fail;
+};
+
+// GLOB: the cell lives in the per-workgroup global scratch (cells above 1024
+// particles), else in LDS
+template <int TPC, int CAP, typename KR, bool GLOB>
+__global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs A) {
   constexpr int PPT = CAP / TPC;
   constexpr int NW = TPC / WAVE;
   static_assert(CAP % TPC == 0 && TPC % WAVE == 0, "bad variant");
@@ -140,48 +174,72 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
   __shared__ int s_ncut[2];
   __shared__ double s_res[2];
   __shared__ double s_ubar[2];
+  __shared__ AdjRec s_rec[ADJ_MAX_SLOTS];
   __shared__ __attribute__((aligned(16))) uint32_t lcnt[CAP + 2];
 
-  char *base = A.scratch + (uint64_t)blockIdx.x * A.stride;
-  double *dv = reinterpret_cast<double *>(base);
+  char *const base = A.scratch + (uint64_t)blockIdx.x * A.stride;
+  // record slots: 9 arrays of CAP doubles (state at the collision's start,
+  // after its momentum restore, and the shared particle's before each pair),
+  // the odd triple's pairs, the correction pairs (energies and members), and
+  // the shuffled lists
+  struct Slot {
+    double *b, *q, *p, *odd, *kb;
+    uint32_t *pq;
+    uint16_t *list;
+  };
+  auto slot_of = [&](int i) -> Slot {
+    double *d = reinterpret_cast<double *>(base + (uint64_t)i * adj_slot_bytes(CAP));
+    Slot s;
+    s.b = d;
+    s.q = d + 3 * CAP;
+    s.p = d + 6 * CAP;
+    s.odd = d + 9 * CAP;
+    s.kb = s.odd + 32;
+    s.pq = reinterpret_cast<uint32_t *>(s.kb + CAP / 2);
+    s.list = reinterpret_cast<uint16_t *>(s.pq + CAP / 2);
+    return s;
+  };
   CellMem M;
-  M.vx = dv;
-  M.vy = dv + CAP;
-  M.vz = dv + 2 * CAP;
-  double *const W = dv + 3 * CAP;
+  double *W, *GX, *GY, *GZ;  // weights, and the adjoint being swept back
+  if constexpr (!GLOB) {
+    __shared__ double lv[7 * CAP];
+    __shared__ __attribute__((aligned(16))) uint16_t lidx[5 * CAP + 4];
+    M.vx = lv;
+    W = lv + 3 * CAP;
+    GX = lv + 4 * CAP;
+    M.list0 = lidx;
+    M.ord0 = lidx + CAP;
+    M.ord1 = lidx + 2 * CAP;
+    M.mem = lidx + 3 * CAP;
+    M.word = lidx + 4 * CAP;
+    // shuffle keys in the orders (dead until the weight order), pair energies
+    // in the bucket counters (dead after it)
+    M.key = reinterpret_cast<uint32_t *>(lidx + CAP);
+    M.kbuf = reinterpret_cast<double *>(lcnt);
+    M.slotbuf = nullptr;
+  } else {
+    double *dv = reinterpret_cast<double *>(base + (uint64_t)A.slots * adj_slot_bytes(CAP));
+    M.vx = dv;
+    W = dv + 3 * CAP;
+    GX = dv + 4 * CAP;
+    M.kbuf = dv + 7 * CAP;  // CAP / 2 doubles
+    M.key = reinterpret_cast<uint32_t *>(M.kbuf + CAP / 2);
+    M.slotbuf = M.key + CAP;
+    uint16_t *ix = reinterpret_cast<uint16_t *>(M.slotbuf + CAP);
+    M.list0 = ix;
+    M.ord0 = ix + CAP;
+    M.ord1 = ix + 2 * CAP;
+    M.mem = ix + 3 * CAP;
+    M.word = ix + 4 * CAP;
+  }
+  M.vy = M.vx + CAP;
+  M.vz = M.vx + 2 * CAP;
   M.w = W;
-  M.bx = dv + 4 * CAP;  // state at the collision's start
-  M.by = dv + 5 * CAP;
-  M.bz = dv + 6 * CAP;
-  double *const GX = dv + 7 * CAP;  // the adjoint being swept back
-  double *const GY = dv + 8 * CAP;
-  double *const GZ = dv + 9 * CAP;
-  double *const QX = dv + 10 * CAP;  // state after the momentum restore
-  double *const QY = dv + 11 * CAP;
-  double *const QZ = dv + 12 * CAP;
-  double *const XX = dv + 13 * CAP;  // the step's input
-  double *const XY = dv + 14 * CAP;
-  double *const XZ = dv + 15 * CAP;
-  double *const PIX = dv + 16 * CAP;  // input state of scatter pair kp
-  double *const PIY = dv + 17 * CAP;
-  double *const PIZ = dv + 18 * CAP;
-  double *const PJX = dv + 19 * CAP;
-  double *const PJY = dv + 20 * CAP;
-  double *const PJZ = dv + 21 * CAP;
-  M.kbuf = dv + 22 * CAP;
-  double *const HX = dv + 23 * CAP;  // adjoint of the collision's start state
-  double *const HY = dv + 24 * CAP;  // through the energy and momentum sums
-  double *const HZ = dv + 25 * CAP;
-  M.key = reinterpret_cast<uint32_t *>(dv + 26 * CAP);
-  M.slotbuf = M.key + CAP;
-  uint16_t *ix = reinterpret_cast<uint16_t *>(M.slotbuf + CAP);
-  M.list0 = ix;
-  M.list1 = ix + CAP;
-  M.ord0 = ix + 2 * CAP;
-  M.ord1 = ix + 3 * CAP;
-  M.mem = ix + 4 * CAP;
-  M.word = ix + 5 * CAP;
+  GY = GX + CAP;
+  GZ = GX + 2 * CAP;
   M.cnt = lcnt;
+  M.list1 = nullptr;
+  M.bx = M.by = M.bz = nullptr;
   M.tx = M.ty = M.tz = M.btx = M.bty = M.btz = M.kdot = nullptr;
 
   const int t = threadIdx.x;
@@ -216,11 +274,15 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
     const int64_t cb = uni(s_cb);
     const int n = uni(s_so[S]);
     const double dV = A.cell_volume ? A.cell_volume[cell] : A.dV;
+    auto load_state = [&]() {
+      for (int e = t; e < n; e += TPC) {
+        M.vx[e] = A.vx[cb + e];
+        M.vy[e] = A.vy[cb + e];
+        M.vz[e] = A.vz[cb + e];
+      }
+    };
     for (int e = t; e < n; e += TPC) {
       W[e] = A.w[cb + e];
-      XX[e] = A.vx[cb + e];
-      XY[e] = A.vy[cb + e];
-      XZ[e] = A.vz[cb + e];
       GX[e] = A.gx[cb + e];
       GY[e] = A.gy[cb + e];
       GZ[e] = A.gz[cb + e];
@@ -247,7 +309,8 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
         block_minmax_u64<TPC, 1>(lo, hi, redu);
         int flag = WORDER_EQUAL;
         if (A.sortw && ns >= 2 && lo[0] != hi[0]) {
-          weight_sort<TPC, PPT, true>(M, ns, nullptr, o, M.word + o, lo[0], hi[0], wsum, &maxocc);
+          weight_sort<TPC, PPT, GLOB>(M, ns, nullptr, o, M.word + o, lo[0], hi[0], wsum,
+                                      &maxocc);
           int tie = 0;
           for (int q = t; q + 1 < ns; q += TPC)
             if (W[M.word[o + q]] == W[M.word[o + q + 1]]) tie = 1;
@@ -264,18 +327,11 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       __syncthreads();
     }
 
-    // what the recorded collision leaves for its reverse sweep
-    struct Rec {
-      double dE, ea, eb, D;
-      int nc0, nc1;
-      double res0, res1;
-      bool fail;
-      const uint16_t *O0, *O1;
-    } R{};
-
     // one collision of the step on M.vx/vy/vz (the step's arithmetic, the
-    // choices it takes included); rec: keep what the reverse sweep needs
-    auto fwd = [&](int k, bool rec) {
+    // choices it takes included); rec: keep in slot sl what the reverse sweep
+    // needs
+    auto fwd = [&](int k, bool rec, int sl) {
+      const Slot R = slot_of(sl);
       const int a = A.coll[k].a, b = A.coll[k].b;
       const bool intra = a == b;
       const int oa = uni(s_so[a]), na = uni(s_so[a + 1]) - oa;
@@ -284,21 +340,24 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       const double ma = A.mass[a], mb = A.mass[b];
       auto in_a = [&](int e) { return (unsigned)(e - oa) < (unsigned)na; };
       auto part = [&](int e) { return in_a(e) || (!intra && (unsigned)(e - ob) < (unsigned)nb); };
-      for (int e = t; e < n; e += TPC)
-        if (part(e)) {
-          M.bx[e] = M.vx[e];
-          M.by[e] = M.vy[e];
-          M.bz[e] = M.vz[e];
-        }
+      // the state at the collision's start goes to the slot in every case; the
+      // sums below read it from there
+      for (int e = t; e < n; e += TPC) {
+        R.b[e] = M.vx[e];
+        R.b[CAP + e] = M.vy[e];
+        R.b[2 * CAP + e] = M.vz[e];
+      }
       if (intra)
-        shuffle_species<TPC, PPT, true>(M, na, oa, (uint32_t)cell, step_lo,
+        shuffle_species<TPC, PPT, GLOB>(M, na, oa, (uint32_t)cell, step_lo,
                                         ctr3(A.step, k, PURPOSE_SHUFFLE0 + 0), k0, k1, M.list0,
                                         wsum, &maxocc);
       else
-        shuffle_two<TPC, PPT, true>(M, na, oa, nb, ob, (uint32_t)cell, step_lo,
+        shuffle_two<TPC, PPT, GLOB>(M, na, oa, nb, ob, (uint32_t)cell, step_lo,
                                     ctr3(A.step, k, PURPOSE_SHUFFLE0 + 0),
                                     ctr3(A.step, k, PURPOSE_SHUFFLE0 + 1), k0, k1, M.list0,
                                     wsum, &maxocc);
+      if (rec)
+        for (int i = t; i < na + (intra ? 0 : nb); i += TPC) R.list[i] = M.list0[i];
       const uint16_t *L0 = M.list0, *L1 = M.list0 + na;
       const uint32_t c3p = ctr3(A.step, k, PURPOSE_PAIR);
       const bool abig = na >= nb;
@@ -318,6 +377,14 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
               J = L0[r == 2 ? 0 : r + 1];
               kp = (uint32_t)r;
               f = 0.5;
+              if (rec) {
+                R.odd[6 * r] = M.vx[I];
+                R.odd[6 * r + 1] = M.vy[I];
+                R.odd[6 * r + 2] = M.vz[I];
+                R.odd[6 * r + 3] = M.vx[J];
+                R.odd[6 * r + 4] = M.vy[J];
+                R.odd[6 * r + 5] = M.vz[J];
+              }
             } else if (odd) {
               I = L0[3 + 2 * (ch - 1)];
               J = L0[4 + 2 * (ch - 1)];
@@ -332,14 +399,12 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
             I = abig ? L0[kk] : L0[ch];
             J = abig ? L1[ch] : L1[kk];
             kp = (uint32_t)kk;
-          }
-          if (rec) {
-            PIX[kp] = M.vx[I];
-            PIY[kp] = M.vy[I];
-            PIZ[kp] = M.vz[I];
-            PJX[kp] = M.vx[J];
-            PJY[kp] = M.vy[J];
-            PJZ[kp] = M.vz[J];
+            if (rec && r > 0) {  // (before a chain's first pair: the start state)
+              const int sh = abig ? J : I;
+              R.p[kk] = M.vx[sh];
+              R.p[CAP + kk] = M.vy[sh];
+              R.p[2 * CAP + kk] = M.vz[sh];
+            }
           }
           const double cf = C.coef * f * nmin_dv;
           if constexpr (sizeof(KR) == 8)
@@ -351,16 +416,20 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
         }
       }
       __syncthreads();
-      if (!A.corr) return;
+      if (!A.corr) {
+        if (rec && t == 0) s_rec[sl].fail = 0;
+        return;
+      }
       // momentum restore, Eq. (17)
       double P[3] = {0.0, 0.0, 0.0};
-      for (int e = t; e < n; e += TPC)
+      for_owned<TPC, PPT, !GLOB>(n, [&](int j, int e) {
         if (part(e)) {
           const double mp = (in_a(e) ? ma : mb) * W[e];
-          P[0] += mp * (M.vx[e] - M.bx[e]);
-          P[1] += mp * (M.vy[e] - M.by[e]);
-          P[2] += mp * (M.vz[e] - M.bz[e]);
+          P[0] += mp * (M.vx[e] - R.b[e]);
+          P[1] += mp * (M.vy[e] - R.b[CAP + e]);
+          P[2] += mp * (M.vz[e] - R.b[2 * CAP + e]);
         }
+      });
       double tot[3];
       block_sum<TPC, 3>(P, red, tot);
       const double D = ma * s_sw2[a] + (intra ? 0.0 : mb * s_sw2[b]);
@@ -368,7 +437,7 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       // energy violation, Eq. (18), and the species energies of Eq. (24)
       double es = 0.0, ec = 0.0;
       double Ev[2] = {0.0, 0.0};
-      for (int e = t; e < n; e += TPC)
+      for_owned<TPC, PPT, !GLOB>(n, [&](int j, int e) {
         if (part(e)) {
           const bool isa = in_a(e);
           const double we = W[e];
@@ -378,17 +447,18 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
           M.vy[e] = vy;
           M.vz[e] = vz;
           if (rec) {
-            QX[e] = vx;
-            QY[e] = vy;
-            QZ[e] = vz;
+            R.q[e] = vx;
+            R.q[CAP + e] = vy;
+            R.q[2 * CAP + e] = vz;
           }
-          const double ox = M.bx[e], oy = M.by[e], oz = M.bz[e];
+          const double ox = R.b[e], oy = R.b[CAP + e], oz = R.b[2 * CAP + e];
           const double dd = (vx - ox) * (vx + ox) + (vy - oy) * (vy + oy) + (vz - oz) * (vz + oz);
           csum_add(es, ec, 0.5 * mp * dd);
           const double ke = 0.5 * mp * (vx * vx + vy * vy + vz * vz);
           Ev[0] += isa ? ke : 0.0;
           Ev[1] += isa ? 0.0 : ke;
         }
+      });
       double dE, et[2];
       block_sum_c1<TPC, 2>(es, ec, Ev, red, dE, et);
       double dEs0 = dE, dEs1 = 0.0, ea = 0.0, eb = 0.0;
@@ -406,7 +476,7 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
           const int f = s_wflag[sp];
           if (f == WORDER_EQUAL) return L;
           if (f == WORDER_DISTINCT) return (const uint16_t *)(M.word + o);
-          weight_sort<TPC, PPT, true>(M, ns, L, 0, ord, s_wlo[sp], s_whi[sp], wsum, &maxocc);
+          weight_sort<TPC, PPT, GLOB>(M, ns, L, 0, ord, s_wlo[sp], s_whi[sp], wsum, &maxocc);
           return (const uint16_t *)ord;
         };
         O0 = order(a, oa, na, L0, M.ord0);
@@ -469,11 +539,16 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       for (int m = t; m < nc0 + nc1; m += TPC) {
         const bool s1 = m >= nc0;
         const int mm = s1 ? m - nc0 : m;
-        const double U = Kb[(s1 ? base1 : 0) + mm];
-        if (U == 0.0) continue;
+        const int at = (s1 ? base1 : 0) + mm;
+        const double U = Kb[at];
         const uint16_t *O = s1 ? O1 : O0;
-        const double ms = s1 ? mb : ma;
         const int p = O[2 * mm], q = O[2 * mm + 1];
+        if (rec) {
+          R.kb[at] = U;
+          R.pq[at] = (uint32_t)p | ((uint32_t)q << 16);
+        }
+        if (U == 0.0) continue;
+        const double ms = s1 ? mb : ma;
         const double m1 = ms * W[p], m2 = ms * W[q];
         const double mu = m1 * m2 / (m1 + m2);
         const double rx = M.vx[p] - M.vx[q], ry = M.vy[p] - M.vy[q], rz = M.vz[p] - M.vz[q];
@@ -492,31 +567,23 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       __syncthreads();
       const bool fail = res0 != 0.0 || res1 != 0.0;
       if (fail && !A.keep)
-        for (int e = t; e < n; e += TPC)
+        for_owned<TPC, PPT, !GLOB>(n, [&](int j, int e) {
           if (part(e)) {
-            M.vx[e] = M.bx[e];
-            M.vy[e] = M.by[e];
-            M.vz[e] = M.bz[e];
+            M.vx[e] = R.b[e];
+            M.vy[e] = R.b[CAP + e];
+            M.vz[e] = R.b[2 * CAP + e];
           }
-      if (rec) {
-        R.dE = dE;
-        R.ea = ea;
-        R.eb = eb;
-        R.D = D;
-        R.nc0 = nc0;
-        R.nc1 = nc1;
-        R.res0 = res0;
-        R.res1 = res1;
-        R.fail = fail;
-        R.O0 = O0;
-        R.O1 = O1;
-      }
+        });
+      if (rec && t == 0) s_rec[sl] = AdjRec{dE, ea, eb, D, res0, res1, nc0, nc1, fail ? 1 : 0};
       __syncthreads();
     };
 
-    // the reverse sweep of collision k (recorded by fwd(k, true)): GX/GY/GZ,
-    // the adjoint of the collision's output, becomes that of its input
-    auto rev = [&](int k, double &lbar) {
+    // the reverse sweep of collision k (recorded by fwd in slot sl): GX/GY/GZ,
+    // the adjoint of the collision's output, becomes that of its input; the
+    // velocities are overwritten with the collision's start state
+    auto rev = [&](int k, int sl, double &lbar) {
+      const Slot R = slot_of(sl);
+      const AdjRec &Z = s_rec[sl];
       const int a = A.coll[k].a, b = A.coll[k].b;
       const bool intra = a == b;
       const int oa = uni(s_so[a]), na = uni(s_so[a + 1]) - oa;
@@ -525,24 +592,30 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
       const double ma = A.mass[a], mb = A.mass[b];
       auto in_a = [&](int e) { return (unsigned)(e - oa) < (unsigned)na; };
       auto part = [&](int e) { return in_a(e) || (!intra && (unsigned)(e - ob) < (unsigned)nb); };
-      if (R.fail && !A.keep) return;  // Sec. 6.2 reset: the output is the input
+      if (Z.fail && !A.keep) return;  // Sec. 6.2 reset: the output is the input
+      const double *QX = R.q, *QY = R.q + CAP, *QZ = R.q + 2 * CAP;
+      for (int e = t; e < n; e += TPC) {
+        M.vx[e] = R.b[e];
+        M.vy[e] = R.b[CAP + e];
+        M.vz[e] = R.b[2 * CAP + e];
+      }
+      double dEbar = 0.0, Bb[3] = {0.0, 0.0, 0.0};
       if (A.corr) {
         const int nsl = intra ? 1 : 2;
         const int base1 = na / 2;
-        const double *Kb = M.kbuf;
         // the cut pair of each species: adjoint of its U (before any pair's
         // adjoint changes GX/GY/GZ)
         if (t < 2) {
           double ub = 0.0;
-          const double res = t == 0 ? R.res0 : R.res1;
-          const int nc = t == 0 ? R.nc0 : R.nc1;
+          const double res = t == 0 ? Z.res0 : Z.res1;
+          const int nc = t == 0 ? Z.nc0 : Z.nc1;
           if (t < nsl && res == 0.0 && nc > 0) {
-            const int c = nc - 1;
-            const double U = Kb[(t ? base1 : 0) + c];
+            const int at = (t ? base1 : 0) + nc - 1;
+            const double U = R.kb[at];
             if (U != 0.0) {
-              const uint16_t *O = t ? R.O1 : R.O0;
+              const uint32_t pq = R.pq[at];
+              const int p = pq & 0xFFFFu, q = pq >> 16;
               const double ms = t ? mb : ma;
-              const int p = O[2 * c], q = O[2 * c + 1];
               const double m1 = ms * W[p], m2 = ms * W[q];
               const double mu = m1 * m2 / (m1 + m2);
               const double rx = QX[p] - QX[q], ry = QY[p] - QY[q], rz = QZ[p] - QZ[q];
@@ -562,15 +635,16 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
         // before the cut has U/K = +-f_E (g fixed); the cut pair's g moves
         // with its K and with U = Delta E_s - sum over earlier pairs of
         // +-f_E K, whose K then carry -+f_E times the adjoint of U.
-        const int nc0 = R.nc0, nc1 = R.nc1;
+        const int nc0 = Z.nc0, nc1 = Z.nc1;
         for (int m = t; m < nc0 + nc1; m += TPC) {
           const bool s1 = m >= nc0;
           const int mm = s1 ? m - nc0 : m;
-          const double U = Kb[(s1 ? base1 : 0) + mm];
+          const int at = (s1 ? base1 : 0) + mm;
+          const double U = R.kb[at];
           if (U == 0.0) continue;
-          const uint16_t *O = s1 ? R.O1 : R.O0;
+          const uint32_t pq = R.pq[at];
+          const int p = pq & 0xFFFFu, q = pq >> 16;
           const double ms = s1 ? mb : ma;
-          const int p = O[2 * mm], q = O[2 * mm + 1];
           const double m1 = ms * W[p], m2 = ms * W[q];
           const double mu = m1 * m2 / (m1 + m2);
           const double rx = QX[p] - QX[q], ry = QY[p] - QY[q], rz = QZ[p] - QZ[q];
@@ -581,7 +655,7 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
           const double a1 = mu / m1, a2 = mu / m2;
           const double dx = a1 * GX[p] - a2 * GX[q], dy = a1 * GY[p] - a2 * GY[q],
                        dz = a1 * GZ[p] - a2 * GZ[q];
-          const double res = s1 ? R.res1 : R.res0;
+          const double res = s1 ? Z.res1 : Z.res0;
           const int nc = s1 ? nc1 : nc0;
           double Kbar = 0.0;
           if (res == 0.0) {
@@ -606,53 +680,49 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
         // energy violation (difference form of Eq. (18)) and partition
         // (Eq. (24)): the cut pairs' U adjoints are those of Delta E_s
         const double ua = s_ubar[0], ubb = nsl == 2 ? s_ubar[1] : 0.0;
-        double dEbar = 0.0, kina = 0.0, kinb = 0.0;
+        double kina = 0.0, kinb = 0.0;
         if (intra) {
           dEbar = ua;
-        } else if (R.dE != 0.0) {
-          const double Ssum = R.ea + R.eb;
-          dEbar = ua * (R.ea / Ssum) + ubb * (R.eb / Ssum);
-          const double eabar = R.dE * (ua - ubb) * R.eb / (Ssum * Ssum);
-          const double ebbar = -R.dE * (ua - ubb) * R.ea / (Ssum * Ssum);
+        } else if (Z.dE != 0.0) {
+          const double Ssum = Z.ea + Z.eb;
+          dEbar = ua * (Z.ea / Ssum) + ubb * (Z.eb / Ssum);
+          const double eabar = Z.dE * (ua - ubb) * Z.eb / (Ssum * Ssum);
+          const double ebbar = -Z.dE * (ua - ubb) * Z.ea / (Ssum * Ssum);
           kina = eabar * (s_sw[a] / na);
           kinb = ebbar * (s_sw[b] / nb);
         }
         // Delta E = sum 1/2 m (|q|^2 - |b|^2), E_s = sum over s of 1/2 m |q|^2:
         // q (after the restore) takes (dEbar + kin_s) m q, b takes -dEbar m b
+        // (at the end)
         double P[3] = {0.0, 0.0, 0.0};
         for (int e = t; e < n; e += TPC)
           if (part(e)) {
             const bool isa = in_a(e);
             const double mp = (isa ? ma : mb) * W[e];
             const double cq = (dEbar + (isa ? kina : kinb)) * mp;
-            GX[e] += cq * QX[e];
-            GY[e] += cq * QY[e];
-            GZ[e] += cq * QZ[e];
-            HX[e] = -dEbar * mp * M.bx[e];
-            HY[e] = -dEbar * mp * M.by[e];
-            HZ[e] = -dEbar * mp * M.bz[e];
+            const double gx = GX[e] + cq * QX[e], gy = GY[e] + cq * QY[e],
+                         gz = GZ[e] + cq * QZ[e];
+            GX[e] = gx;
+            GY[e] = gy;
+            GZ[e] = gz;
             // momentum restore, q = v_ps - B w: adjoint of B is -sum w g_q
-            P[0] -= W[e] * GX[e];
-            P[1] -= W[e] * GY[e];
-            P[2] -= W[e] * GZ[e];
+            P[0] -= W[e] * gx;
+            P[1] -= W[e] * gy;
+            P[2] -= W[e] * gz;
           }
-        double Bb[3];
         block_sum<TPC, 3>(P, red, Bb);
         // B = sum m (v_ps - b) / D: v_ps takes Bbar m / D, b takes -Bbar m / D
         for (int e = t; e < n; e += TPC)
           if (part(e)) {
-            const double c = (in_a(e) ? ma : mb) * W[e] / R.D;
+            const double c = (in_a(e) ? ma : mb) * W[e] / Z.D;
             GX[e] += Bb[0] * c;
             GY[e] += Bb[1] * c;
             GZ[e] += Bb[2] * c;
-            HX[e] -= Bb[0] * c;
-            HY[e] -= Bb[1] * c;
-            HZ[e] -= Bb[2] * c;
           }
-        __syncthreads();
       }
+      __syncthreads();
       // the scatter: chains of pairs (one lane each), last pair first
-      const uint16_t *L0 = M.list0, *L1 = M.list0 + na;
+      const uint16_t *L0 = R.list, *L1 = R.list + na;
       const uint32_t c3p = ctr3(A.step, k, PURPOSE_PAIR);
       const bool abig = na >= nb;
       const int Nmax = abig ? na : nb, Nmin = abig ? nb : na;
@@ -665,63 +735,85 @@ __global__ void __launch_bounds__(TPC) adjoint_kernel(AdjointArgs A) {
           int I, J;
           uint32_t kp;
           double f = 1.0;
-          if (intra) {
-            if (odd && ch == 0) {
-              I = L0[r];
-              J = L0[r == 2 ? 0 : r + 1];
-              kp = (uint32_t)r;
-              f = 0.5;
-            } else if (odd) {
-              I = L0[3 + 2 * (ch - 1)];
-              J = L0[4 + 2 * (ch - 1)];
-              kp = (uint32_t)(3 + ch - 1);
-            } else {
-              I = L0[2 * ch];
-              J = L0[2 * ch + 1];
-              kp = (uint32_t)ch;
-            }
+          double ux, uy, uz;
+          if (odd && ch == 0) {
+            I = L0[r];
+            J = L0[r == 2 ? 0 : r + 1];
+            kp = (uint32_t)r;
+            f = 0.5;
+            ux = R.odd[6 * r] - R.odd[6 * r + 3];
+            uy = R.odd[6 * r + 1] - R.odd[6 * r + 4];
+            uz = R.odd[6 * r + 2] - R.odd[6 * r + 5];
           } else {
-            const int kk = r * Nmin + ch;
-            I = abig ? L0[kk] : L0[ch];
-            J = abig ? L1[ch] : L1[kk];
-            kp = (uint32_t)kk;
+            if (intra) {
+              const int m = odd ? 3 + 2 * (ch - 1) : 2 * ch;
+              I = L0[m];
+              J = L0[m + 1];
+              kp = (uint32_t)(odd ? 2 + ch : ch);
+            } else {
+              const int kk = r * Nmin + ch;
+              I = abig ? L0[kk] : L0[ch];
+              J = abig ? L1[ch] : L1[kk];
+              kp = (uint32_t)kk;
+            }
+            double ix = M.vx[I], iy = M.vy[I], iz = M.vz[I];
+            double jx = M.vx[J], jy = M.vy[J], jz = M.vz[J];
+            if (!intra && r > 0) {
+              const double px = R.p[kp], py = R.p[CAP + kp], pz = R.p[2 * CAP + kp];
+              if (abig) {
+                jx = px;
+                jy = py;
+                jz = pz;
+              } else {
+                ix = px;
+                iy = py;
+                iz = pz;
+              }
+            }
+            ux = ix - jx;
+            uy = iy - jy;
+            uz = iz - jz;
           }
-          pair_adjoint<KR>(PIX[kp], PIY[kp], PIZ[kp], PJX[kp], PJY[kp], PJZ[kp], W[I], W[J], kp,
-                           C.coef * f * nmin_dv, C.fa, C.fb, A.method, (uint32_t)cell, step_lo,
-                           c3p, k0, k1, A.n97, A.inv_lnl, GX, GY, GZ, I, J, lbar);
+          const PairBar u = pair_adjoint<KR>(ux, uy, uz, W[I], W[J], kp, C.coef * f * nmin_dv,
+                                             C.fa, C.fb, A.method, (uint32_t)cell, step_lo, c3p,
+                                             k0, k1, A.n97, A.inv_lnl, GX[I], GY[I], GZ[I],
+                                             GX[J], GY[J], GZ[J], lbar);
+          GX[I] += u.x;
+          GY[I] += u.y;
+          GZ[I] += u.z;
+          GX[J] -= u.x;
+          GY[J] -= u.y;
+          GZ[J] -= u.z;
         }
       }
       __syncthreads();
+      // the start state's adjoint through the energy and momentum sums
       if (A.corr)
         for (int e = t; e < n; e += TPC)
           if (part(e)) {
-            GX[e] += HX[e];
-            GY[e] += HY[e];
-            GZ[e] += HZ[e];
+            const double mp = (in_a(e) ? ma : mb) * W[e], c = mp / Z.D;
+            GX[e] += -dEbar * mp * M.vx[e] - Bb[0] * c;
+            GY[e] += -dEbar * mp * M.vy[e] - Bb[1] * c;
+            GZ[e] += -dEbar * mp * M.vz[e] - Bb[2] * c;
           }
       __syncthreads();
     };
 
-    double lbar = 0.0;
-    for (int k = A.n_coll - 1; k >= 0; --k) {
+    auto has_pairs = [&](int k) {
       const int a = A.coll[k].a, b = A.coll[k].b;
       const int na = uni(s_so[a + 1]) - uni(s_so[a]), nb = uni(s_so[b + 1]) - uni(s_so[b]);
-      if (a == b ? na < 2 : (na == 0 || nb == 0)) continue;  // no pairs: the identity
-      for (int e = t; e < n; e += TPC) {
-        M.vx[e] = XX[e];
-        M.vy[e] = XY[e];
-        M.vz[e] = XZ[e];
-      }
+      return a == b ? na >= 2 : (na > 0 && nb > 0);
+    };
+    double lbar = 0.0;
+    for (int k1_ = A.n_coll; k1_ > 0;) {
+      const int kg = k1_ > A.slots ? k1_ - A.slots : 0;  // the group [kg, k1_)
+      load_state();
       __syncthreads();
-      for (int j = 0; j < k; ++j) {
-        const int aj = A.coll[j].a, bj = A.coll[j].b;
-        const int nja = uni(s_so[aj + 1]) - uni(s_so[aj]);
-        const int njb = uni(s_so[bj + 1]) - uni(s_so[bj]);
-        if (aj == bj ? nja < 2 : (nja == 0 || njb == 0)) continue;
-        fwd(j, false);
-      }
-      fwd(k, true);
-      rev(k, lbar);
+      for (int k = 0; k < k1_; ++k)
+        if (has_pairs(k)) fwd(k, k >= kg, k >= kg ? k - kg : 0);
+      for (int k = k1_ - 1; k >= kg; --k)
+        if (has_pairs(k)) rev(k, k - kg, lbar);
+      k1_ = kg;
     }
     double acc[1] = {lbar}, tot[1];
     block_sum<TPC, 1>(acc, red, tot);
@@ -745,24 +837,53 @@ __global__ void __launch_bounds__(1024) k_sum_f64(const double *x, int64_t n, do
   if (threadIdx.x == 0) out[0] = tot[0];
 }
 
-// kernels per (threads per cell, capacity) of the forward-mode variants
+// the kernel of a bucket (largest cell `most`) at the forward-mode variant's
+// threads per cell: in LDS up to 1024 particles, above that in global scratch
 template <typename KR>
-const void *adjoint_kernel_of(int tpc, int cap) {
-  if (cap > 4096) return reinterpret_cast<const void *>(&adjoint_kernel<64, 32768, KR>);
-  if (tpc >= 256) return reinterpret_cast<const void *>(&adjoint_kernel<256, 4096, KR>);
-  if (tpc >= 128) return reinterpret_cast<const void *>(&adjoint_kernel<128, 4096, KR>);
-  return reinterpret_cast<const void *>(&adjoint_kernel<64, 4096, KR>);
+const void *adjoint_kernel_of(int tpc, int most, int &cap, int &threads) {
+  auto is = [&](int c, int n) {
+    cap = c;
+    threads = n;
+  };
+  if (most > 4096) {
+    is(32768, 64);
+    return reinterpret_cast<const void *>(&adjoint_kernel<64, 32768, KR, true>);
+  }
+  if (tpc >= 256 && most <= 1024) {
+    is(1024, 256);
+    return reinterpret_cast<const void *>(&adjoint_kernel<256, 1024, KR, false>);
+  }
+  if (tpc >= 128 && most <= 512) {
+    is(512, 128);
+    return reinterpret_cast<const void *>(&adjoint_kernel<128, 512, KR, false>);
+  }
+  if (tpc == 64 && most <= 128) {
+    is(128, 64);
+    return reinterpret_cast<const void *>(&adjoint_kernel<64, 128, KR, false>);
+  }
+  if (tpc == 64 && most <= 256) {
+    is(256, 64);
+    return reinterpret_cast<const void *>(&adjoint_kernel<64, 256, KR, false>);
+  }
+  is(4096, 64);
+  return reinterpret_cast<const void *>(&adjoint_kernel<64, 4096, KR, true>);
 }
 
-hipError_t launch_adjoint(const AdjointArgs &base, bool fp32, const int32_t *lists,
-                          const uint32_t *counts, int32_t n_cells, int b, int tpc, int cap,
-                          int grid, hipStream_t s) {
+AdjointKernel adjoint_kernel_for(bool fp32, int tpc, int most) {
+  AdjointKernel k;
+  k.fn = fp32 ? adjoint_kernel_of<float>(tpc, most, k.cap, k.tpc)
+              : adjoint_kernel_of<double>(tpc, most, k.cap, k.tpc);
+  return k;
+}
+
+hipError_t launch_adjoint(const AdjointKernel &k, const AdjointArgs &base, const int32_t *lists,
+                          const uint32_t *counts, int32_t n_cells, int b, int grid,
+                          hipStream_t s) {
   AdjointArgs A = base;
   A.cell_list = lists + (int64_t)b * (n_cells > 0 ? n_cells : 1);
   A.cell_count = counts + b;
   void *kargs[] = {&A};
-  const void *k = fp32 ? adjoint_kernel_of<float>(tpc, cap) : adjoint_kernel_of<double>(tpc, cap);
-  return hipLaunchKernel(k, dim3(grid), dim3(tpc), kargs, 0, s);
+  return hipLaunchKernel(k.fn, dim3(grid), dim3(k.tpc), kargs, 0, s);
 }
 
 hipError_t launch_sum_f64(const double *x, int64_t n, double *out, hipStream_t s) {

@@ -29,13 +29,33 @@ struct AdjointArgs {
   double *lnl_part;  // [n_cells]: per-cell adjoint of lnL
   int32_t *err;
   const double2 *n97;
-  char *scratch;
+  char *scratch;    // per-workgroup scratch, `stride` bytes each
   uint64_t stride;
+  int32_t slots;    // record slots in it
 };
 
-// per-workgroup scratch: 26 doubles, 2 u32 and 6 u16 per particle of capacity
-constexpr unsigned long long adj_stride_bytes(int cap) {
-  return ((unsigned long long)cap * (26 * 8 + 2 * 4 + 6 * 2) + 255ull) & ~255ull;
+// record slots per workgroup: the collisions a forward pass records before
+// the sweep back over them (longer lists are taken in groups).  Six cover
+// three species; three for the large-cell scratch, whose slots are 2.6 MB.
+constexpr int ADJ_MAX_SLOTS = 6, ADJ_BIG_SLOTS = 3;
+
+// one record slot: 9 doubles, half a double, half a u32 and a u16 per
+// particle of capacity, and 32 doubles
+constexpr unsigned long long adj_slot_bytes(int cap) {
+  return ((unsigned long long)cap * (9 * 8 + 4 + 2 + 2) + 32 * 8 + 255ull) & ~255ull;
 }
+// per-workgroup scratch: the slots, and for the cells in global scratch 7.5
+// doubles, 2 u32 and 5 u16 per particle of capacity
+constexpr unsigned long long adj_stride_bytes(int cap, int slots, bool global) {
+  return adj_slot_bytes(cap) * (unsigned)slots +
+         (global ? (((unsigned long long)cap * (7 * 8 + 4 + 2 * 4 + 5 * 2) + 255ull) & ~255ull)
+                 : 0ull);
+}
+
+// a compiled reverse-mode kernel: its capacity and threads per cell
+struct AdjointKernel {
+  const void *fn = nullptr;
+  int cap = 0, tpc = 0;
+};
 
 }  // namespace mcc

@@ -68,9 +68,11 @@ hipError_t launch_gather(int64_t n, const int32_t *perm, const double *w, const 
                          const double *vy, const double *vz, double *gw, double *gx, double *gy,
                          double *gz, hipStream_t s);
 struct AdjointArgs;
-hipError_t launch_adjoint(const AdjointArgs &base, bool fp32, const int32_t *lists,
-                          const uint32_t *counts, int32_t n_cells, int b, int tpc, int cap,
-                          int grid, hipStream_t s);
+struct AdjointKernel;
+AdjointKernel adjoint_kernel_for(bool fp32, int tpc, int most);
+hipError_t launch_adjoint(const AdjointKernel &k, const AdjointArgs &base, const int32_t *lists,
+                          const uint32_t *counts, int32_t n_cells, int b, int grid,
+                          hipStream_t s);
 hipError_t launch_sum_f64(const double *x, int64_t n, double *out, hipStream_t s);
 }  // namespace mcc
 #include "mcc_adjoint_args.hpp"
@@ -833,21 +835,29 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
     uint32_t hc[NBUCKET];
     HIP_TRY(hipMemcpyAsync(hc, ctx->counts.p, sizeof(hc), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    const bool fp32 = p->precision == MCC_FP32_KINEMATICS;
     for (int b = 0; b < NBUCKET; ++b) {
       if (hc[b] == 0) continue;
       // threads per cell of the forward-mode variant of the bucket, so the
       // per-cell sums (and the choices they decide) round as there
-      const Variant V = variant_of(MODE_TAN, pick.v[b]);
-      const bool big = kBucketCap[b] > 4096;
-      const int tpc = big ? 64 : V.tpc;
-      const int cap = big ? MCC_MAX_CELL : 4096;
-      const int grid = (int)std::min<uint32_t>(hc[b], (uint32_t)(big ? ctx->n_cu : ctx->n_cu * 2));
+      const AdjointKernel K =
+          adjoint_kernel_for(fp32, variant_of(MODE_TAN, pick.v[b]).tpc, kBucketCap[b]);
+      const bool big = K.cap > 4096, global = K.cap > 1024;
+      int occ = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, K.fn, K.tpc, 0) != hipSuccess ||
+          occ < 1)
+        occ = 1;
+      // (as many workgroups of the global form as before the records of a
+      // whole step were kept: its scratch is 1.3 MB and 10 MB each)
+      if (global) occ = big ? 1 : 2;
+      const int grid = (int)std::min<uint32_t>(hc[b], (uint32_t)(ctx->n_cu * occ));
       DevBuf &buf = big ? ctx->adj_big : ctx->adj_small;
-      A.stride = adj_stride_bytes(cap);
+      A.slots = std::min(std::max(n_coll, 1), global ? ADJ_BIG_SLOTS : ADJ_MAX_SLOTS);
+      A.stride = adj_stride_bytes(K.cap, A.slots, global);
       if (!buf.ensure(A.stride * (uint64_t)grid)) return MCC_ERR_OOM;
       A.scratch = buf.as<char>();
-      HIP_TRY(launch_adjoint(A, p->precision == MCC_FP32_KINEMATICS, ctx->lists.as<int32_t>(),
-                             ctx->counts.as<uint32_t>(), n_cells, b, tpc, cap, grid, s));
+      HIP_TRY(launch_adjoint(K, A, ctx->lists.as<int32_t>(), ctx->counts.as<uint32_t>(), n_cells,
+                             b, grid, s));
     }
   }
   if (g_coulomb_log)
