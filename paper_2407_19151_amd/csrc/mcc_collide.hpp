@@ -668,10 +668,10 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
   // their room would cost a resident cell per CU (read from HBM there)
   constexpr bool W_LDS = LAY != LAYOUT_COMPACT || CAP <= 1024;
   // pairs of intra-species collisions run as one pass (not in the tangent,
-  // relativistic, diagnostic and N x N forms)
+  // diagnostic and N x N forms)
   constexpr bool NXN = PAIRING == PAIR_NXN;
   constexpr bool DUP = PAIRING == PAIR_DUPLICITY;
-  constexpr bool DUAL = !TAN && !REL && !DIAG && PAIRING == PAIR_ORDER_N;
+  constexpr bool DUAL = !TAN && !DIAG && PAIRING == PAIR_ORDER_N;
   static_assert(PAIRING == PAIR_ORDER_N || !(TAN || DIAG),
                 "the N x N and duplicity pairings have no tangent or diagnostic form");
   static_assert(!GL || TPC <= 512, "the global layout runs at most 8 waves per cell");
@@ -1216,10 +1216,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
               // (the pairs of its fewer-population particle)
               if (!intra) cf = Cs.coef * ((double)Nmax / dV) / (double)len;
             }
-            if constexpr (REL)
-              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, ma, mb, A.c, A.method,
-                               (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
-            else if constexpr (TAN)
+            if constexpr (REL) {
+              const double mI = sb ? mb : ma;
+              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+            } else if constexpr (TAN)
               scatter_pair_nr_tan(M.vx, M.vy, M.vz, M.tx, M.ty, M.tz, M.w, I, J, kp, cf, C.fa, C.fb,
                                   A.method, (uint32_t)cell, step_lo, c3p, k0, k1, A.n97, A.dlnl);
             else if constexpr (sizeof(KR) == 8)
@@ -1462,7 +1463,6 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
       }
       double *Kb = M.kbuf;
       const int base1 = na / 2;           // pair slots of the second species
-      double *Xb = Kb + CAP / 2;          // REL: h(-mu_R) per pair
       double resid0 = dEs0, resid1 = dEs1;
       double tresid0 = tdEs0, tresid1 = tdEs1;  // tangent form
       int used_total = 0;
@@ -1470,10 +1470,10 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
         if (resid0 == 0.0 && resid1 == 0.0) break;
         MCC_PHASE(5);  // pair energies
         // K of every pair; pairs are disjoint, so each K is the value the
-        // sequential loop of Alg. 1 sees.  In the plain non-relativistic
-        // form the cut-off computes K itself, 64 pairs at a time and only up
-        // to the cut pair (usually within the first 64).
-        constexpr bool KCUT = !REL && !TAN;
+        // sequential loop of Alg. 1 sees.  Except in the tangent form the
+        // cut-off computes K itself, 64 pairs at a time and only up to the
+        // cut pair (usually within the first 64).
+        constexpr bool KCUT = !TAN;
         const int np0 = (!KCUT && resid0 != 0.0) ? na / 2 : 0;
         const int np1 = (!KCUT && nsl == 2 && resid1 != 0.0) ? nb / 2 : 0;
         for (int m = t; m < np0 + np1; m += TPC) {
@@ -1484,52 +1484,77 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
           const int slot = (s1 ? base1 : 0) + mm;
           const int p = O[2 * mm], q = O[2 * mm + 1];
           const double m1 = ms * M.w[p], m2 = ms * M.w[q];
-          if constexpr (REL) {
-            Kb[slot] = pair_K_rel(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q],
-                                  A.c);
-            RelPair R;
-            R.init(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q], A.c);
-            double dh;
-            Xb[slot] = R.h0(-R.mu(), dh);
-          } else {
-            Kb[slot] = pair_K_nr(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q]);
-            if constexpr (TAN) {
-              const double mu = m1 * m2 / (m1 + m2);
-              M.kdot[slot] = mu * ((M.vx[p] - M.vx[q]) * (M.tx[p] - M.tx[q]) +
-                                   (M.vy[p] - M.vy[q]) * (M.ty[p] - M.ty[q]) +
-                                   (M.vz[p] - M.vz[q]) * (M.tz[p] - M.tz[q]));
-            }
+          Kb[slot] = pair_K_nr(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q]);
+          if constexpr (TAN) {
+            const double mu = m1 * m2 / (m1 + m2);
+            M.kdot[slot] = mu * ((M.vx[p] - M.vx[q]) * (M.tx[p] - M.tx[q]) +
+                                 (M.vy[p] - M.vy[q]) * (M.ty[p] - M.ty[q]) +
+                                 (M.vz[p] - M.vz[q]) * (M.tz[p] - M.tz[q]));
           }
         }
         if constexpr (!KCUT) __syncthreads();
         MCC_PHASE(6);  // sequential cut-off loop
+        const int lane = t & (WAVE - 1);
         if constexpr (REL) {
-          // the running violation, in the paper's order (one lane per species):
-          // whether a pair can take U depends on the running value itself
-          const int sl = (t == 0) ? 0 : ((NW > 1 && t == WAVE) ? 1 : -1);
-          for (int s2 = (NW > 1 ? sl : 0); s2 >= 0 && s2 < nsl; s2 += (NW > 1 ? nsl : 1)) {
-            if (NW == 1 && t != 0) break;
-            double E = s2 == 0 ? resid0 : resid1;
+          // The running violation, in the paper's order: whether a pair can
+          // take U depends on the running value itself.  One wave per
+          // species evaluates 64 pairs at a time and then walks through
+          // them, every lane alike, until nothing is left (usually a few
+          // pairs: evaluating every pair beforehand took a quarter of the
+          // step).
+          auto cutoff = [&](int s2) {
+            double E = uni(s2 == 0 ? resid0 : resid1);
             const int np = (s2 == 0 ? na : nb) / 2, kb = s2 == 0 ? 0 : base1;
-            int m = 0, used = 0;
-            for (; m < np; ++m) {
-              if (E == 0.0) break;
-              const double K = Kb[kb + m];
-              double U = 0.0;
-              if (K != 0.0) {
-                const double lim = A.fE * K;
-                U = fabs(E) < lim ? E : copysign(lim, E);
-                if (U > 0.0 && Xb[kb + m] + U > 0.0) U = 0.0;  // no root: skip the pair
+            const bool down = E > 0.0;  // (E keeps its sign)
+            int ncut = 0, used = 0;
+            for (int m0 = 0; m0 < np && E != 0.0; m0 += WAVE) {
+              const int m = m0 + lane;
+              double K = 0.0, X = 0.0;  // X: h(-mu_R), the most a pair can give up
+              if (m < np) {
+                const uint16_t *O = s2 ? O1 : O0;
+                const double ms = s2 ? mb : ma;
+                const int p = O[2 * m], q = O[2 * m + 1];
+                const double m1 = ms * M.w[p], m2 = ms * M.w[q];
+                K = pair_K_rel(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q],
+                               A.c);
+                if (down) {
+                  RelPair R;
+                  R.init(m1, m2, M.vx[p], M.vy[p], M.vz[p], M.vx[q], M.vy[q], M.vz[q], A.c);
+                  double dh;
+                  X = R.h0(-R.mu(), dh);
+                }
               }
-              Kb[kb + m] = U;
-              if (U != 0.0) {
-                E -= U;
-                ++used;
+              const int last = np - m0 < WAVE ? np - m0 : WAVE;
+              double mine = 0.0;
+              int i = 0;
+              for (; i < last && E != 0.0; ++i) {
+                const double Ki = wave_bcast(K, i);
+                double U = 0.0;
+                if (Ki != 0.0) {
+                  const double lim = A.fE * Ki;
+                  U = fabs(E) < lim ? E : copysign(lim, E);
+                  if (U > 0.0 && wave_bcast(X, i) + U > 0.0) U = 0.0;  // no root: skip the pair
+                }
+                if (lane == i) mine = U;
+                if (U != 0.0) {
+                  E = uni(E - U);
+                  ++used;
+                }
               }
+              if (lane < i) Kb[kb + m] = mine;
+              ncut = m0 + i;
             }
-            s_ncut[s2] = m;
-            s_res[s2] = E;
-            s_used[s2] = used;
+            if (lane == 0) {
+              s_ncut[s2] = ncut;
+              s_res[s2] = E;
+              s_used[s2] = used;
+            }
+          };
+          if constexpr (NW > 1) {
+            if (t / WAVE < nsl) cutoff(t / WAVE);
+          } else {
+            cutoff(0);
+            if (nsl == 2) cutoff(1);
           }
         } else {
           // The running violation E of one species, one wave per species.
@@ -1537,7 +1562,6 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
           // smaller than f_E K of the next pair, which takes the remainder
           // (Eq. (23)); that pair is the first whose inclusive prefix sum of
           // f_E K reaches |E|.  The prefix sums run over 64 pairs at a time.
-          const int lane = t & (WAVE - 1);
           auto cutoff = [&](int s2) {
             const double E0 = s2 == 0 ? resid0 : resid1;
             const double sgn = E0 < 0.0 ? -1.0 : 1.0;
