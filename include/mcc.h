@@ -177,9 +177,7 @@ mcc_status mcc_device_error(mcc_ctx *ctx, int32_t *code);
  * 9 (1024,4096), 10 (64,32768, one wave with global scratch), 11 (256,2048),
  * 12 (512,4096), 13 (256,4096), 14 (256,32768) and 15 (512,32768) (four and
  * eight waves with global scratch; the diagnostic and tangent forms run them
- * as 10).  In relativistic mode 9, 12 and 13 run in
- * global scratch: as (256,4096), four waves, in the order-N step, and as
- * (64,4096), one wave, in its diagnostic, N x N and duplicity forms.  -1 restores the default, which depends on
+ * as 10).  -1 restores the default, which depends on
  * the precision mode and on whether n_cells exceeds the device's compute
  * units (built-in tables, the fastest measured on lognormal cell-size mixes
  * and on few cells).  The variant's capacity must hold the bucket's largest cell,
@@ -414,9 +412,8 @@ mcc_status mcc_rebin_out(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t n_spe
  * alone (per cell and species: sum w, sum w^2, the weight range, and the
  * descending-weight order of Algorithm 1), owning 40 B per (cell, species)
  * and 2 B per particle of device memory for it.  A plan whose cells need the
- * large-cell kernels (above 4096 particles, or above 2048 in relativistic
- * mode) owns their global scratch too, 2.75 MB per compute unit for cells
- * above 4096 particles (0.34 MB up to 4096), held until mcc_plan_destroy:
+ * large-cell kernels (above 4096 particles) owns their global scratch too,
+ * 2.75 MB per compute unit, held until mcc_plan_destroy:
  * its graph replays against that scratch, so later calls on the context
  * (which grow the context's own scratch) never move it.  A plan shares the
  * context's cell-queue counters and error word, so its replays must not

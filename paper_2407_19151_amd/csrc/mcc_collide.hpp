@@ -659,7 +659,6 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
   constexpr bool GL = LAY == LAYOUT_GLOBAL;
   constexpr bool BIG = GL;  // snapshot in memory, runtime owner loops
   static_assert(CAP % TPC == 0 && TPC % WAVE == 0, "bad variant");
-  static_assert(!(REL && LAY == LAYOUT_COMPACT), "REL needs the full pair buffer");
   // the descending-weight order has an LDS home up to 1024 particles in the
   // compact layout (above, its room would cost a second resident cell per
   // CU); there a plan's order is read from HBM

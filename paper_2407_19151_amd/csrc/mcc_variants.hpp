@@ -28,14 +28,6 @@ enum Mode {
   NMODE = 13
 };
 
-// the order-N mode whose variants and defaults another pairing's mode shares
-inline constexpr int base_mode(int mode) {
-  return (mode == MODE_FP64_NXN || mode == MODE_FP64_DUP)   ? MODE_FP64
-         : (mode == MODE_FP32_NXN || mode == MODE_FP32_DUP) ? MODE_FP32
-         : (mode == MODE_REL_NXN || mode == MODE_REL_DUP)   ? MODE_REL
-                                                             : mode;
-}
-
 // layout: 0 all in LDS; 1 compact LDS (weights read from the input);
 // 2 per-workgroup global scratch (one wave per cell, or several waves for
 // the plain FP64 and FP32 modes)
@@ -54,26 +46,20 @@ constexpr Variant kVariants[NVARIANT] = {
 // the one-wave global variant, which the modes without multi-wave global
 // kernels use in place of variants 14 and 15
 constexpr int kGlobalOneWave = 10;
-// the relativistic mode keeps a per-pair h(-mu) buffer, which the compact
-// layout has no room for: its 4096-cell variants use global scratch
-constexpr Variant kRelVariant4096 = {64, 4096, 2};
-// the same with 4 waves per cell, for the relativistic order-N step (8 waves
-// would cap the registers at 256 and spill)
-constexpr Variant kRelVariant4096Wide = {256, 4096, 2};
 
 // cell-size buckets: bucket b holds cells with kBucketCap[b-1] < n <= kBucketCap[b]
 constexpr int NBUCKET = 7;
 constexpr int kBucketCap[NBUCKET] = {128, 256, 512, 1024, 2048, 4096, 32768};
 // default variant per bucket (the fastest measured on lognormal cell-size
-// mixes; the autotuner may pick another candidate).  The FP32 and FP64 modes
+// mixes; the autotuner may pick another candidate).  The compact layouts
 // take 256 threads for the 2048 bucket (under the 2-wave register cap the
 // FP64 512-thread kernel holds one workgroup per CU: 0.55 against 0.43 ms on
-// the 65,536-cell mix); the relativistic and tangent modes, whose cells keep
-// the full LDS layout, 512.  Cells above 4096 particles take 8 waves in
+// the 65,536-cell mix); the tangent mode, whose cells keep the full LDS
+// layout, has its own large-cell variant.  Cells above 4096 particles take 8 waves in
 // global scratch (measured on cells of 4 400 to 8 200 particles: 5.1-5.3x the
 // one-wave variant, 1.5x the 4-wave)
-constexpr int kDefaultVariant[NBUCKET] = {0, 1, 3, 5, 7, 12, 15};
-constexpr int kDefaultVariantFP[NBUCKET] = {0, 1, 3, 5, 11, 12, 15};
+constexpr int kDefaultVariant[NBUCKET] = {0, 1, 3, 5, 11, 12, 15};
+constexpr int kDefaultVariantTan[NBUCKET] = {0, 1, 3, 5, 7, 12, 15};
 // With at most as many cells as the device has compute units, every cell has
 // a CU to itself: resident cells per CU no longer matter, the latency of one
 // cell does, and four waves per cell shorten it (16 cells, FP64 N97, kernel
@@ -96,10 +82,12 @@ constexpr int kCandidates[NBUCKET][5] = {
 // LDS up to 1024 particles, above that in global scratch
 constexpr Variant kTanVariantBig = {64, 4096, 2};
 
-// The FP64 and FP32 modes run every LDS variant in the compact layout
-// (weights read from HBM, keys and pair energies aliased: 40-42 B of LDS per
-// particle of capacity instead of 56, so more cells are resident per CU); the
-// relativistic and tangent modes keep the full layout.
+// Every mode but the tangent form runs every LDS variant in the compact
+// layout (weights read from HBM, keys and pair energies aliased: 40-42 B of
+// LDS per particle of capacity instead of 56, so more cells are resident per
+// CU; relativistic cells of 576 + 448: 484 us per step of 4096
+// cells at three waves per SIMD, 593 in the full layout at two; cells of 3000:
+// 254 us per 400 in LDS, 608 in global scratch).
 inline constexpr Variant compact_of(Variant V) {
   return V.layout == 0 ? Variant{V.tpc, V.cap, 1} : V;
 }
@@ -107,10 +95,8 @@ inline constexpr Variant compact_of(Variant V) {
 // few: no more cells than compute units
 inline constexpr int default_variant(int mode, int bucket, bool few) {
   return few ? kFewVariant[bucket]
-         : (base_mode(mode) == MODE_FP32 || mode == MODE_FP32_DIAG || base_mode(mode) == MODE_FP64 ||
-          mode == MODE_FP64_DIAG)
-             ? kDefaultVariantFP[bucket]
-             : kDefaultVariant[bucket];
+         : mode == MODE_TAN ? kDefaultVariantTan[bucket]
+                            : kDefaultVariant[bucket];
 }
 
 // multi-wave global-scratch kernels: the FP64, FP32 and relativistic modes
@@ -121,18 +107,13 @@ inline constexpr bool multiwave_global(int m) {
          m == MODE_FP32_NXN || m == MODE_REL_NXN || m == MODE_FP64_DUP || m == MODE_FP32_DUP ||
          m == MODE_REL_DUP;
 }
-inline constexpr Variant variant_of(int m, int v) {
-  const int mode = base_mode(m);
-  return (kVariants[v].layout == 2 && kVariants[v].tpc > 64 && !multiwave_global(m))
-             ? variant_of(m, kGlobalOneWave)
-         : ((mode == MODE_REL || mode == MODE_REL_DIAG) && kVariants[v].layout == 1)
-             ? (m == MODE_REL ? kRelVariant4096Wide : kRelVariant4096)
+inline constexpr Variant variant_of(int mode, int v) {
+  return (kVariants[v].layout == 2 && kVariants[v].tpc > 64 && !multiwave_global(mode))
+             ? kVariants[kGlobalOneWave]
          : (mode == MODE_TAN && kVariants[v].cap > 1024 && kVariants[v].layout != 2)
              ? kTanVariantBig
-         : (mode == MODE_FP64 || mode == MODE_FP32 || mode == MODE_FP64_DIAG ||
-            mode == MODE_FP32_DIAG)
-             ? compact_of(kVariants[v])
-             : kVariants[v];
+         : mode == MODE_TAN ? kVariants[v]
+                            : compact_of(kVariants[v]);
 }
 
 // Minimum waves per SIMD the compiler must leave room for (it then caps the
