@@ -666,11 +666,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
   // weights: in LDS except in the compact layout above 1024 particles, where
   // their room would cost a resident cell per CU (read from HBM there)
   constexpr bool W_LDS = LAY != LAYOUT_COMPACT || CAP <= 1024;
-  // pairs of intra-species collisions run as one pass (not in the tangent,
-  // diagnostic and N x N forms)
+  // pairs of intra-species collisions run as one pass (not in the tangent and
+  // diagnostic forms)
   constexpr bool NXN = PAIRING == PAIR_NXN;
   constexpr bool DUP = PAIRING == PAIR_DUPLICITY;
-  constexpr bool DUAL = !TAN && !DIAG && PAIRING == PAIR_ORDER_N;
+  constexpr bool DUAL = !TAN && !DIAG;
   static_assert(PAIRING == PAIR_ORDER_N || !(TAN || DIAG),
                 "the N x N and duplicity pairings have no tangent or diagnostic form");
   static_assert(!GL || TPC <= 512, "the global layout runs at most 8 waves per cell");
@@ -1021,7 +1021,10 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
       if constexpr (DUAL) {
         if (intra && k + 1 < A.n_coll) {
           const int a2 = uni(A.coll[k + 1].a);
-          if (a2 == uni(A.coll[k + 1].b) && a2 != a && uni(s_so[a2 + 1]) - uni(s_so[a2]) >= 2) {
+          const int n2 = uni(s_so[a2 + 1]) - uni(s_so[a2]);
+          // (N x N: only where the rounds of both fit the workgroup's lanes)
+          if (a2 == uni(A.coll[k + 1].b) && a2 != a && n2 >= 2 &&
+              (!NXN || (na + 1) / 2 + (n2 + 1) / 2 <= TPC)) {
             dual = true;
             b = a2;
             kn = k + 2;
@@ -1114,48 +1117,65 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
         //         (i + r) mod N_max; N_max rounds of min(N_a, N_b) pairs,
         //         visited from the shorter list
         // kp = r * P + slot, P = np / 2 (intra) or N_a (inter).
-        const double cf = C.coef / dV;
-        const int np = na + (na & 1), R = intra ? np - 1 : Nmax;
-        const int P = intra ? np / 2 : na;
-        const int per = intra ? np / 2 : Nmin;  // slots visited per round
+        // The rounds of a dual pass hold the pairs of both species, species b's
+        // on the lanes after species a's.  Bound by the pairs' arithmetic, a
+        // wave at a time: filling its lanes is what counts (cells of 50 + 50
+        // on one wave: 49 rounds of 50 pairs instead of 98 of 25, then 50 of
+        // 50; 4096 such cells 1033 -> 725 us, FP64).
+        const int npa = na + (na & 1), npb = nb + (nb & 1);
+        const int pera = intra ? npa / 2 : Nmin, perb = dual ? npb / 2 : 0;  // slots per round
+        const bool sb = dual && t >= pera;  // this lane's pairs are species b's
+        const int ns = sb ? nb : na, per = sb ? perb : pera;
+        const int Rs = intra ? (sb ? npb : npa) - 1 : Nmax;  // this lane's rounds
+        const int R = dual && npb > npa ? npb - 1 : (intra ? npa - 1 : Nmax);
+        const int P = intra ? per : na;
+        const uint16_t *L = sb ? L1 : L0;
+        const CollConst &Cs = s_cc[sb ? 1 : 0];
+        const double cf = Cs.coef / dV;
+        const uint32_t c3s = sb ? ctr3(step, k + 1, PURPOSE_PAIR) : c3p;
         for (int r = 0; r < R; ++r) {
-          for (int sl = t; sl < per; sl += TPC) {
+          for (int sl = sb ? t - pera : t; sl < per && r < Rs; sl += TPC) {
             int I = -1, J = -1, i = sl;
             if (intra) {
-              const int x = sl == 0 ? r : (r + sl) % R;
-              const int y = sl == 0 ? np - 1 : (r - sl + R) % R;
-              if (x < na && y < na) {
-                I = L0[x];
-                J = L0[y];
+              // (r and sl are at most Rs: one wrap)
+              int x = r + sl, y = r - sl;
+              x = sl == 0 ? r : (x >= Rs ? x - Rs : x);
+              y = sl == 0 ? Rs : (y < 0 ? y + Rs : y);
+              if (x < ns && y < ns) {
+                I = L[x];
+                J = L[y];
               }
             } else {
               // a slot of the shorter list; i indexes list a, j list b
-              i = abig ? (sl - r + Nmax) % Nmax : sl;
-              const int j = abig ? sl : (sl + r) % Nmax;
+              const int d = sl - r, u = sl + r;
+              i = abig ? (d < 0 ? d + Nmax : d) : sl;
+              const int j = abig ? sl : (u >= Nmax ? u - Nmax : u);
               I = L0[i];
               J = L1[j];
             }
             if (I < 0) continue;
             const uint32_t kp = (uint32_t)(r * P + i);
-            if constexpr (REL)
-              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, ma, mb, A.c, A.method,
-                               (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
-            else if constexpr (sizeof(KR) == 8)
-              scatter_pair_nr_f64(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
-                                  (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
+            if constexpr (REL) {
+              const double mI = sb ? mb : ma;
+              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+            } else if constexpr (sizeof(KR) == 8)
+              scatter_pair_nr_f64(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
             else if constexpr (TAB_LDS)
-              scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
-                                  (uint32_t)cell, step_lo, c3p, k0, k1, s_tab);
+              scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+                                  (uint32_t)cell, step_lo, c3s, k0, k1, s_tab);
             else
-              scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
-                                  (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
+              scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
           }
           if (r + 1 < R) __syncthreads();
         }
         __syncthreads();
         if (t == 0) {
           s_st[0] += intra ? (unsigned long long)na * (na - 1) / 2 : (unsigned long long)na * nb;
-          s_st[3] += 1;
+          if (dual) s_st[0] += (unsigned long long)nb * (nb - 1) / 2;
+          s_st[3] += dual ? 2 : 1;
         }
       } else {
         // Pairs that share a particle form a chain, run in order by one lane:
