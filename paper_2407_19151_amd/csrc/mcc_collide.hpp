@@ -555,10 +555,15 @@ __device__ __forceinline__ void shuffle_two(const CellMem &M, int na, int oa, in
 constexpr uint32_t OCC_LIMIT = 48;
 constexpr int MAX_WEIGHT_VALUES = 32;
 
+// crowded: the buckets are known to hold more than that, and are not tried
+// (their counters are a few contended LDS words: 180 cells of 8200 in two
+// classes 357 -> 334 us per step, 4096 of 1024 with a beam class 484 -> 446).
+// Returns whether they do.
 template <int TPC, int PPT, bool G>
-__device__ __forceinline__ void weight_sort(const CellMem &M, int ns, const uint16_t *L, int off,
+__device__ __forceinline__ bool weight_sort(const CellMem &M, int ns, const uint16_t *L, int off,
                                             uint16_t *O, uint64_t lo, uint64_t hi,
-                                            uint32_t *wsum, uint32_t *maxocc) {
+                                            uint32_t *wsum, uint32_t *maxocc,
+                                            bool crowded = false) {
   const int t = threadIdx.x;
   const double scale = (double)ns / ((double)(hi - lo) + 1.0);
   const double *w = M.w;
@@ -567,15 +572,16 @@ __device__ __forceinline__ void weight_sort(const CellMem &M, int ns, const uint
     const double wo = w[item(o)], wq = w[item(q)];
     return wo > wq || (wo == wq && o < q);
   };
-  const uint32_t occ = bucket_rank_sort<TPC, PPT, G>(
-      ns, M.cnt, M.mem, O, wsum, maxocc,
-      [&](int q) -> uint32_t {
-        const uint64_t b = (uint64_t)__double_as_longlong(w[item(q)]);
-        const uint32_t k = (uint32_t)((double)(hi - b) * scale);
-        return k < (uint32_t)ns ? k : (uint32_t)(ns - 1);
-      },
-      before, M.slotbuf, IdentityMap(), OCC_LIMIT);
-  if (occ > OCC_LIMIT) {
+  if (!crowded)
+    crowded = bucket_rank_sort<TPC, PPT, G>(
+                  ns, M.cnt, M.mem, O, wsum, maxocc,
+                  [&](int q) -> uint32_t {
+                    const uint64_t b = (uint64_t)__double_as_longlong(w[item(q)]);
+                    const uint32_t k = (uint32_t)((double)(hi - b) * scale);
+                    return k < (uint32_t)ns ? k : (uint32_t)(ns - 1);
+                  },
+                  before, M.slotbuf, IdentityMap(), OCC_LIMIT) > OCC_LIMIT;
+  if (crowded) {
     // Crowded buckets come from ties, usually among few distinct weights:
     // ranking inside a bucket would cost its occupancy squared.  Instead,
     // one pass per distinct weight value, largest first, appends the items
@@ -619,10 +625,12 @@ __device__ __forceinline__ void weight_sort(const CellMem &M, int ns, const uint
   }
   for (int q = t; q < ns; q += TPC) O[q] = (uint16_t)item(O[q]);
   __syncthreads();
+  return crowded;
 }
 
-// weight classes of a species, decided once per cell
-enum : int { WORDER_EQUAL = 0, WORDER_DISTINCT = 1, WORDER_TIES = 2 };
+// weight classes of a species, decided once per cell (CROWDED: ties that fill
+// the sort's buckets past OCC_LIMIT, which the weights alone decide)
+enum : int { WORDER_EQUAL = 0, WORDER_DISTINCT = 1, WORDER_TIES = 2, WORDER_CROWDED = 3 };
 
 // Owner loop: particle e = threadIdx.x + j*TPC, j < PPT, unrolled when the
 // per-thread count is small.
@@ -982,12 +990,13 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
           // without an LDS home the order is kept only by a plan's weight
           // pass (M.word is list0 then, free before any collision)
           if (HAS_WORD || A.prep_mode == PREP_WRITE) {
-            weight_sort<TPC, PPT, GL>(M, ns, nullptr, o, M.word + o, lo[0], hi[0], wsum,
-                                      &maxocc);
+            const bool crowded = weight_sort<TPC, PPT, GL>(M, ns, nullptr, o, M.word + o, lo[0],
+                                                           hi[0], wsum, &maxocc);
             int tie = 0;
             for (int q = t; q + 1 < ns; q += TPC)
               if (M.w[M.word[o + q]] == M.w[M.word[o + q + 1]]) tie = 1;
-            flag = __syncthreads_or(tie) ? WORDER_TIES : WORDER_DISTINCT;
+            flag = __syncthreads_or(tie) ? (crowded ? WORDER_CROWDED : WORDER_TIES)
+                                         : WORDER_DISTINCT;
           }
         }
         if (t == 0) {
@@ -1474,7 +1483,8 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             else
               return (const uint16_t *)(A.prep_word + cb + o);
           }
-          weight_sort<TPC, PPT, GL>(M, ns, L, 0, ord, s_wlo[sp], s_whi[sp], wsum, &maxocc);
+          weight_sort<TPC, PPT, GL>(M, ns, L, 0, ord, s_wlo[sp], s_whi[sp], wsum, &maxocc,
+                                    f == WORDER_CROWDED);
           return (const uint16_t *)ord;
         };
         O0 = order(a, oa, na, L0, M.ord0);
