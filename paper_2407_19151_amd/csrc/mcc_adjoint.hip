@@ -52,7 +52,7 @@ template <typename KR>
 __device__ __forceinline__ PairBar pair_adjoint(
     double ux, double uy, double uz, double wi, double wj, uint32_t kp, double cf, double fa,
     double fb, int method, uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
-    const double2 *n97tab, double inv_lnl, double gIx, double gIy, double gIz, double gJx,
+    const double *n97tab, double inv_lnl, double gIx, double gIy, double gIz, double gJx,
     double gJy, double gJz, double &lbar) {
   using K = KMath<double>;
   const double wmax = wi > wj ? wi : wj;
@@ -66,12 +66,8 @@ __device__ __forceinline__ PairBar pair_adjoint(
   }
   const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
   const double u3 = unif64(r.w);
-  const double wratio = (wi < wj ? wi : wj) / wmax;
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wratio;
-  else if (wj < wi)
-    ai = u3 <= wratio;
+  const bool take = u3 * wmax <= (wi < wj ? wi : wj);
+  const bool ai = take || wi <= wj, aj = take || wj <= wi;
   // adjoint of du
   const double bx = (ai ? fa * gIx : 0.0) - (aj ? fb * gJx : 0.0);
   const double by = (ai ? fa * gIy : 0.0) - (aj ? fb * gJy : 0.0);
@@ -99,19 +95,10 @@ __device__ __forceinline__ PairBar pair_adjoint(
       oc = 2.0 * d2 * q;
       ocs = oc * q / s;  // 2 q^2 d(delta^2)/ds, d(delta^2)/ds = delta^2 / s
     }
-  } else {  // N97: dA/ds = -exp(-s) / L'(A)
-    const double A = n97_A_fast<double>(s, n97tab);
-    const double e = expm1(-2.0 * A), den = 1.0 + u0 * e;
-    if (__builtin_isinf(A))
-      oc = 0.0;
-    else if (A == 0.0)
-      oc = 2.0 * u0;
-    else
-      oc = -log1p(u0 * e) / A;
-    oc = oc < 0.0 ? 0.0 : (oc > 2.0 ? 2.0 : oc);
-    st = sqrt(oc * (2.0 - oc));
-    if (A > 0.0 && !__builtin_isinf(A) && oc > 0.0 && oc < 2.0)
-      ocs = (2.0 * u0 * (e + 1.0) / den - oc) / A * (-exp(-s) / langevin_prime(A));
+  } else {
+    const N97Root root = n97_root(s, n97tab);
+    n97_angle(s, u0, root, oc, st);
+    ocs = n97_oc_s(s, u0, oc, root);
   }
   double sp, cp;
   sincospi(2.0 * u2, &sp, &cp);
@@ -160,6 +147,7 @@ template <int TPC, int CAP, typename KR, bool GLOB>
 __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs A) {
   constexpr int PPT = CAP / TPC;
   constexpr int NW = TPC / WAVE;
+  constexpr int VS = GLOB ? SPACE_GLOBAL : SPACE_LDS;  // where the cell lives
   static_assert(CAP % TPC == 0 && TPC % WAVE == 0, "bad variant");
   __shared__ double red[2 * 6 * NW];
   uint64_t *redu = reinterpret_cast<uint64_t *>(red);
@@ -408,8 +396,10 @@ __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs 
           }
           const double cf = C.coef * f * nmin_dv;
           if constexpr (sizeof(KR) == 8)
-            scatter_pair_nr_f64(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
-                                (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
+            scatter_pair_nr_f64<VS, VS>(in_space<VS>(M.vx), in_space<VS>(M.vy),
+                                        in_space<VS>(M.vz), in_space<VS>(M.w), I, J, kp, cf,
+                                        C.fa, C.fb, A.method, (uint32_t)cell, step_lo, c3p, k0,
+                                        k1, A.n97seg);
           else
             scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
                                 (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);
@@ -776,7 +766,7 @@ __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs 
           }
           const PairBar u = pair_adjoint<KR>(ux, uy, uz, W[I], W[J], kp, C.coef * f * nmin_dv,
                                              C.fa, C.fb, A.method, (uint32_t)cell, step_lo, c3p,
-                                             k0, k1, A.n97, A.inv_lnl, GX[I], GY[I], GZ[I],
+                                             k0, k1, A.n97seg, A.inv_lnl, GX[I], GY[I], GZ[I],
                                              GX[J], GY[J], GZ[J], lbar);
           GX[I] += u.x;
           GY[I] += u.y;

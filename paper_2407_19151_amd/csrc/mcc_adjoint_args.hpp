@@ -28,7 +28,8 @@ struct AdjointArgs {
   const uint32_t *cell_count;
   double *lnl_part;  // [n_cells]: per-cell adjoint of lnL
   int32_t *err;
-  const double2 *n97;
+  const double2 *n97;    // as in CollideArgs
+  const double *n97seg;
   char *scratch;    // per-workgroup scratch, `stride` bytes each
   uint64_t stride;
   int32_t slots;    // record slots in it

@@ -50,8 +50,10 @@ hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, i
                       int64_t *offsets, int32_t *perm, int32_t *err, hipStream_t s);
 hipError_t launch_sample_angles(int method, int precision, int64_t n, const double *s,
                                 const uint32_t *a0, const uint32_t *a1, double *oc, double *st,
-                                double *A, const double2 *tab, hipStream_t st_);
+                                double *A, const double2 *tab, const double *seg,
+                                hipStream_t st_);
 hipError_t launch_n97_table(double2 *tab, hipStream_t s);
+const double *n97_segments_host();
 size_t rebin_scratch_bytes(int64_t n, int64_t m);
 int64_t rebin_tiles_needed(int64_t n, int64_t m);
 hipError_t launch_rebin(int64_t n, int64_t m, int32_t S, int32_t n_cells, const int64_t *off,
@@ -158,7 +160,8 @@ struct mcc_ctx {
   int32_t *err = nullptr;  // device error word
   DevBuf lists, counts;
   BigScratch big;  // large-cell scratch of the direct (non-plan) calls
-  DevBuf n97;  // N97 A(s) table (built once)
+  DevBuf n97;                      // N97 table of the FP32 form (built once)
+  const double *n97seg = nullptr;  // of the FP64 form (the device's)
   // per size bucket: the collide kernels' cell-claim and finished-workgroup
   // counters (zero between launches: each launch resets them at its end, so
   // launches of one context must not overlap)
@@ -284,7 +287,7 @@ void fill_args(CollideArgs &A, int64_t n, int32_t n_cells, int32_t S, const int6
                const double *w, double *vx, double *vy, double *vz, const double *cell_volume,
                double dVs, const mcc_species *sp, int32_t n_coll, const mcc_collision *coll,
                double dt, double lnL, uint64_t seed, uint64_t step, const mcc_params *p,
-               mcc_stats *stats, int32_t *cell_corr, int32_t *err, const double2 *n97) {
+               mcc_stats *stats, int32_t *cell_corr, const mcc_ctx *ctx) {
   std::memset(&A, 0, sizeof(A));
   A.offsets = offsets;
   A.w = w;
@@ -328,8 +331,9 @@ void fill_args(CollideArgs &A, int64_t n, int32_t n_cells, int32_t S, const int6
   }
   A.stats = stats;
   A.cell_corr = cell_corr;
-  A.err = err;
-  A.n97 = n97;
+  A.err = ctx->err;
+  A.n97 = ctx->n97.as<double2>();
+  A.n97seg = ctx->n97seg;
 }
 
 bool ensure_lists(mcc_ctx *ctx, DevBuf &lists, DevBuf &counts, int32_t n_cells) {
@@ -502,12 +506,18 @@ constexpr int32_t NOALLOC_MAX_CELLS = 1 << 18;
 constexpr size_t NOALLOC_BYTES = 256 + sizeof(int32_t) * (size_t)NBUCKET * NOALLOC_MAX_CELLS;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
+// The FP64 form's N97 table, constant once written: filled once per device by
+// the first context there (a copy per context would cost each creation a
+// device allocation and a host copy).
+static __device__ __align__(128) double n97_segments[N97_SEGMENTS * N97_SEG_DOUBLES];
+
 namespace {
-constexpr int NOALLOC_MAX_DEVICES = 64;
+constexpr int NOALLOC_MAX_DEVICES = 1024;
 std::mutex g_noalloc_mu;
 void *g_noalloc_ptr[NOALLOC_MAX_DEVICES] = {};
 hipError_t g_noalloc_rc[NOALLOC_MAX_DEVICES] = {};
 bool g_noalloc_done[NOALLOC_MAX_DEVICES] = {};
+const double *g_n97seg_ptr[NOALLOC_MAX_DEVICES] = {};
 
 // once per device, with that device current
 void noalloc_setup(int device) {
@@ -518,6 +528,21 @@ void noalloc_setup(int device) {
   g_noalloc_rc[device] = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
   g_noalloc_ptr[device] = g_noalloc_rc[device] == hipSuccess ? p : nullptr;
   g_noalloc_done[device] = true;
+}
+
+// the device's N97 table, filled on the first call (nullptr: the runtime
+// refused, and the next call tries again)
+const double *n97seg_setup(int device) {
+  if (device < 0 || device >= NOALLOC_MAX_DEVICES) return nullptr;
+  std::lock_guard<std::mutex> lock(g_noalloc_mu);
+  if (!g_n97seg_ptr[device]) {
+    void *p = nullptr;
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(n97_segments)) == hipSuccess &&
+        hipMemcpy(p, n97_segments_host(), sizeof(n97_segments), hipMemcpyHostToDevice) ==
+            hipSuccess)
+      g_n97seg_ptr[device] = static_cast<const double *>(p);
+  }
+  return g_n97seg_ptr[device];
 }
 
 void *noalloc_ptr(int device) {
@@ -553,6 +578,8 @@ mcc_status mcc_create(mcc_ctx **out, int device, void *hip_stream) {
   if (e == hipSuccess)
     e = ctx->n97.ensure(sizeof(double2) * N97_TABLE_SIZE) ? hipSuccess : hipErrorOutOfMemory;
   if (e == hipSuccess) e = launch_n97_table(ctx->n97.as<double2>(), nullptr);
+  ctx->n97seg = n97seg_setup(device);
+  if (e == hipSuccess && !ctx->n97seg) e = hipErrorUnknown;
   if (e == hipSuccess)
     e = ctx->work.ensure(sizeof(uint32_t) * WORK_QUEUES * WORK_STRIDE * NBUCKET)
             ? hipSuccess
@@ -630,7 +657,8 @@ mcc_status mcc_sample_angles(mcc_ctx *ctx, int32_t method, int32_t precision, in
   if (n > 0 && (!s || !a0 || !a1 || !oc || !st)) return MCC_ERR_INVALID;
   HIP_TRY(hipSetDevice(ctx->device));
   HIP_TRY(launch_sample_angles(method, precision, n, s, a0, a1, oc, st, A,
-                               ctx->n97.as<double2>(), ctx->stream));
+                               ctx->n97.as<double2>(), ctx->n97seg,
+                               ctx->stream));
   return finish(ctx);
 }
 
@@ -659,7 +687,7 @@ mcc_status mcc_collide_sorted(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t 
   CollideArgs A;
   fill_args(A, n, n_cells, n_species, offsets, weights, vx, vy, vz, cell_volume,
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, step, p, stats,
-            cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
+            cell_corr_pairs, ctx);
   hipStream_t s = ctx->stream;
   if (n_cells == 0) {
     if (stats) HIP_TRY(launch_zero_stats(stats, s));
@@ -701,7 +729,7 @@ mcc_status mcc_collide_sorted_noalloc(mcc_ctx *ctx, int64_t n, int32_t n_cells,
   CollideArgs A;
   fill_args(A, n, n_cells, n_species, offsets, weights, vx, vy, vz, cell_volume,
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, step, p, stats,
-            cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
+            cell_corr_pairs, ctx);
   const int mode = mode_of(p, A);
   hipStream_t s = ctx->stream;
   if (n_cells == 0) {
@@ -753,7 +781,7 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells, int3
   q.diagnostics = 0;
   fill_args(A, n, n_cells, n_species, offsets, weights, vx, vy, vz, cell_volume,
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, step, &q, stats,
-            nullptr, ctx->err, ctx->n97.as<double2>());
+            nullptr, ctx);
   A.tx = tx;
   A.ty = ty;
   A.tz = tz;
@@ -794,8 +822,7 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
   CollideArgs F;
   fill_args(F, n, n_cells, n_species, offsets, weights, const_cast<double *>(vx),
             const_cast<double *>(vy), const_cast<double *>(vz), cell_volume, cell_volume_scalar,
-            species, n_coll, coll, dt, coulomb_log, seed, step, p, nullptr, nullptr, ctx->err,
-            ctx->n97.as<double2>());
+            species, n_coll, coll, dt, coulomb_log, seed, step, p, nullptr, nullptr, ctx);
   AdjointArgs A;
   std::memset(&A, 0, sizeof(A));
   A.offsets = offsets;
@@ -825,6 +852,7 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
   A.lnl_part = ctx->adj_part.as<double>();
   A.err = ctx->err;
   A.n97 = ctx->n97.as<double2>();
+  A.n97seg = ctx->n97seg;
   hipStream_t s = ctx->stream;
   const Variants pick = pick_variants(ctx, MODE_TAN, n_cells);
   HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, ctx->lists.as<int32_t>(),
@@ -1077,7 +1105,7 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   }
   fill_args(pl->args, n, n_cells, n_species, offsets, weights, vx, vy, vz, cell_volume,
             cell_volume_scalar, species, n_coll, coll, dt, coulomb_log, seed, 0, p, stats,
-            cell_corr_pairs, ctx->err, ctx->n97.as<double2>());
+            cell_corr_pairs, ctx);
   pl->mode = mode_of(p, pl->args);
   for (int b = 0; b < NBUCKET; ++b)  // (a plan keeps every bucket's own list)
     pl->pick.v[b] = default_variant(pl->mode, b, n_cells <= ctx->n_cu);

@@ -499,14 +499,23 @@ namespace mcc {
 template <typename T>
 __global__ void k_sample_angles(int method, int64_t n, const double *s, const uint32_t *a0,
                                 const uint32_t *a1, double *oc, double *st, double *A,
-                                const double2 *tab) {
+                                const double2 *tab, const double *seg) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     T o, t;
-    sample_angle<T>(method, (T)s[i], a0[i], a1[i], o, t, tab);
+    const T si = (T)s[i];
+    double a = 0.0;
+    if constexpr (sizeof(T) == 8) {
+      sample_angle(method, si, a0[i], a1[i], o, t, seg);
+      if (method == 1 && !(si > KMath<double>::S_ISO))
+        a = si > 0.0 ? 1.0 / n97_root(si, seg).R() : __builtin_inf();
+    } else {
+      sample_angle(method, si, a0[i], a1[i], o, t, tab);
+      if (method == 1) a = (double)n97_A_fast(si, tab);
+    }
     oc[i] = (double)o;
     st[i] = (double)t;
-    if (A) A[i] = method == 1 ? (double)n97_A_fast<T>((T)s[i], tab) : 0.0;
+    if (A) A[i] = a;
   }
 }
 
@@ -645,6 +654,87 @@ hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, i
   return hipGetLastError();
 }
 
+// ----------------------------------------------------------------------------
+// The FP64 form's N97 table (N97_SEGMENTS polynomials), computed once per
+// process in extended precision: on each segment the root A of Nanbu's
+// equation at the eight Chebyshev nodes, the polynomial through 1/A and
+// exp(-2A) or expm1(-2A) there by divided differences.  The truncation error
+// is below 2 (1/128)^8 = 3e-17 relative.
+// ----------------------------------------------------------------------------
+static long double n97_root_l(long double s) {
+  // Newton on 1 - L(A) = -expm1(-s) (A > 1.6) or L(A) = exp(-s), from the
+  // leading terms of either end
+  const bool useM = s <= 0.6931471805599453L;
+  const long double y = expl(-s), target = useM ? -expm1l(-s) : y;
+  long double A = y < 0.5L ? 3.0L * y * (1.0L + 0.6L * y * y) : 1.0L / -expm1l(-s);
+  for (int it = 0; it < 60; ++it) {
+    long double g, d;
+    if (A < 0.5L) {  // Lambert's continued fraction of coth A - 1/A
+      const long double x2 = A * A;
+      long double cf = 43.0L;
+      for (int k = 20; k >= 1; --k) cf = (2.0L * k + 1.0L) + x2 / cf;
+      const long double L = A / cf;
+      g = useM ? target - (1.0L - L) : L - target;
+      d = 1.0L / 3.0L - x2 / 15.0L + 2.0L * x2 * x2 / 189.0L - x2 * x2 * x2 / 675.0L;
+    } else {
+      const long double e = 2.0L / expm1l(2.0L * A), sh = sinhl(A);
+      g = useM ? target - (1.0L / A - e) : (1.0L + e - 1.0L / A) - target;
+      d = 1.0L / (A * A) - 1.0L / (sh * sh);
+    }
+    long double An = A - g / d;
+    if (!(An > 0.0L)) An = 0.5L * A;
+    const bool done = fabsl(An - A) <= 2e-19L * A;
+    A = An;
+    if (done) break;
+  }
+  return A;
+}
+
+struct N97Segments {
+  double v[N97_SEGMENTS * N97_SEG_DOUBLES];
+  N97Segments() {
+    constexpr int N = N97_SEG_DEG + 1;
+    // segment 0: A > 64, so 1/A = -expm1(-s) and exp(-2A) = 0
+    long double fact = 1.0L;
+    for (int k = 0; k < N; ++k) {
+      if (k) fact *= k;
+      v[k] = k == 0 ? 0.0 : (double)((k & 1 ? 1.0L : -1.0L) / fact);
+      v[N + k] = 0.0;
+    }
+    for (int i = 1; i < N97_SEGMENTS; ++i) {
+      const int e = N97_SEG_E0 + ((i - 1) >> N97_SEG_BITS);
+      const int m = (i - 1) & ((1 << N97_SEG_BITS) - 1);
+      const long double c = ldexpl(1.0L + (m + 0.5L) / (1 << N97_SEG_BITS), e);
+      const long double h = ldexpl(0.5L / (1 << N97_SEG_BITS), e);
+      long double z[N], w[2][N];
+      for (int q = 0; q < N; ++q) {
+        z[q] = cosl((2 * q + 1) * 3.14159265358979323846264338L / (2 * N));
+        const long double A = n97_root_l(c + h * z[q]);
+        w[0][q] = 1.0L / A;
+        w[1][q] = c < N97_SEG_SPLIT ? expl(-2.0L * A) : expm1l(-2.0L * A);
+      }
+      for (int f = 0; f < 2; ++f) {
+        long double *d = w[f], p[N] = {};
+        for (int o = 1; o < N; ++o)
+          for (int q = N - 1; q >= o; --q) d[q] = (d[q] - d[q - 1]) / (z[q] - z[q - o]);
+        for (int q = N - 1; q >= 0; --q) {  // Newton form to powers of z
+          for (int k = N - 1; k > 0; --k) p[k] = p[k - 1] - z[q] * p[k];
+          p[0] = d[q] - z[q] * p[0];
+        }
+        long double hk = 1.0L;
+        for (int k = 0; k < N; ++k, hk *= h)
+          v[i * N97_SEG_DOUBLES + f * N + k] = (double)(p[k] / hk);
+      }
+    }
+  }
+};
+
+// the table on the host (built on first use; safe from several threads)
+const double *n97_segments_host() {
+  static const N97Segments t;
+  return t.v;
+}
+
 hipError_t launch_n97_table(double2 *tab, hipStream_t s) {
   hipLaunchKernelGGL(k_n97_table, dim3((N97_TN + 63) / 64), dim3(64), 0, s, tab);
   return hipGetLastError();
@@ -652,14 +742,15 @@ hipError_t launch_n97_table(double2 *tab, hipStream_t s) {
 
 hipError_t launch_sample_angles(int method, int precision, int64_t n, const double *s,
                                 const uint32_t *a0, const uint32_t *a1, double *oc, double *st,
-                                double *A, const double2 *tab, hipStream_t st_) {
+                                double *A, const double2 *tab, const double *seg,
+                                hipStream_t st_) {
   if (n <= 0) return hipSuccess;
   if (precision == 1)
     hipLaunchKernelGGL(k_sample_angles<float>, dim3(grid_for(n, 256)), dim3(256), 0, st_, method,
-                       n, s, a0, a1, oc, st, A, tab);
+                       n, s, a0, a1, oc, st, A, tab, seg);
   else
     hipLaunchKernelGGL(k_sample_angles<double>, dim3(grid_for(n, 256)), dim3(256), 0, st_,
-                       method, n, s, a0, a1, oc, st, A, tab);
+                       method, n, s, a0, a1, oc, st, A, tab, seg);
   return hipGetLastError();
 }
 

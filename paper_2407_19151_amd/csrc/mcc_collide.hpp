@@ -48,9 +48,9 @@ struct CellMem {
 // ---------------------------------------------------------------------------
 // Pair scatter (Sec. 3.1-3.2, Eq. (12)); non-relativistic
 // ---------------------------------------------------------------------------
-template <typename KR, class Tab>
-__device__ __forceinline__ void scatter_pair_nr(double *vx, double *vy, double *vz,
-                                                const double *w, int I, int J, uint32_t kp,
+template <typename KR, class Tab, class VP, class WP>
+__device__ __forceinline__ void scatter_pair_nr(VP vx, VP vy, VP vz, WP w, int I, int J,
+                                                uint32_t kp,
                                                 double coef_f_nmin_dV, double fa, double fb,
                                                 int method, uint32_t cell, uint32_t step_lo,
                                                 uint32_t c3, uint32_t k0, uint32_t k1,
@@ -68,20 +68,16 @@ __device__ __forceinline__ void scatter_pair_nr(double *vx, double *vy, double *
   if (!(s > KR(0))) return;
   const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
   KR oc, st;
-  sample_angle<KR>(method, s, r.x, r.y, oc, st, n97tab);
+  sample_angle(method, s, r.x, r.y, oc, st, n97tab);
   KR sp, cp;
   K::sincos2pi(K::u(r.z), sp, cp);
   KR dx, dy, dz;
   rotate_delta<KR>(ux, uy, uz, st, oc, sp, cp, dx, dy, dz);
-  // acceptance of the heavier particle, decided in FP64 in every mode
-  // (w_min / w_max: one division for either branch)
+  // acceptance of the heavier particle (u3 <= w_min / w_max), decided in FP64
+  // in every mode and without the division
   const double u3 = unif64(r.w);
-  const double wratio = (wi < wj ? wi : wj) / wmax;
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wratio;
-  else if (wj < wi)
-    ai = u3 <= wratio;
+  const bool take = u3 * wmax <= (wi < wj ? wi : wj);
+  const bool ai = take || wi <= wj, aj = take || wj <= wi;
   if (ai) {
     vx[I] = vix + fa * (double)dx;
     vy[I] = viy + fa * (double)dy;
@@ -100,8 +96,9 @@ __device__ __forceinline__ void scatter_pair_nr(double *vx, double *vy, double *
 // probability 1 - exp(-s) and then scatters isotropically (1 - cos chi
 // uniform on (0, 2)).  Words: x the collision, y the angle, z the azimuth,
 // w the heavier particle's acceptance.  FP64.
-__device__ __forceinline__ void scatter_pair_hs(double *vx, double *vy, double *vz,
-                                                const double *w, int I, int J, uint32_t kp,
+template <class VP, class WP>
+__device__ __forceinline__ void scatter_pair_hs(VP vx, VP vy, VP vz, WP w, int I, int J,
+                                                uint32_t kp,
                                                 double sigma_dt_f_nmin_dV, double fa, double fb,
                                                 uint32_t cell, uint32_t step_lo, uint32_t c3,
                                                 uint32_t k0, uint32_t k1) {
@@ -123,12 +120,8 @@ __device__ __forceinline__ void scatter_pair_hs(double *vx, double *vy, double *
   double dx, dy, dz;
   rotate_delta<double>(ux, uy, uz, st, oc, sp, cp, dx, dy, dz);
   const double u3 = unif64(r.w);
-  const double wratio = (wi < wj ? wi : wj) / wmax;
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wratio;
-  else if (wj < wi)
-    ai = u3 <= wratio;
+  const bool take = u3 * wmax <= (wi < wj ? wi : wj);
+  const bool ai = take || wi <= wj, aj = take || wj <= wi;
   if (ai) {
     vx[I] = vix + fa * dx;
     vy[I] = viy + fa * dy;
@@ -145,10 +138,13 @@ __device__ __forceinline__ void scatter_pair_hs(double *vx, double *vy, double *
 // code then does not share a register allocation with the rest of the cell
 // kernel, which roughly halves the kernel's registers (measured: the FP64
 // step runs in 0.63x the time); the FP32 form is cheaper inline.
+// VS, WS: the address spaces of the velocities and the weights.
+template <int VS, int WS>
 __device__ __attribute__((noinline)) void scatter_pair_nr_f64(
-    double *vx, double *vy, double *vz, const double *w, int I, int J, uint32_t kp,
-    double coef_f_nmin_dV, double fa, double fb, int method, uint32_t cell, uint32_t step_lo,
-    uint32_t c3, uint32_t k0, uint32_t k1, const double2 *n97tab) {
+    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
+    SpacePtr<WS, const double> w, int I, int J, uint32_t kp, double coef_f_nmin_dV, double fa,
+    double fb, int method, uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
+    const double *n97tab) {
   if (method == MCC_HARD_SPHERE)
     scatter_pair_hs(vx, vy, vz, w, I, J, kp, coef_f_nmin_dV, fa, fb, cell, step_lo, c3, k0, k1);
   else
@@ -163,27 +159,36 @@ __device__ __attribute__((noinline)) void scatter_pair_nr_f64(
 // random numbers and the acceptance fixed.  A(s) is differentiated as the
 // root of Nanbu's equation: dA/ds = -exp(-s) / L'(A).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double langevin_prime(double A) {
+// L'(A), A = 1 / R
+__device__ __forceinline__ double langevin_prime(double A, double R, const N97Root &r) {
   if (A < 0.5) {
     double L, dL;
     langevin_series(A, L, dL);
     return dL;
   }
   // 1/sinh^2 A = 4 e^{-2A} / (1 - e^{-2A})^2, finite for every A
-  const double em = expm1(-2.0 * A), ra = 1.0 / A;
-  return ra * ra - 4.0 * (em + 1.0) / (em * em);
+  return R * R - 4.0 * r.F / (r.E * r.E);
+}
+// d(1 - cos theta)/ds of the N97 angle, with the uniform u0 fixed (0 in the
+// limits, where oc is clamped or does not depend on s)
+__device__ __forceinline__ double n97_oc_s(double s, double u0, double oc, const N97Root &r) {
+  const double R = r.R();
+  if (!(oc > 0.0 && oc < 2.0) || s > KMath<double>::S_ISO || R == 0.0) return 0.0;
+  const double A = 1.0 / R;
+  // oc = -log1p(u0 E) / A: d/dA, times dA/ds = -exp(-s) / L'(A)
+  return (2.0 * u0 * r.F / (1.0 + u0 * r.E) - oc) * R * (-exp(-s) / langevin_prime(A, R, r));
 }
 
 // Tangent of a pair's velocity change du (the rotation of u = v_I - v_J by
 // the sampled angle, TA77 form) along (tu, ts): tu the tangent of u and ts
-// that of s, with the random numbers fixed; u0 the angle's uniform and A
-// Nanbu's parameter of s (N97).  oc = 1 - cos(theta), st = sin(theta), and
+// that of s, with the random numbers fixed; u0 the angle's uniform and root
+// Nanbu's root of s (N97).  oc = 1 - cos(theta), st = sin(theta), and
 // (sp, cp) the azimuth's sine and cosine, as the primal sampled them.
 __device__ __forceinline__ void rot_tangent(int method, double ux, double uy, double uz, double um,
                                             double s, double oc, double st, double sp,
-                                            double cp, double u0, double A, double tux,
-                                            double tuy, double tuz, double ts, double &tdx,
-                                            double &tdy, double &tdz) {
+                                            double cp, double u0, const N97Root &root,
+                                            double tux, double tuy, double tuz, double ts,
+                                            double &tdx, double &tdy, double &tdz) {
   using K = KMath<double>;
   const double tum = (ux * tux + uy * tuy + uz * tuz) / um;
   // tangent of 1 - cos(theta) and sin(theta)
@@ -195,14 +200,7 @@ __device__ __forceinline__ void rot_tangent(int method, double ux, double uy, do
       toc = 2.0 / ((1.0 + d2) * (1.0 + d2)) * d2 * ts / s;
     }
   } else {
-    if (A > 0.0 && !__builtin_isinf(A) && oc > 0.0 && oc < 2.0) {
-      const double e = expm1(-2.0 * A);
-      const double den = 1.0 + u0 * e;
-      const double dl_dA = -2.0 * u0 * (e + 1.0) / den;  // d log1p(u0 e) / dA
-      const double doc_dA = -dl_dA / A - oc / A;
-      const double dA_ds = -exp(-s) / langevin_prime(A);
-      toc = doc_dA * dA_ds * ts;
-    }
+    toc = n97_oc_s(s, u0, oc, root) * ts;
   }
   // st^2 = oc (2 - oc) for either sign of st
   const double tst = st != 0.0 ? (1.0 - oc) * toc / st : 0.0;
@@ -225,11 +223,13 @@ __device__ __forceinline__ void rot_tangent(int method, double ux, double uy, do
   }
 }
 
+template <int VS, int WS>
 __device__ __attribute__((noinline)) void scatter_pair_nr_tan(
-    double *vx, double *vy, double *vz, double *tx, double *ty, double *tz, const double *w,
-    int I, int J, uint32_t kp, double coef_f_nmin_dV, double fa, double fb, int method,
+    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
+    SpacePtr<VS, double> tx, SpacePtr<VS, double> ty, SpacePtr<VS, double> tz,
+    SpacePtr<WS, const double> w, int I, int J, uint32_t kp, double coef_f_nmin_dV, double fa, double fb, int method,
     uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
-    const double2 *n97tab, double dlnl) {
+    const double *n97tab, double dlnl) {
   using K = KMath<double>;
   const double vix = vx[I], viy = vy[I], viz = vz[I];
   const double vjx = vx[J], vjy = vy[J], vjz = vz[J];
@@ -243,26 +243,29 @@ __device__ __attribute__((noinline)) void scatter_pair_nr_tan(
   if (!(s > 0.0)) return;
   const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
   double oc, st;
-  sample_angle<double>(method, s, r.x, r.y, oc, st, n97tab);
+  const double u0 = K::u(r.x);
+  N97Root root{};
+  if (method == 0) {
+    sample_ta77<double>(s, r.x, r.y, oc, st);
+  } else {
+    root = n97_root(s, n97tab);
+    n97_angle(s, u0, root, oc, st);
+  }
   double sp, cp;
   K::sincos2pi(K::u(r.z), sp, cp);
   double dx, dy, dz;
   rotate_delta<double>(ux, uy, uz, st, oc, sp, cp, dx, dy, dz);
   const double u3 = unif64(r.w);
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wi / wj;
-  else if (wj < wi)
-    ai = u3 <= wj / wi;
+  const bool take = u3 * wmax <= (wi < wj ? wi : wj);
+  const bool ai = take || wi <= wj, aj = take || wj <= wi;
 
   // tangent of u, |u| and s (s ~ lnL / |u|^3)
   const double tux = tx[I] - tx[J], tuy = ty[I] - ty[J], tuz = tz[I] - tz[J];
   const double tum = (ux * tux + uy * tuy + uz * tuz) / um;
   const double ts = s * (dlnl - 3.0 * tum / um);
-  const double A = method == 0 ? 0.0 : n97_A_fast<double>(s, n97tab);
   double tdx, tdy, tdz;
-  rot_tangent(method, ux, uy, uz, um, s, oc, st, sp, cp, K::u(r.x), A, tux, tuy, tuz, ts, tdx,
-              tdy, tdz);
+  rot_tangent(method, ux, uy, uz, um, s, oc, st, sp, cp, u0, root, tux, tuy, tuz, ts, tdx, tdy,
+              tdz);
   if (ai) {
     vx[I] = vix + fa * dx;
     vy[I] = viy + fa * dy;
@@ -287,10 +290,12 @@ __device__ __attribute__((noinline)) void scatter_pair_nr_tan(
 // boosted back; s from the invariant rate with the CM deflection.
 // Species (unweighted) masses ma, mb; u = gamma v.  All FP64.
 // ---------------------------------------------------------------------------
+template <int VS, int WS>
 __device__ __attribute__((noinline)) void scatter_pair_rel(
-    double *vx, double *vy, double *vz, const double *w, int I, int J, uint32_t kp,
+    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
+    SpacePtr<WS, const double> w, int I, int J, uint32_t kp,
     double coef_f_nmin_dV, double ma, double mb, double c, int method, uint32_t cell,
-    uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1, const double2 *n97tab) {
+    uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1, const double *n97tab) {
   const double c2 = c * c;
   const double uix = vx[I], uiy = vy[I], uiz = vz[I];
   const double ujx = vx[J], ujy = vy[J], ujz = vz[J];
@@ -326,7 +331,7 @@ __device__ __attribute__((noinline)) void scatter_pair_rel(
   const double psx = Qx / ecm + crx * kb, psy = Qy / ecm + cry * kb, psz = Qz / ecm + crz * kb;
   const U4 r = philox(kp, cell, step_lo, c3, k0, k1);
   double oc, st;
-  sample_angle<double>(method, s, r.x, r.y, oc, st, n97tab);
+  sample_angle(method, s, r.x, r.y, oc, st, n97tab);
   double sp, cp;
   KMath<double>::sincos2pi(unif64(r.z), sp, cp);
   double Dx, Dy, Dz;
@@ -334,11 +339,8 @@ __device__ __attribute__((noinline)) void scatter_pair_rel(
   const double Dp = (Dx * ptx + Dy * pty + Dz * ptz) * kb;
   const double px = Dx + Dp * ptx, py = Dy + Dp * pty, pz = Dz + Dp * ptz;
   const double u3 = unif64(r.w);
-  bool ai = true, aj = true;
-  if (wi < wj)
-    aj = u3 <= wi / wj;
-  else if (wj < wi)
-    ai = u3 <= wj / wi;
+  const bool take = u3 * wmax <= (wi < wj ? wi : wj);
+  const bool ai = take || wi <= wj, aj = take || wj <= wi;
   if (ai) {
     vx[I] = uix + px / ma;
     vy[I] = uiy + py / ma;
@@ -897,6 +899,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
     const int n = uni(s_so[S]);
     const double dV = A.cell_volume ? A.cell_volume[cell] : A.dV;
     if constexpr (!W_LDS) M.w = A.w + cb;
+    // the cell's arrays with their address spaces (the out-of-line pairs)
+    constexpr int VS = GL ? SPACE_GLOBAL : SPACE_LDS;
+    constexpr int WS = GL || !W_LDS ? SPACE_GLOBAL : SPACE_LDS;
+    const auto pvx = in_space<VS>(M.vx), pvy = in_space<VS>(M.vy), pvz = in_space<VS>(M.vz);
+    const auto pw = in_space<WS>(M.w);
     const bool prep_read = A.corr && A.prep_mode == PREP_READ;
 
     if constexpr (!GL) {
@@ -1166,11 +1173,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             const uint32_t kp = (uint32_t)(r * P + i);
             if constexpr (REL) {
               const double mI = sb ? mb : ma;
-              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, mI, intra ? mI : mb, A.c,
-                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+              scatter_pair_rel<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             } else if constexpr (sizeof(KR) == 8)
-              scatter_pair_nr_f64(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
-                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+              scatter_pair_nr_f64<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             else if constexpr (TAB_LDS)
               scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
                                   (uint32_t)cell, step_lo, c3s, k0, k1, s_tab);
@@ -1246,14 +1253,15 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             }
             if constexpr (REL) {
               const double mI = sb ? mb : ma;
-              scatter_pair_rel(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, mI, intra ? mI : mb, A.c,
-                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+              scatter_pair_rel<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+                               A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             } else if constexpr (TAN)
-              scatter_pair_nr_tan(M.vx, M.vy, M.vz, M.tx, M.ty, M.tz, M.w, I, J, kp, cf, C.fa, C.fb,
-                                  A.method, (uint32_t)cell, step_lo, c3p, k0, k1, A.n97, A.dlnl);
+              scatter_pair_nr_tan<VS, WS>(pvx, pvy, pvz, in_space<VS>(M.tx), in_space<VS>(M.ty),
+                                          in_space<VS>(M.tz), pw, I, J, kp, cf, C.fa, C.fb,
+                                  A.method, (uint32_t)cell, step_lo, c3p, k0, k1, A.n97seg, A.dlnl);
             else if constexpr (sizeof(KR) == 8)
-              scatter_pair_nr_f64(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
-                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97);
+              scatter_pair_nr_f64<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+                                  (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             else if constexpr (TAB_LDS)
               scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
                                   (uint32_t)cell, step_lo, c3s, k0, k1, s_tab);

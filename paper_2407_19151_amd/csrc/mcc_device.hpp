@@ -69,6 +69,17 @@ __device__ __forceinline__ void lds_copy(const T *src, U *dst, int ndw) {
 }
 __device__ __forceinline__ void lds_copy_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Pointers with their address space, for the out-of-line pair functions: a
+// generic pointer there costs flat accesses, which wait on both the LDS and
+// the vector-memory path.
+template <int SPACE, class T>
+using SpacePtr = __attribute__((address_space(SPACE))) T *;
+constexpr int SPACE_GLOBAL = 1, SPACE_LDS = 3;
+template <int SPACE, class T>
+__device__ __forceinline__ SpacePtr<SPACE, T> in_space(T *p) {
+  return (SpacePtr<SPACE, T>)p;
+}
+
 // values the whole wave holds alike (read from LDS): kept in scalar registers
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 __device__ __forceinline__ long long uni(long long x) {
@@ -791,12 +802,12 @@ __device__ T n97_A(T s) {
 }
 
 // ---------------------------------------------------------------------------
-// Fast A(s) for the collision step.  Nanbu's equation L(A) = coth A - 1/A =
-// exp(-s) has closed-form solutions to rounding at both ends; in between A
-// is interpolated (cubic Hermite in t = ln s on a table of A and dA/dt
-// computed once per context by n97_A above) and, in FP64, polished by one
-// Newton step on the equation itself (the interpolant is good to ~1e-9, so
-// one step reaches rounding).
+// Fast A(s) for the collision step: Nanbu's equation L(A) = coth A - 1/A =
+// exp(-s) without a solver.
+// FP32: closed forms at both ends, and in between a cubic Hermite interpolant
+// in t = ln s on a table of A and dA/dt computed once per context by n97_A.
+// FP64: polynomials of 1/A and exp(-2A) (what the inverse CDF takes) on
+// segments found from the bits of s.
 // ---------------------------------------------------------------------------
 constexpr int N97_TN = N97_TABLE_SIZE;
 constexpr double N97_T0 = -3.25;
@@ -827,80 +838,146 @@ __device__ __forceinline__ void langevin_series(double A, double &L, double &dL)
   dL = q;
 }
 
-// one Newton step on Nanbu's equation from A (FP64): the 1 - L form against
-// -expm1(-s) for s <= ln 2 (there A > 1.6), else the L form against exp(-s)
-__device__ __forceinline__ double n97_newton(double s, double A) {
-  double L, M, dL;
-  if (A < 0.5) {
-    langevin_series(A, L, dL);
-    M = 1.0 - L;
-  } else {
-    const double em1 = expm1(2.0 * A);
-    const double r1 = 1.0 / em1, ra = 1.0 / A;
-    M = ra - 2.0 * r1;
-    L = 1.0 - M;
-    dL = ra * ra - 4.0 * (em1 + 1.0) * r1 * r1;  // 1/A^2 - 1/sinh^2 A
-  }
-  double g;
-  if (s <= 0.69314718055994531)
-    g = -expm1(-s) - M;  // = L(A) - exp(-s), formed without cancellation
-  else
-    g = L - exp(-s);
-  return A - g / dL;
-}
-
 // (tab: double2 in HBM, or float2 holding the same entries rounded to FP32,
 // which is what the FP32 form takes of them)
-template <typename T, class Tab>
-__device__ __forceinline__ T n97_A_fast(T s, const Tab *tab) {
-  using M = KMath<T>;
-  if (!(s > T(0))) return T(__builtin_inf());
-  if (s > M::S_ISO) return T(0);
-  if (s >= T(N97_S_HI)) return T(3) * M::exp_(-s);
-  if (s <= T(N97_S_LO)) return M::div(T(1), -M::expm1_(-s));
-  const T x = (M::log_(s) - T(N97_T0)) * T(1.0 / N97_H);
+template <class Tab>
+__device__ __forceinline__ float n97_A_fast(float s, const Tab *tab) {
+  using M = KMath<float>;
+  if (!(s > 0.0f)) return __builtin_inff();
+  if (s > M::S_ISO) return 0.0f;
+  if (s >= (float)N97_S_HI) return 3.0f * M::exp_(-s);
+  if (s <= (float)N97_S_LO) return M::div(1.0f, -M::expm1_(-s));
+  const float x = (M::log_(s) - (float)N97_T0) * (float)(1.0 / N97_H);
   int i = (int)x;
   i = i < 0 ? 0 : (i > N97_TN - 2 ? N97_TN - 2 : i);
-  const T f = x - T(i);
+  const float f = x - (float)i;
   const Tab k0 = tab[i], k1 = tab[i + 1];
-  const T f2 = f * f, f3 = f2 * f;
+  const float f2 = f * f, f3 = f2 * f;
   // Hermite basis; the table holds A and h dA/dt at the knots
-  const T A = (T(2) * f3 - T(3) * f2 + T(1)) * T(k0.x) + (f3 - T(2) * f2 + f) * T(k0.y) +
-              (T(3) * f2 - T(2) * f3) * T(k1.x) + (f3 - f2) * T(k1.y);
-  if constexpr (sizeof(T) == 8)
-    return n97_newton(s, A);
-  else
-    return A;
+  return (2.0f * f3 - 3.0f * f2 + 1.0f) * (float)k0.x + (f3 - 2.0f * f2 + f) * (float)k0.y +
+         (3.0f * f2 - 2.0f * f3) * (float)k1.x + (f3 - f2) * (float)k1.y;
+}
+
+// Nanbu's root for one pair, FP64, as its uses take it: R = 1/A,
+// E = expm1(-2A) and F = exp(-2A).  Where E is near -1 the table holds F, and
+// E = F - 1 is its rounded value; where F is near 1 it holds E.  R comes as
+// R0 + r (r at most 1/64 of R0), which a product takes with one rounding.
+// s > 0; above KMath::S_ISO the caller takes the isotropic limit.
+// About 50 instructions where the table, Newton step and expm1 it replaces
+// took 850, several times per wave with every range of s that its lanes hold;
+// R within 2.3e-16 of the root's (before: A within 1.7e-15).
+struct N97Root {
+  double R0, r, E, F;
+  __device__ __forceinline__ double R() const { return R0 + r; }
+};
+__device__ __forceinline__ N97Root n97_root(double s, const double *seg) {
+  N97Root r;
+  const int hi = __double2hiint(s);
+  constexpr int SH = 20 - N97_SEG_BITS;
+  int i = (hi >> SH) - ((1023 + N97_SEG_E0) << N97_SEG_BITS) + 1;
+  i = i < 0 ? 0 : (i > N97_SEGMENTS - 1 ? N97_SEGMENTS - 1 : i);
+  // the segment's centre has the next mantissa bit set and the rest clear
+  const double c =
+      i == 0 ? 0.0 : __hiloint2double((hi & ~((1 << SH) - 1)) | (1 << (SH - 1)), 0);
+  const double f = s - c;  // exact
+  // (global loads: in the out-of-line pair functions the pointer is generic)
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const SpacePtr<SPACE_GLOBAL, const d2> p =
+      (SpacePtr<SPACE_GLOBAL, const d2>)(seg + (int64_t)i * N97_SEG_DOUBLES);
+  constexpr int H = (N97_SEG_DEG + 1) / 2;
+  d2 q[H], v[H];
+#pragma unroll
+  for (int k = 0; k < H; ++k) q[k] = p[k];
+  double R = q[H - 1].y;
+#pragma unroll
+  for (int k = H - 1; k >= 0; --k) {
+    if (k < H - 1) R = fma(R, f, q[k].y);
+    if (k > 0) R = fma(R, f, q[k].x);
+  }
+  asm volatile("" : "+v"(R) : : "memory");
+#pragma unroll
+  for (int k = 0; k < H; ++k) v[k] = p[H + k];
+  double T = v[H - 1].y;
+#pragma unroll
+  for (int k = H - 1; k >= 0; --k) {
+    if (k < H - 1) T = fma(T, f, v[k].y);
+    T = fma(T, f, v[k].x);
+  }
+  const bool low = s < N97_SEG_SPLIT;
+  r.R0 = q[0].x;
+  r.r = R * f;
+  r.E = low ? T - 1.0 : T;
+  r.F = low ? T : T + 1.0;
+  if (s >= N97_SEG_TOP) {
+    // A = 3y + 9/5 y^3 + 297/175 y^5 + ..., y = exp(-s) < 3.4e-4, and the
+    // series of expm1(-2A)
+    const double y = exp(-s), y2 = y * y;
+    const double A = y * fma(y2, fma(y2, 297.0 / 175.0, 1.8), 3.0);
+    r.R0 = 1.0 / A;
+    r.r = 0.0;
+    r.E = -2.0 * A *
+          fma(-A, fma(-A, fma(-A, fma(-A, 2.0 / 15.0, 1.0 / 3.0), 2.0 / 3.0), 1.0), 1.0);
+    r.F = 1.0 + r.E;
+  }
+  return r;
 }
 
 // Sampled polar angle: oc = 1 - cos(theta), st = sin(theta).
-template <typename T, class Tab>
-__device__ __forceinline__ void sample_angle(int method, T s, uint32_t a0, uint32_t a1, T &oc,
-                                             T &st, const Tab *n97tab) {
+// TA77: tan(theta/2) ~ N(0, s/2)
+template <typename T>
+__device__ __forceinline__ void sample_ta77(T s, uint32_t a0, uint32_t a1, T &oc, T &st) {
   using M = KMath<T>;
-  const T u0 = M::u(a0);
-  if (method == 0) {  // TA77: tan(theta/2) ~ N(0, s/2)
-    const T z = M::sqrt_(T(-2) * M::log_(u0)) * M::cos2pi(M::u(a1));
-    const T delta = M::sqrt_(T(0.5) * s) * z;
-    const T d2 = delta * delta;
-    if (__builtin_isinf(d2)) {
-      oc = T(2);
-      st = T(0);
-    } else {
-      const T q = M::div(T(1), T(1) + d2);
-      st = T(2) * delta * q;
-      oc = T(2) * d2 * q;
-    }
+  const T z = M::sqrt_(T(-2) * M::log_(M::u(a0))) * M::cos2pi(M::u(a1));
+  const T delta = M::sqrt_(T(0.5) * s) * z;
+  const T d2 = delta * delta;
+  if (__builtin_isinf(d2)) {
+    oc = T(2);
+    st = T(0);
+  } else {
+    const T q = M::div(T(1), T(1) + d2);
+    st = T(2) * delta * q;
+    oc = T(2) * d2 * q;
+  }
+}
+
+// FP32 form (n97tab: the Hermite table, double2 or float2)
+template <class Tab>
+__device__ __forceinline__ void sample_angle(int method, float s, uint32_t a0, uint32_t a1,
+                                             float &oc, float &st, const Tab *n97tab) {
+  using M = KMath<float>;
+  if (method == 0) {
+    sample_ta77<float>(s, a0, a1, oc, st);
   } else {  // N97
-    const T A = n97_A_fast<T>(s, n97tab);
+    const float u0 = M::u(a0);
+    const float A = n97_A_fast(s, n97tab);
     if (__builtin_isinf(A))
-      oc = T(0);
-    else if (A == T(0))
-      oc = T(2) * u0;
+      oc = 0.0f;
+    else if (A == 0.0f)
+      oc = 2.0f * u0;
     else
-      oc = M::div(-M::log1p_(u0 * M::expm1_(T(-2) * A)), A);
-    oc = oc < T(0) ? T(0) : (oc > T(2) ? T(2) : oc);
-    st = M::sqrt_(oc * (T(2) - oc));
+      oc = M::div(-M::log1p_(u0 * M::expm1_(-2.0f * A)), A);
+    oc = oc < 0.0f ? 0.0f : (oc > 2.0f ? 2.0f : oc);
+    st = M::sqrt_(oc * (2.0f - oc));
+  }
+}
+
+// the N97 angle of a root (FP64)
+__device__ __forceinline__ void n97_angle(double s, double u0, const N97Root &r, double &oc,
+                                          double &st) {
+  const double l = -log1p(u0 * r.E);
+  oc = s > KMath<double>::S_ISO ? 2.0 * u0 : fma(l, r.R0, l * r.r);
+  oc = oc < 0.0 ? 0.0 : (oc > 2.0 ? 2.0 : oc);
+  st = sqrt(oc * (2.0 - oc));
+}
+
+// FP64 form (seg: the segment table)
+__device__ __forceinline__ void sample_angle(int method, double s, uint32_t a0, uint32_t a1,
+                                             double &oc, double &st, const double *seg) {
+  if (method == 0) {
+    sample_ta77<double>(s, a0, a1, oc, st);
+  } else {
+    const double u0 = unif64(a0);
+    n97_angle(s, u0, n97_root(s, seg), oc, st);
   }
 }
 

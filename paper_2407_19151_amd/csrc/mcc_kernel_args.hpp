@@ -9,8 +9,18 @@
 
 namespace mcc {
 
-// knots of the N97 A(s) table (uniform in ln s)
+// knots of the FP32 form's N97 A(s) table (uniform in ln s)
 constexpr int N97_TABLE_SIZE = 256;
+
+// The FP64 form's N97 table: polynomials of degree 7 on 32 segments per
+// binade of s from 2^-6 to 8, and segment 0 for all smaller s.  Per segment
+// the coefficients (about its centre) of 1/A(s) and of exp(-2A) (s < 2) or
+// expm1(-2A) (s >= 2): 128 bytes, one cache line per lookup.
+constexpr int N97_SEG_BITS = 5, N97_SEG_E0 = -6, N97_SEG_E1 = 3, N97_SEG_DEG = 7;
+constexpr int N97_SEG_DOUBLES = 2 * (N97_SEG_DEG + 1);
+constexpr int N97_SEGMENTS = 1 + ((N97_SEG_E1 - N97_SEG_E0) << N97_SEG_BITS);
+constexpr double N97_SEG_TOP = 8.0;    // 2^E1
+constexpr double N97_SEG_SPLIT = 2.0;  // below: exp(-2A), above: expm1(-2A)
 
 // Per-collision constants computed on the host in FP64.
 struct CollConst {
@@ -62,7 +72,8 @@ struct CollideArgs {
   char *big_scratch;            // large-cell variants: per-block global scratch
   uint64_t big_stride;          // bytes per block
   unsigned long long *phase;    // profiling builds (MCC_PHASE_TIMING): clock ticks per phase
-  const double2 *n97;           // N97 table: A and h dA/dt at the knots of t = ln s
+  const double2 *n97;           // N97 table, FP32 form: A and h dA/dt at the knots of t = ln s
+  const double *n97seg;         // N97 table, FP64 form: N97_SEGMENTS polynomials
   // tangent (forward-mode) form only
   double *tx, *ty, *tz;         // tangent of the velocities, in/out
   double dlnl;                  // tangent of ln(Lambda) relative to ln(Lambda)
