@@ -46,7 +46,7 @@ int64_t bin_tiles(int64_t n);
 int64_t bin_hist_entries(int64_t n);
 hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
                       int32_t S, uint32_t *keys0, uint32_t *keys1, int32_t *vals0,
-                      int32_t *vals1, uint32_t *hist, int64_t *pos, int64_t *tiles,
+                      int32_t *vals1, uint32_t *hist, uint32_t *pos, int64_t *tiles,
                       int64_t *offsets, int32_t *perm, int32_t *err, hipStream_t s);
 hipError_t launch_sample_angles(int method, int precision, int64_t n, const double *s,
                                 const uint32_t *a0, const uint32_t *a1, double *oc, double *st,
@@ -901,13 +901,13 @@ static mcc_status bin_into(mcc_ctx *ctx, int64_t n, const int32_t *cells,
   if (!ctx->bin_k0.ensure(4 * nn) || !ctx->bin_k1.ensure(4 * nn) ||
       !ctx->bin_v0.ensure(4 * nn) || !ctx->bin_v1.ensure(4 * nn) ||
       !ctx->bin_hist.ensure(sizeof(uint32_t) * (size_t)hb) ||
-      !ctx->bin_pos.ensure(sizeof(int64_t) * (size_t)(hb + 1)) ||
+      !ctx->bin_pos.ensure(sizeof(uint32_t) * (size_t)hb) ||
       !ctx->tiles.ensure(sizeof(int64_t) * (size_t)scan_tiles_needed(hb)))
     return MCC_ERR_OOM;
   return from_hip(launch_bin(n, cells, species_id, n_cells, n_species,
                              ctx->bin_k0.as<uint32_t>(), ctx->bin_k1.as<uint32_t>(),
                              ctx->bin_v0.as<int32_t>(), ctx->bin_v1.as<int32_t>(),
-                             ctx->bin_hist.as<uint32_t>(), ctx->bin_pos.as<int64_t>(),
+                             ctx->bin_hist.as<uint32_t>(), ctx->bin_pos.as<uint32_t>(),
                              ctx->tiles.as<int64_t>(), offsets, perm, ctx->err, ctx->stream));
 }
 

@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256)
   }
 }
 
-// three-phase scan of u32 counts into int64 offsets (offsets[m] = total)
+// three-phase exclusive scan of u32 counts (totals below 2^32)
 constexpr int SCAN_TPB = 256, SCAN_PPT = 8, SCAN_TILE = SCAN_TPB * SCAN_PPT;
 
 __global__ void k_scan_tiles(const uint32_t *in, int64_t m, int64_t *tile_sums) {
@@ -214,7 +214,7 @@ __global__ void k_scan_tile_sums(int64_t *tile_sums, int64_t ntiles) {
 // the thread sums are scanned by shuffles in each wave and across waves, and
 // each thread writes its entries' offsets
 __global__ void k_scan_apply(const uint32_t *in, int64_t m, const int64_t *tile_off,
-                             int64_t *out) {
+                             uint32_t *out) {
   __shared__ int64_t wtot[SCAN_TPB / WAVE];
   const int t = threadIdx.x;
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)t * SCAN_PPT;
@@ -239,10 +239,9 @@ __global__ void k_scan_apply(const uint32_t *in, int64_t m, const int64_t *tile_
     if (k < t / WAVE) run += wtot[k];
 #pragma unroll
   for (int j = 0; j < SCAN_PPT; ++j) {
-    if (base + j < m) out[base + j] = run;
+    if (base + j < m) out[base + j] = (uint32_t)run;
     run += v[j];
   }
-  if (base <= m - 1 && m - 1 < base + SCAN_PPT) out[m] = run;  // the total
 }
 
 // ----------------------------------------------------------------------------
@@ -263,12 +262,46 @@ constexpr int RADIX_ROWS = 16;                    // rows of 64 particles per wa
 constexpr int RADIX_TILE = RADIX_WPB * RADIX_ROWS * WAVE;  // 4096 particles
 static_assert(RADIX_BINS % (RADIX_WPB * WAVE) == 0, "digits per thread");
 
-__device__ __forceinline__ uint32_t bin_key(const int32_t *cells, const int32_t *species,
-                                            int64_t i, int32_t n_cells, int32_t S,
-                                            uint32_t m) {
-  const int32_t c = cells[i], sp = species[i];
-  return (c < 0 || c >= n_cells || sp < 0 || sp >= S) ? m
-                                                       : (uint32_t)c * (uint32_t)S + (uint32_t)sp;
+// The tile of a workgroup.  Consecutive workgroups go to the eight XCDs in
+// turn; each XCD takes a range of consecutive tiles, so that what neighbouring
+// tiles share -- lines of the digit-major histograms, and the output lines in
+// which one tile's run of a digit ends and the next one's begins -- meets in
+// one L2.  Launched with xcd_grid(T) workgroups; at least T: no tile.
+constexpr int XCDS = 8;
+__device__ __forceinline__ int64_t xcd_tile(int64_t T) {
+  const int64_t per = (T + XCDS - 1) / XCDS, k = blockIdx.x / XCDS;
+  const int64_t tile = (blockIdx.x % XCDS) * per + k;
+  return k < per && tile < T ? tile : T;
+}
+static inline unsigned xcd_grid(int64_t T) { return (unsigned)((T + XCDS - 1) / XCDS * XCDS); }
+
+// The keys of a thread's RADIX_ROWS items, row by row of its wave, every load
+// in flight before the first is used (n > 0; a row past the end reads the last
+// item, and its key is not used).  FIRST: the group keys, m for an id out of
+// range.
+template <bool FIRST>
+__device__ __forceinline__ void load_keys(int64_t i0, int64_t n, const int32_t *cells,
+                                          const int32_t *species, int32_t n_cells, int32_t S,
+                                          uint32_t m, const uint32_t *keys,
+                                          uint32_t ky[RADIX_ROWS]) {
+  int32_t sp[FIRST ? RADIX_ROWS : 1];
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r) {
+    const int64_t i = i0 + r * WAVE, ic = i < n ? i : n - 1;
+    if constexpr (FIRST) {
+      ky[r] = (uint32_t)cells[ic];
+      sp[r] = species[ic];
+    } else {
+      ky[r] = keys[ic];
+    }
+  }
+  if constexpr (FIRST) {
+#pragma unroll
+    for (int r = 0; r < RADIX_ROWS; ++r) {
+      const bool bad = ky[r] >= (uint32_t)n_cells || (uint32_t)sp[r] >= (uint32_t)S;
+      ky[r] = bad ? m : ky[r] * (uint32_t)S + (uint32_t)sp[r];
+    }
+  }
 }
 
 // digit histogram of every tile: hist[d * T + tile]
@@ -279,114 +312,78 @@ __global__ void __launch_bounds__(RADIX_WPB * WAVE)
                  uint32_t *hist, int32_t *err) {
   constexpr int TPB = RADIX_WPB * WAVE, DPT = RADIX_BINS / TPB;  // digits per thread
   __shared__ uint32_t h[RADIX_BINS];
-  const int t = threadIdx.x;
-  const int64_t tile = blockIdx.x;
+  const int t = threadIdx.x, wv = t / WAVE, lane = t & (WAVE - 1);
+  const int64_t tile = xcd_tile(T);
+  if (tile >= T) return;
 #pragma unroll
   for (int j = 0; j < DPT; ++j) h[t + j * TPB] = 0u;
+  const int64_t i0 = tile * RADIX_TILE + (int64_t)wv * RADIX_ROWS * WAVE + lane;
+  uint32_t ky[RADIX_ROWS];
+  load_keys<FIRST>(i0, n, cells, species, n_cells, S, m, keys, ky);
   __syncthreads();
-  const int64_t base = tile * RADIX_TILE;
-  int bad = 0;
-  auto add = [&](uint32_t k) {
-    if (FIRST && k == m) bad = 1;
-    atomicAdd(&h[(k >> shift) & (RADIX_BINS - 1)], 1u);
-  };
-  if (!FIRST && base + RADIX_TILE <= n) {
-    // a whole tile: four keys per load (order does not matter here)
-    const uint4 *k4 = reinterpret_cast<const uint4 *>(keys + base);
-    for (int j = t; j < RADIX_TILE / 4; j += TPB) {
-      const uint4 q = k4[j];
-      add(q.x);
-      add(q.y);
-      add(q.z);
-      add(q.w);
+  bool bad = false;
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r)
+    if (i0 + r * WAVE < n) {
+      bad |= FIRST && ky[r] == m;
+      atomicAdd(&h[(ky[r] >> shift) & (RADIX_BINS - 1)], 1u);
     }
-  } else {
-    for (int j = t; j < RADIX_TILE; j += TPB) {
-      const int64_t i = base + j;
-      if (i < n) add(FIRST ? bin_key(cells, species, i, n_cells, S, m) : keys[i]);
-    }
-  }
   if (FIRST && bad) atomicCAS(err, 0, 3);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < DPT; ++j) hist[(int64_t)(t + j * TPB) * T + tile] = h[t + j * TPB];
 }
 
-// Stable scatter of (key, value) by the digit; pos[d * T + tile] is the
-// first output position of the tile's digit d (scan of the histograms).
-// The tile is first sorted by digit in LDS -- wave w ranks its 16 rows in
-// order (ballots over the digit bits give a particle's rank among the
-// equal digits of its row), the per-(digit, wave) counts are scanned --
-// then written out along the sorted order, so every digit's run of the
-// tile goes to consecutive addresses.
-template <bool FIRST>
-__global__ void __launch_bounds__(RADIX_WPB * WAVE)
-    k_radix_scatter(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
-                    int32_t S, uint32_t m, const uint32_t *keys_in, const int32_t *vals_in,
-                    int shift, int64_t T, const int64_t *pos, uint32_t *keys_out,
-                    int32_t *vals_out) {
-  __shared__ uint32_t cnt[RADIX_WPB][RADIX_BINS];  // per wave: its digit counts
-  __shared__ uint32_t lbase[RADIX_BINS];           // first local slot of each digit
-  __shared__ uint32_t gsum[RADIX_WPB];
-  __shared__ uint32_t lk[RADIX_TILE];
-  __shared__ int32_t lv[RADIX_TILE];
+// Stable ranks of a tile's items by the digit.  On return slot[r] is the
+// item's place in the tile sorted by digit, and gbase[d] + slot its output
+// position (pos[d * T + tile]: the first output position of the tile's digit
+// d, from the scan of the histograms).  Wave w ranks its rows in order:
+// ballots over the digit bits give an item's rank among the equal digits of
+// its row, the wave's counts those of the rows before, and the scan of the
+// per-(digit, wave) counts the rest.
+template <class Cnt>
+__device__ __forceinline__ void radix_ranks(int64_t i0, int64_t n, const uint32_t ky[RADIX_ROWS],
+                                            int shift, int64_t T, int64_t tile,
+                                            const uint32_t *pos, Cnt cnt, uint32_t *gbase,
+                                            uint32_t *gsum, uint32_t slot[RADIX_ROWS]) {
   const int t = threadIdx.x, wv = t / WAVE, lane = t & (WAVE - 1);
-  const int64_t tile = blockIdx.x;
-  const int64_t base = tile * RADIX_TILE;
+  constexpr int TPB = RADIX_WPB * WAVE, DPT = RADIX_BINS / TPB;
   const uint64_t lt = (1ull << lane) - 1ull;
+  uint32_t gp[DPT];  // (in flight during the ranking)
+#pragma unroll
+  for (int j = 0; j < DPT; ++j) gp[j] = pos[(int64_t)(DPT * t + j) * T + tile];
   for (int d = lane; d < RADIX_BINS; d += WAVE) cnt[wv][d] = 0u;
   __builtin_amdgcn_wave_barrier();
-  uint32_t rk[RADIX_ROWS];  // rank of the lane's particle among its wave's equal digits
-  uint32_t ky[RADIX_ROWS];
-  int32_t vl[RADIX_ROWS];
 #pragma unroll
   for (int r = 0; r < RADIX_ROWS; ++r) {
-    const int64_t i = base + (int64_t)(wv * RADIX_ROWS + r) * WAVE + lane;
-    const bool act = i < n;
-    uint32_t k = 0u;
-    int32_t v = 0;
-    if (act) {
-      if constexpr (FIRST) {
-        k = bin_key(cells, species, i, n_cells, S, m);
-        v = (int32_t)i;
-      } else {
-        k = keys_in[i];
-        v = vals_in[i];
-      }
-    }
-    const uint32_t d = (k >> shift) & (RADIX_BINS - 1);
+    const bool act = i0 + r * WAVE < n;
+    const uint32_t d = (ky[r] >> shift) & (RADIX_BINS - 1);
     uint64_t eq = __ballot(act);
 #pragma unroll
     for (int b = 0; b < RADIX_BITS; ++b) {
       const uint64_t bb = __ballot((d >> b) & 1u);
       eq &= ((d >> b) & 1u) ? bb : ~bb;
     }
-    rk[r] = act ? cnt[wv][d] + (uint32_t)__popcll(eq & lt) : 0u;
-    ky[r] = k;
-    vl[r] = v;
+    slot[r] = act ? cnt[wv][d] + (uint32_t)__popcll(eq & lt) : 0u;
     // (every lane has read the count before the leader of its digit advances it)
     __builtin_amdgcn_wave_barrier();
     if (act && (eq & lt) == 0ull) cnt[wv][d] += (uint32_t)__popcll(eq);
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-  // digit totals of the tile and their exclusive scan (thread t owns the
-  // DPT consecutive digits from DPT t)
-  constexpr int TPB = RADIX_WPB * WAVE, DPT = RADIX_BINS / TPB;
-  uint32_t tot[DPT], sum = 0;
+  // digit totals of the tile and their exclusive scan (thread t owns the DPT
+  // consecutive digits from DPT t)
+  uint32_t sum = 0;
 #pragma unroll
-  for (int j = 0; j < DPT; ++j) {
-    tot[j] = 0;
+  for (int j = 0; j < DPT; ++j)
 #pragma unroll
-    for (int w = 0; w < RADIX_WPB; ++w) tot[j] += cnt[w][DPT * t + j];
-    sum += tot[j];
-  }
+    for (int w = 0; w < RADIX_WPB; ++w) sum += cnt[w][DPT * t + j];
   uint32_t gt;
   uint32_t run = block_excl_scan1<TPB, false>(sum, gsum, gt);
 #pragma unroll
   for (int j = 0; j < DPT; ++j) {
     const int d = DPT * t + j;
-    lbase[d] = run;
+    gbase[d] = gp[j] - run;  // (mod 2^32: a slot added gives the position)
     // each wave's first slot within the digit
 #pragma unroll
     for (int w = 0; w < RADIX_WPB; ++w) {
@@ -397,34 +394,85 @@ __global__ void __launch_bounds__(RADIX_WPB * WAVE)
   }
   __syncthreads();
 #pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r)
+    slot[r] += cnt[wv][(ky[r] >> shift) & (RADIX_BINS - 1)];
+}
+
+// Stable scatter of (key, value) by the digit: the tile goes through LDS in
+// digit order, so that every digit's run is written to consecutive addresses.
+// Bound by LDS and latency (6e6 particles: 35 and 30 us for the two passes,
+// 2.8 TB/s; 63 and 51 when each row's loads waited for the row before).
+template <bool FIRST>
+__global__ void __launch_bounds__(RADIX_WPB * WAVE)
+    k_radix_scatter(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
+                    int32_t S, uint32_t m, const uint32_t *keys_in, const int32_t *vals_in,
+                    int shift, int64_t T, const uint32_t *pos, uint32_t *keys_out,
+                    int32_t *vals_out) {
+  __shared__ uint32_t cnt[RADIX_WPB][RADIX_BINS];  // per wave: its digit counts
+  __shared__ uint32_t gbase[RADIX_BINS];
+  __shared__ uint32_t gsum[RADIX_WPB];
+  __shared__ uint32_t lk[RADIX_TILE];
+  __shared__ int32_t lv[RADIX_TILE];
+  const int t = threadIdx.x, wv = t / WAVE, lane = t & (WAVE - 1);
+  const int64_t tile = xcd_tile(T);
+  if (tile >= T) return;
+  const int64_t base = tile * RADIX_TILE;
+  const int64_t i0 = base + (int64_t)wv * RADIX_ROWS * WAVE + lane;
+  uint32_t ky[RADIX_ROWS], slot[RADIX_ROWS];
+  int32_t vl[RADIX_ROWS];
+  load_keys<FIRST>(i0, n, cells, species, n_cells, S, m, keys_in, ky);
+#pragma unroll
   for (int r = 0; r < RADIX_ROWS; ++r) {
-    const int64_t i = base + (int64_t)(wv * RADIX_ROWS + r) * WAVE + lane;
-    if (i < n) {
-      const uint32_t d = (ky[r] >> shift) & (RADIX_BINS - 1);
-      const uint32_t slot = cnt[wv][d] + rk[r];
-      lk[slot] = ky[r];
-      lv[slot] = vl[r];
-    }
+    const int64_t i = i0 + r * WAVE;
+    vl[r] = FIRST ? (int32_t)i : vals_in[i < n ? i : n - 1];
   }
+  radix_ranks(i0, n, ky, shift, T, tile, pos, cnt, gbase, gsum, slot);
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r)
+    if (i0 + r * WAVE < n) {
+      lk[slot[r]] = ky[r];
+      lv[slot[r]] = vl[r];
+    }
   __syncthreads();
   const int64_t tn = n - base < RADIX_TILE ? n - base : RADIX_TILE;
   for (int j = t; j < tn; j += RADIX_WPB * WAVE) {
     const uint32_t k = lk[j];
-    const uint32_t d = (k >> shift) & (RADIX_BINS - 1);
-    const int64_t g = pos[(int64_t)d * T + tile] + (j - (int64_t)lbase[d]);
+    const uint32_t g = gbase[(k >> shift) & (RADIX_BINS - 1)] + (uint32_t)j;
     keys_out[g] = k;
     vals_out[g] = lv[j];
   }
 }
 
 // group offsets from the sorted keys: offsets[g] = first position whose key
-// is >= g (keys above m - 1 mark particles with bad ids, at the end)
-__global__ void k_bin_bounds(int64_t n, const uint32_t *keys, uint32_t m, int64_t *offsets) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t kp = i == 0 ? -1 : (int64_t)keys[i - 1];
-    const int64_t k = i == n ? (int64_t)m : ((int64_t)keys[i] < (int64_t)m ? keys[i] : m);
-    for (int64_t g = kp + 1; g <= k; ++g) offsets[g] = i;
+// is >= g (keys above m - 1 mark particles with bad ids, at the end).  Each
+// thread takes BOUNDS_PT keys in a row (HBM bound: 4 B per particle).
+constexpr int BOUNDS_PT = 8;
+__global__ void __launch_bounds__(256)
+    k_bin_bounds(int64_t n, const uint32_t *keys, uint32_t m, int64_t *offsets) {
+  const int64_t i0 = (blockIdx.x * 256ll + threadIdx.x) * BOUNDS_PT;
+  if (i0 > n) return;
+  uint32_t k[BOUNDS_PT];
+  if (i0 + BOUNDS_PT <= n) {  // (the key buffers are 256-byte aligned)
+    const uint4 *p = reinterpret_cast<const uint4 *>(keys + i0);
+#pragma unroll
+    for (int j = 0; j < BOUNDS_PT / 4; ++j) {
+      const uint4 q = p[j];
+      k[4 * j] = q.x;
+      k[4 * j + 1] = q.y;
+      k[4 * j + 2] = q.z;
+      k[4 * j + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < BOUNDS_PT; ++j) k[j] = i0 + j < n ? keys[i0 + j] : m;
+  }
+  int64_t prev = i0 == 0 ? -1 : (int64_t)keys[i0 - 1];
+#pragma unroll
+  for (int j = 0; j < BOUNDS_PT; ++j) {
+    if (i0 + j > n) break;
+    const int64_t kk = k[j] < m ? (int64_t)k[j] : (int64_t)m;  // (at n: m)
+    for (int64_t g = prev + 1; g <= kk; ++g) offsets[g] = i0 + j;
+    prev = k[j];
   }
 }
 
@@ -587,15 +635,10 @@ hipError_t launch_front(const int64_t *offsets, int32_t n_cells, int32_t S, int6
   return hipGetLastError();
 }
 
-// offsets[m+1] from counts[m]; tiles: scratch of ceil(m / SCAN_TILE) int64
-hipError_t launch_scan(const uint32_t *counts, int64_t m, int64_t *tiles, int64_t *offsets,
-                       hipStream_t s) {
+// exclusive scan of counts[m] (m > 0); tiles: scratch of ceil(m / SCAN_TILE) int64
+static hipError_t launch_scan(const uint32_t *counts, int64_t m, int64_t *tiles,
+                              uint32_t *offsets, hipStream_t s) {
   const int64_t nt = (m + SCAN_TILE - 1) / SCAN_TILE;
-  if (nt == 0) {
-    hipLaunchKernelGGL(k_set_u64, dim3(1), dim3(64), 0, s, reinterpret_cast<uint64_t *>(offsets),
-                       0ull);
-    return hipGetLastError();
-  }
   hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)nt), dim3(SCAN_TPB), 0, s, counts, m, tiles);
   hipLaunchKernelGGL(k_scan_tile_sums, dim3(1), dim3(SCAN_TPB), 0, s, tiles, nt);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nt), dim3(SCAN_TPB), 0, s, counts, m, tiles,
@@ -616,7 +659,7 @@ int64_t bin_hist_entries(int64_t n) {
 
 hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
                       int32_t S, uint32_t *keys0, uint32_t *keys1, int32_t *vals0,
-                      int32_t *vals1, uint32_t *hist, int64_t *pos, int64_t *tiles,
+                      int32_t *vals1, uint32_t *hist, uint32_t *pos, int64_t *tiles,
                       int64_t *offsets, int32_t *perm, int32_t *err, hipStream_t s) {
   const uint32_t m = (uint32_t)((int64_t)n_cells * S);
   int bits = 1;
@@ -626,7 +669,7 @@ hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, i
   uint32_t *kb[2] = {keys0, keys1};
   int32_t *vb[2] = {vals0, vals1};
   if (n > 0) {
-    const int grid = (int)T;
+    const unsigned grid = xcd_grid(T);
     for (int p = 0; p < passes; ++p) {
       const int shift = p * RADIX_BITS;
       const uint32_t *kin = p ? kb[(p - 1) & 1] : nullptr;
@@ -649,7 +692,7 @@ hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, i
                            cells, species, n_cells, S, m, kin, vin, shift, T, pos, kout, vout);
     }
   }
-  hipLaunchKernelGGL(k_bin_bounds, dim3(grid_for(n + 1, 256)), dim3(256), 0, s, n,
+  hipLaunchKernelGGL(k_bin_bounds, dim3((unsigned)(n / (256 * BOUNDS_PT) + 1)), dim3(256), 0, s, n,
                      kb[(passes - 1) & 1], m, offsets);
   return hipGetLastError();
 }
