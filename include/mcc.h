@@ -257,8 +257,10 @@ mcc_status mcc_collide_sorted_noalloc(mcc_ctx *ctx, int64_t n, int32_t n_cells,
  * int32[n].  Particles are grouped by (cell, species) keeping ascending
  * index order inside each group, the sorted step is applied, and the
  * velocities are written back in place.  Same other arguments.  The context
- * grows scratch of about 68 bytes per particle for it (the grouping, the
- * payload in grouped order and in 32-byte records) plus 16 for the binning.
+ * grows scratch of 80 bytes per particle for it (the payload in grouped
+ * order and between passes, keys, places; 46 up to 511 groups, 86 and 92 where
+ * the group numbers have more than 18 and 27 bits), and mcc_bin's 8 B per 4096
+ * particles and digit bin.
  */
 mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells,
                        const int32_t *species_id, int32_t n_cells,
@@ -349,7 +351,7 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
  * then counts the particles with valid ids).  Cost: ceil(b/9) passes of a
  * radix sort over 9-bit digits, b the bits of n_cells * n_species, each
  * reading and writing 8 B per particle.  Scratch: 16 B per particle plus
- * 12 B per 4096 particles per digit bin (512 bins), owned by the context.
+ * 8 B per 4096 particles per digit bin (512 bins), owned by the context.
  * Errors: MCC_ERR_UNSUPPORTED above 2^31 - 1 particles or groups.
  */
 mcc_status mcc_bin(mcc_ctx *ctx, int64_t n, const int32_t *cells,

@@ -59,13 +59,16 @@ int64_t rebin_tiles_needed(int64_t n, int64_t m);
 hipError_t launch_rebin(int64_t n, int64_t m, int32_t S, int32_t n_cells, const int64_t *off,
                         const int32_t *cells_new, int64_t *off_new, int32_t *perm,
                         void *scratch, int64_t *tiles, int32_t *err, hipStream_t s);
-hipError_t launch_gather_rec(int64_t n, const int32_t *perm, const double *w, const double *vx,
-                             const double *vy, const double *vz, void *rec, double *gw,
-                             double *gx, double *gy, double *gz, hipStream_t s);
-hipError_t launch_scatter_back_rec(int64_t n, const int32_t *perm, const double *gw,
-                                   const double *gx, const double *gy, const double *gz,
-                                   void *rec, double *vx, double *vy, double *vz,
-                                   hipStream_t s);
+int bin_passes(int64_t m);
+hipError_t launch_bin_move(int64_t n, const int32_t *cells, const int32_t *species,
+                           int32_t n_cells, int32_t S, uint32_t *keys0, uint32_t *keys1,
+                           uint32_t *const *place, uint16_t *const *local, uint32_t *hist,
+                           uint32_t *pos, int64_t *tiles, int64_t *offsets,
+                           const double *const *payload, double *g, double *rec, int64_t n_pad,
+                           int32_t *err, hipStream_t s);
+hipError_t launch_move_back(int64_t n, int64_t m, uint32_t *const *place, uint16_t *const *local,
+                            double *g, double *rec, int64_t n_pad, double *const *v,
+                            hipStream_t s);
 hipError_t launch_gather(int64_t n, const int32_t *perm, const double *w, const double *vx,
                          const double *vy, const double *vz, double *gw, double *gx, double *gy,
                          double *gz, hipStream_t s);
@@ -166,8 +169,9 @@ struct mcc_ctx {
   // counters (zero between launches: each launch resets them at its end, so
   // launches of one context must not overlap)
   DevBuf work;
-  // unsorted entry
-  DevBuf tiles, off, perm, gw, gx, gy, gz, rec;
+  // unsorted entry: the payload in grouped order and between the passes, and
+  // where a pass's items went (mcc_rebin uses `grouped` for its copy)
+  DevBuf tiles, off, grouped, rec, place[3], local;
   DevBuf bin_k0, bin_k1, bin_v0, bin_v1, bin_hist, bin_pos;  // radix-sort scratch
   // reverse-mode form: per-workgroup scratch (cells up to 4096 particles,
   // and above), per-cell lnL adjoints
@@ -622,9 +626,10 @@ void mcc_destroy(mcc_ctx *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   ctx->big.release();
-  for (DevBuf *b : {&ctx->lists, &ctx->counts, &ctx->tiles, &ctx->off, &ctx->perm,
+  for (DevBuf *b : {&ctx->lists, &ctx->counts, &ctx->tiles, &ctx->off, &ctx->rec,
+                    &ctx->place[0], &ctx->place[1], &ctx->place[2], &ctx->local,
                     &ctx->bin_k0, &ctx->bin_k1, &ctx->bin_v0, &ctx->bin_v1, &ctx->bin_hist,
-                    &ctx->bin_pos, &ctx->gw, &ctx->gx, &ctx->gy, &ctx->gz, &ctx->rec, &ctx->n97,
+                    &ctx->bin_pos, &ctx->grouped, &ctx->n97,
                     &ctx->work, &ctx->rb, &ctx->adj_small, &ctx->adj_big,
                     &ctx->adj_part})
     b->release();
@@ -893,16 +898,29 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
   return finish(ctx);
 }
 
+// scratch of the radix passes: two key buffers, the tiles' digit histograms
+// and their scan
+static bool ensure_passes(mcc_ctx *ctx, int64_t n) {
+  const size_t nn = (size_t)std::max<int64_t>(n, 1);
+  const int64_t hb = bin_hist_entries(n);
+  return ctx->bin_k0.ensure(4 * nn) && ctx->bin_k1.ensure(4 * nn) &&
+         ctx->bin_hist.ensure(sizeof(uint32_t) * (size_t)hb) &&
+         ctx->bin_pos.ensure(sizeof(uint32_t) * (size_t)hb) &&
+         ctx->tiles.ensure(sizeof(int64_t) * (size_t)scan_tiles_needed(hb));
+}
+
+// w, vx, vy, vz in grouped order: four arrays, each starting on a memory line
+static int64_t grouped_pad(int64_t n) { return (std::max<int64_t>(n, 1) + 31) / 32 * 32; }
+static size_t grouped_bytes(int64_t n) { return 4 * sizeof(double) * (size_t)grouped_pad(n); }
+static void grouped_arrays(mcc_ctx *ctx, int64_t n, double *g[4]) {
+  for (int i = 0; i < 4; ++i) g[i] = ctx->grouped.as<double>() + i * grouped_pad(n);
+}
+
 static mcc_status bin_into(mcc_ctx *ctx, int64_t n, const int32_t *cells,
                            const int32_t *species_id, int32_t n_cells, int32_t n_species,
                            int64_t *offsets, int32_t *perm) {
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
-  const int64_t hb = bin_hist_entries(n);  // digit histograms of the tiles
-  if (!ctx->bin_k0.ensure(4 * nn) || !ctx->bin_k1.ensure(4 * nn) ||
-      !ctx->bin_v0.ensure(4 * nn) || !ctx->bin_v1.ensure(4 * nn) ||
-      !ctx->bin_hist.ensure(sizeof(uint32_t) * (size_t)hb) ||
-      !ctx->bin_pos.ensure(sizeof(uint32_t) * (size_t)hb) ||
-      !ctx->tiles.ensure(sizeof(int64_t) * (size_t)scan_tiles_needed(hb)))
+  if (!ensure_passes(ctx, n) || !ctx->bin_v0.ensure(4 * nn) || !ctx->bin_v1.ensure(4 * nn))
     return MCC_ERR_OOM;
   return from_hip(launch_bin(n, cells, species_id, n_cells, n_species,
                              ctx->bin_k0.as<uint32_t>(), ctx->bin_k1.as<uint32_t>(),
@@ -959,17 +977,15 @@ mcc_status mcc_rebin(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t n_species
   if (st != MCC_OK) return st;
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
   if (any && n > 0 && (int64_t)n_cells * n_species > 0) {
-    if (!ctx->gw.ensure(sizeof(double) * nn) || !ctx->gx.ensure(sizeof(double) * nn) ||
-        !ctx->gy.ensure(sizeof(double) * nn) || !ctx->gz.ensure(sizeof(double) * nn))
-      return MCC_ERR_OOM;
-    HIP_TRY(launch_gather(n, perm_out, weights, vx, vy, vz, ctx->gw.as<double>(),
-                          ctx->gx.as<double>(), ctx->gy.as<double>(), ctx->gz.as<double>(),
-                          ctx->stream));
+    if (!ctx->grouped.ensure(grouped_bytes(n))) return MCC_ERR_OOM;
+    double *g[4];
+    grouped_arrays(ctx, n, g);
+    HIP_TRY(launch_gather(n, perm_out, weights, vx, vy, vz, g[0], g[1], g[2], g[3], ctx->stream));
     const size_t b = sizeof(double) * (size_t)n;
-    HIP_TRY(hipMemcpyAsync(weights, ctx->gw.p, b, hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(vx, ctx->gx.p, b, hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(vy, ctx->gy.p, b, hipMemcpyDeviceToDevice, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(vz, ctx->gz.p, b, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(hipMemcpyAsync(weights, g[0], b, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(hipMemcpyAsync(vx, g[1], b, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(hipMemcpyAsync(vy, g[2], b, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(hipMemcpyAsync(vz, g[3], b, hipMemcpyDeviceToDevice, ctx->stream));
   }
   return finish(ctx);
 }
@@ -1010,28 +1026,41 @@ mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int3
   const int64_t m = (int64_t)n_cells * n_species;
   if (m > (int64_t)INT32_MAX) return MCC_ERR_UNSUPPORTED;
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
-  if (!ctx->off.ensure(sizeof(int64_t) * (size_t)(m + 1)) ||
-      !ctx->perm.ensure(sizeof(int32_t) * nn) || !ctx->gw.ensure(sizeof(double) * nn) ||
-      !ctx->gx.ensure(sizeof(double) * nn) || !ctx->gy.ensure(sizeof(double) * nn) ||
-      !ctx->gz.ensure(sizeof(double) * nn) || !ctx->rec.ensure(32 * nn))
-    return MCC_ERR_OOM;
-  st = bin_into(ctx, n, cells, species_id, n_cells, n_species, ctx->off.as<int64_t>(),
-                ctx->perm.as<int32_t>());
-  if (st != MCC_OK) return st;
-  HIP_TRY(launch_gather_rec(n, ctx->perm.as<int32_t>(), weights, vx, vy, vz, ctx->rec.p,
-                            ctx->gw.as<double>(), ctx->gx.as<double>(), ctx->gy.as<double>(),
-                            ctx->gz.as<double>(), ctx->stream));
+  const int passes = bin_passes(m);
+  bool ok = ctx->off.ensure(sizeof(int64_t) * (size_t)(m + 1)) &&
+            ctx->grouped.ensure(grouped_bytes(n)) && ensure_passes(ctx, n) &&
+            ctx->local.ensure(2 * nn * (size_t)passes) &&
+            (passes == 1 || ctx->rec.ensure(grouped_bytes(n)));
+  uint32_t *place[4] = {};
+  uint16_t *local[4] = {};
+  for (int p = 0; ok && p < passes; ++p) {
+    local[p] = ctx->local.as<uint16_t>() + (size_t)p * nn;
+    if (p > 0 && p == passes - 1) {  // over the pass's input keys
+      place[p] = ((p - 1) & 1 ? ctx->bin_k1 : ctx->bin_k0).as<uint32_t>();
+    } else {
+      ok = ctx->place[p].ensure(4 * nn);
+      place[p] = ctx->place[p].as<uint32_t>();
+    }
+  }
+  if (!ok) return MCC_ERR_OOM;
+  double *g[4];
+  grouped_arrays(ctx, n, g);
+  const double *const payload[4] = {weights, vx, vy, vz};
+  HIP_TRY(launch_bin_move(n, cells, species_id, n_cells, n_species, ctx->bin_k0.as<uint32_t>(),
+                          ctx->bin_k1.as<uint32_t>(), place, local,
+                          ctx->bin_hist.as<uint32_t>(), ctx->bin_pos.as<uint32_t>(),
+                          ctx->tiles.as<int64_t>(), ctx->off.as<int64_t>(), payload, g[0],
+                          ctx->rec.as<double>(), grouped_pad(n), ctx->err, ctx->stream));
   const bool v = ctx->validate;
   ctx->validate = false;
-  st = mcc_collide_sorted(ctx, n, n_cells, n_species, ctx->off.as<int64_t>(),
-                          ctx->gw.as<double>(), ctx->gx.as<double>(), ctx->gy.as<double>(),
-                          ctx->gz.as<double>(), cell_volume, cell_volume_scalar, species, n_coll,
-                          coll, dt, coulomb_log, seed, step, p, stats, cell_corr_pairs);
+  st = mcc_collide_sorted(ctx, n, n_cells, n_species, ctx->off.as<int64_t>(), g[0], g[1], g[2],
+                          g[3], cell_volume, cell_volume_scalar, species, n_coll, coll, dt,
+                          coulomb_log, seed, step, p, stats, cell_corr_pairs);
   ctx->validate = v;
   if (st != MCC_OK) return st;
-  HIP_TRY(launch_scatter_back_rec(n, ctx->perm.as<int32_t>(), ctx->gw.as<double>(),
-                                  ctx->gx.as<double>(), ctx->gy.as<double>(),
-                                  ctx->gz.as<double>(), ctx->rec.p, vx, vy, vz, ctx->stream));
+  double *const v_out[3] = {vx, vy, vz};
+  HIP_TRY(launch_move_back(n, m, place, local, g[0], ctx->rec.as<double>(), grouped_pad(n),
+                           v_out, ctx->stream));
   return finish(ctx);
 }
 

@@ -490,53 +490,121 @@ __global__ void k_gather(int64_t n, const int32_t *perm, const double *w, const 
   }
 }
 
-// The unsorted entry's payload moves through 32-byte records (w, vx, vy, vz)
-// of a context-owned array in the caller's order: a particle's random access
-// is then one aligned 32-byte record, one memory segment, instead of an 8-byte
-// word in each of four arrays.  Packing and unpacking stream.
-struct alignas(32) Rec4 {
-  double w, x, y, z;
+// The unsorted entry's payload travels with the keys through the radix passes,
+// each of its four arrays staged in LDS in digit order and written as runs of
+// a digit (8 particles at 512 digits and tiles of 4096): neighbouring tiles
+// continue each other's runs, so memory lines are used whole, where one random
+// access per particle over the whole population costs a line each.  `place` and
+// `local` keep, in a tile's digit order, where its items went and which of the
+// tile's they are; the way back follows them, pass by pass.
+struct Payload {
+  const double *in[4];  // w, vx, vy, vz
+  double *out[4];
 };
 
-__global__ void k_pack_rec(int64_t n, const double *w, const double *vx, const double *vy,
-                           const double *vz, Rec4 *rec) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    rec[i] = Rec4{w[i], vx[i], vy[i], vz[i]};
-}
-
-__global__ void k_gather_rec(int64_t n, const int32_t *perm, const Rec4 *rec, double *gw,
-                             double *gx, double *gy, double *gz) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = perm[j];
-    if (i < 0 || i >= n) continue;
-    const Rec4 r = rec[i];
-    gw[j] = r.w;
-    gx[j] = r.x;
-    gy[j] = r.y;
-    gz[j] = r.z;
+template <bool FIRST>
+__global__ void __launch_bounds__(RADIX_WPB * WAVE)
+    k_radix_move(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
+                 int32_t S, uint32_t m, const uint32_t *keys_in, int shift, int64_t T,
+                 const uint32_t *pos, uint32_t *keys_out, uint32_t *place, uint16_t *local,
+                 Payload P) {
+  constexpr int TPB = RADIX_WPB * WAVE;
+  __shared__ uint32_t cnt[RADIX_WPB][RADIX_BINS];
+  __shared__ uint32_t gbase[RADIX_BINS];
+  __shared__ uint32_t gsum[RADIX_WPB];
+  __shared__ double stage[RADIX_TILE];
+  uint32_t *lk = reinterpret_cast<uint32_t *>(stage);  // keys and indices, before the payload
+  uint16_t *li = reinterpret_cast<uint16_t *>(lk + RADIX_TILE);
+  const int t = threadIdx.x, wv = t / WAVE, lane = t & (WAVE - 1);
+  const int64_t tile = xcd_tile(T);
+  if (tile >= T) return;
+  const int64_t base = tile * RADIX_TILE;
+  const int64_t i0 = base + (int64_t)wv * RADIX_ROWS * WAVE + lane;
+  const int tn = (int)(n - base < RADIX_TILE ? n - base : RADIX_TILE);
+  uint32_t ky[RADIX_ROWS], slot[RADIX_ROWS];
+  load_keys<FIRST>(i0, n, cells, species, n_cells, S, m, keys_in, ky);
+  double q[RADIX_ROWS];  // one array's rows, in flight
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r) {
+    const int64_t i = i0 + r * WAVE;
+    q[r] = P.in[0][i < n ? i : n - 1];
+  }
+  radix_ranks(i0, n, ky, shift, T, tile, pos, cnt, gbase, gsum, slot);
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r)
+    if (i0 + r * WAVE < n) {
+      lk[slot[r]] = ky[r];
+      li[slot[r]] = (uint16_t)(i0 + r * WAVE - base);
+    }
+  __syncthreads();
+  uint32_t g[RADIX_ROWS];  // output positions of the slots this thread writes
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r) {
+    const int j = t + r * TPB;
+    if (j < tn) {
+      const uint32_t k = lk[j];
+      g[r] = gbase[(k >> shift) & (RADIX_BINS - 1)] + (uint32_t)j;
+      keys_out[g[r]] = k;
+      place[base + j] = g[r];
+      local[base + j] = li[j];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RADIX_ROWS; ++r)
+      if (i0 + r * WAVE < n) stage[slot[r]] = q[r];
+    if (c < 3) {
+#pragma unroll
+      for (int r = 0; r < RADIX_ROWS; ++r) {
+        const int64_t i = i0 + r * WAVE;
+        q[r] = P.in[c + 1][i < n ? i : n - 1];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RADIX_ROWS; ++r)
+      if (t + r * TPB < tn) P.out[c][g[r]] = stage[t + r * TPB];
   }
 }
 
-// whole records back (the weight unchanged), then the velocities out
-__global__ void k_scatter_rec(int64_t n, const int32_t *perm, const double *gw, const double *gx,
-                              const double *gy, const double *gz, Rec4 *rec) {
-  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
-       j += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = perm[j];
-    if (i < 0 || i >= n) continue;
-    rec[i] = Rec4{gw[j], gx[j], gy[j], gz[j]};
+// the way back through one pass: the velocities of its output (in) to its
+// input.  Read in runs and put in order in LDS: gathered by each item instead,
+// with 8 B of a line per request, the two passes took 0.74 ms at 2.15e7.
+__global__ void __launch_bounds__(RADIX_WPB * WAVE)
+    k_move_back(int64_t n, int64_t T, const uint32_t *place, const uint16_t *local, Payload P) {
+  constexpr int TPB = RADIX_WPB * WAVE;
+  __shared__ double stage[RADIX_TILE];
+  const int t = threadIdx.x;
+  const int64_t tile = xcd_tile(T);
+  if (tile >= T) return;
+  const int64_t base = tile * RADIX_TILE;
+  const int tn = (int)(n - base < RADIX_TILE ? n - base : RADIX_TILE);
+  uint32_t g[RADIX_ROWS], li[RADIX_ROWS];
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r) {
+    const int j = t + r * TPB, jc = j < tn ? j : tn - 1;
+    g[r] = place[base + jc];
+    li[r] = local[base + jc];
   }
-}
-
-__global__ void k_unpack_v(int64_t n, const Rec4 *rec, double *vx, double *vy, double *vz) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const Rec4 r = rec[i];
-    vx[i] = r.x;
-    vy[i] = r.y;
-    vz[i] = r.z;
+  double q[RADIX_ROWS];  // one array's rows, in flight
+#pragma unroll
+  for (int r = 0; r < RADIX_ROWS; ++r) q[r] = P.in[1][g[r]];
+#pragma unroll
+  for (int c = 1; c < 4; ++c) {
+#pragma unroll
+    for (int r = 0; r < RADIX_ROWS; ++r)
+      if (t + r * TPB < tn) stage[li[r]] = q[r];
+    if (c < 3) {
+#pragma unroll
+      for (int r = 0; r < RADIX_ROWS; ++r) q[r] = P.in[c + 1][g[r]];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RADIX_ROWS; ++r)
+      if (t + r * TPB < tn) P.out[c][base + t + r * TPB] = stage[t + r * TPB];
+    __syncthreads();
   }
 }
 
@@ -657,43 +725,114 @@ int64_t bin_hist_entries(int64_t n) {
   return (int64_t)RADIX_BINS * (T > 0 ? T : 1);
 }
 
+// radix passes of the group keys (which run up to m, the bad-id key)
+int bin_passes(int64_t m) {
+  int bits = 1;
+  while (bits < 32 && ((uint32_t)m >> bits) != 0u) ++bits;
+  return (bits + RADIX_BITS - 1) / RADIX_BITS;
+}
+
+// the tiles' digit histograms of one pass and their scan into pos
+template <bool FIRST>
+static hipError_t launch_pass_positions(int64_t n, const int32_t *cells, const int32_t *species,
+                                        int32_t n_cells, int32_t S, uint32_t m,
+                                        const uint32_t *keys, int shift, uint32_t *hist,
+                                        uint32_t *pos, int64_t *tiles, int32_t *err,
+                                        hipStream_t s) {
+  const int64_t T = bin_tiles(n);
+  hipLaunchKernelGGL(k_radix_hist<FIRST>, dim3(xcd_grid(T)), dim3(RADIX_WPB * WAVE), 0, s, n,
+                     cells, species, n_cells, S, m, keys, shift, T, hist, err);
+  return launch_scan(hist, (int64_t)RADIX_BINS * T, tiles, pos, s);
+}
+
+static hipError_t launch_bounds(int64_t n, const uint32_t *keys, uint32_t m, int64_t *offsets,
+                                hipStream_t s) {
+  hipLaunchKernelGGL(k_bin_bounds, dim3((unsigned)(n / (256 * BOUNDS_PT) + 1)), dim3(256), 0, s,
+                     n, keys, m, offsets);
+  return hipGetLastError();
+}
+
 hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
                       int32_t S, uint32_t *keys0, uint32_t *keys1, int32_t *vals0,
                       int32_t *vals1, uint32_t *hist, uint32_t *pos, int64_t *tiles,
                       int64_t *offsets, int32_t *perm, int32_t *err, hipStream_t s) {
   const uint32_t m = (uint32_t)((int64_t)n_cells * S);
-  int bits = 1;
-  while (bits < 32 && (m >> bits) != 0u) ++bits;  // keys run up to m (the bad-id key)
-  const int passes = (bits + RADIX_BITS - 1) / RADIX_BITS;
+  const int passes = bin_passes(m);
   const int64_t T = bin_tiles(n);
   uint32_t *kb[2] = {keys0, keys1};
   int32_t *vb[2] = {vals0, vals1};
-  if (n > 0) {
-    const unsigned grid = xcd_grid(T);
-    for (int p = 0; p < passes; ++p) {
-      const int shift = p * RADIX_BITS;
-      const uint32_t *kin = p ? kb[(p - 1) & 1] : nullptr;
-      const int32_t *vin = p ? vb[(p - 1) & 1] : nullptr;
-      uint32_t *kout = kb[p & 1];
-      int32_t *vout = p == passes - 1 ? perm : vb[p & 1];
-      if (p == 0)
-        hipLaunchKernelGGL(k_radix_hist<true>, dim3(grid), dim3(RADIX_WPB * WAVE), 0, s, n,
-                           cells, species, n_cells, S, m, kin, shift, T, hist, err);
-      else
-        hipLaunchKernelGGL(k_radix_hist<false>, dim3(grid), dim3(RADIX_WPB * WAVE), 0, s, n,
-                           cells, species, n_cells, S, m, kin, shift, T, hist, err);
-      hipError_t e = launch_scan(hist, (int64_t)RADIX_BINS * T, tiles, pos, s);
-      if (e != hipSuccess) return e;
-      if (p == 0)
-        hipLaunchKernelGGL(k_radix_scatter<true>, dim3(grid), dim3(RADIX_WPB * WAVE), 0, s, n,
-                           cells, species, n_cells, S, m, kin, vin, shift, T, pos, kout, vout);
-      else
-        hipLaunchKernelGGL(k_radix_scatter<false>, dim3(grid), dim3(RADIX_WPB * WAVE), 0, s, n,
-                           cells, species, n_cells, S, m, kin, vin, shift, T, pos, kout, vout);
-    }
+  for (int p = 0; n > 0 && p < passes; ++p) {
+    const int shift = p * RADIX_BITS;
+    const uint32_t *kin = p ? kb[(p - 1) & 1] : nullptr;
+    const int32_t *vin = p ? vb[(p - 1) & 1] : nullptr;
+    int32_t *vout = p == passes - 1 ? perm : vb[p & 1];
+    auto positions = p ? launch_pass_positions<false> : launch_pass_positions<true>;
+    const hipError_t e = positions(n, cells, species, n_cells, S, m, kin, shift, hist, pos,
+                                   tiles, err, s);
+    if (e != hipSuccess) return e;
+    auto scatter = p ? k_radix_scatter<false> : k_radix_scatter<true>;
+    hipLaunchKernelGGL(scatter, dim3(xcd_grid(T)), dim3(RADIX_WPB * WAVE), 0, s, n, cells,
+                       species, n_cells, S, m, kin, vin, shift, T, pos, kb[p & 1], vout);
   }
-  hipLaunchKernelGGL(k_bin_bounds, dim3((unsigned)(n / (256 * BOUNDS_PT) + 1)), dim3(256), 0, s, n,
-                     kb[(passes - 1) & 1], m, offsets);
+  return launch_bounds(n, kb[(passes - 1) & 1], m, offsets, s);
+}
+
+// where the payload is after pass p: the last pass leaves it in g, the ones
+// before take turns, so that more passes need no more memory (g and rec are
+// four arrays of n_pad >= n doubles each; a single pass uses no rec)
+static double *payload_buffer(int passes, int p, double *g, double *rec) {
+  return (passes - 1 - p) & 1 ? rec : g;
+}
+
+// The grouping of launch_bin with the payload moved through the passes: g
+// receives w, vx, vy, vz in grouped order.  place, local: one array of n
+// each per pass; the last of two or more passes may put its places over its
+// input keys, keys0 or keys1 (a tile's keys are read before they are written).
+hipError_t launch_bin_move(int64_t n, const int32_t *cells, const int32_t *species,
+                           int32_t n_cells, int32_t S, uint32_t *keys0, uint32_t *keys1,
+                           uint32_t *const *place, uint16_t *const *local, uint32_t *hist,
+                           uint32_t *pos, int64_t *tiles, int64_t *offsets,
+                           const double *const *payload, double *g, double *rec, int64_t n_pad,
+                           int32_t *err, hipStream_t s) {
+  const uint32_t m = (uint32_t)((int64_t)n_cells * S);
+  const int passes = bin_passes(m);
+  const int64_t T = bin_tiles(n);
+  uint32_t *kb[2] = {keys0, keys1};
+  for (int p = 0; n > 0 && p < passes; ++p) {
+    const int shift = p * RADIX_BITS;
+    const uint32_t *kin = p ? kb[(p - 1) & 1] : nullptr;
+    auto positions = p ? launch_pass_positions<false> : launch_pass_positions<true>;
+    const hipError_t e = positions(n, cells, species, n_cells, S, m, kin, shift, hist, pos,
+                                   tiles, err, s);
+    if (e != hipSuccess) return e;
+    Payload P;
+    for (int c = 0; c < 4; ++c) {
+      P.in[c] = p ? payload_buffer(passes, p - 1, g, rec) + c * n_pad : payload[c];
+      P.out[c] = payload_buffer(passes, p, g, rec) + c * n_pad;
+    }
+    auto move = p ? k_radix_move<false> : k_radix_move<true>;
+    hipLaunchKernelGGL(move, dim3(xcd_grid(T)), dim3(RADIX_WPB * WAVE), 0, s, n, cells, species,
+                       n_cells, S, m, kin, shift, T, pos, kb[p & 1], place[p], local[p],
+                       P);
+  }
+  return launch_bounds(n, kb[(passes - 1) & 1], m, offsets, s);
+}
+
+// the velocities back to the caller's order, through the passes in reverse
+hipError_t launch_move_back(int64_t n, int64_t m, uint32_t *const *place, uint16_t *const *local,
+                            double *g, double *rec, int64_t n_pad, double *const *v,
+                            hipStream_t s) {
+  const int passes = bin_passes(m);
+  const int64_t T = bin_tiles(n);
+  for (int p = passes - 1; n > 0 && p >= 0; --p) {
+    Payload P;
+    for (int c = 1; c < 4; ++c) {
+      P.in[c] = payload_buffer(passes, p, g, rec) + c * n_pad;
+      P.out[c] = p ? payload_buffer(passes, p - 1, g, rec) + c * n_pad : v[c - 1];
+    }
+    hipLaunchKernelGGL(k_move_back, dim3(xcd_grid(T)), dim3(RADIX_WPB * WAVE), 0, s, n, T,
+                       place[p], local[p], P);
+  }
   return hipGetLastError();
 }
 
@@ -805,30 +944,5 @@ hipError_t launch_gather(int64_t n, const int32_t *perm, const double *w, const 
                      gw, gx, gy, gz);
   return hipGetLastError();
 }
-
-// gather through records: rec (32 * n bytes, 32-byte aligned) is scratch
-hipError_t launch_gather_rec(int64_t n, const int32_t *perm, const double *w, const double *vx,
-                             const double *vy, const double *vz, void *rec, double *gw,
-                             double *gx, double *gy, double *gz, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  Rec4 *r = static_cast<Rec4 *>(rec);
-  hipLaunchKernelGGL(k_pack_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, w, vx, vy, vz, r);
-  hipLaunchKernelGGL(k_gather_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, perm, r, gw, gx,
-                     gy, gz);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter_back_rec(int64_t n, const int32_t *perm, const double *gw,
-                                   const double *gx, const double *gy, const double *gz,
-                                   void *rec, double *vx, double *vy, double *vz,
-                                   hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  Rec4 *r = static_cast<Rec4 *>(rec);
-  hipLaunchKernelGGL(k_scatter_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, perm, gw, gx, gy,
-                     gz, r);
-  hipLaunchKernelGGL(k_unpack_v, dim3(grid_for(n, 256)), dim3(256), 0, s, n, r, vx, vy, vz);
-  return hipGetLastError();
-}
-
 
 }  // namespace mcc
