@@ -6,9 +6,9 @@
 //   CAP  largest cell (all species) this variant holds
 //   KR   type of the pair kinematics (double, or float for the FP32 form)
 //   REL  relativistic (Appendix A; FP64 only)
-//   LAY  where the cell lives: LAYOUT_LDS (everything in LDS), LAYOUT_COMPACT
-//        (LDS with aliased scratch and the weights read from the input, for
-//        cells up to 4096), LAYOUT_GLOBAL (per-workgroup global scratch for
+//   LAY  where the cell lives: LAYOUT_COMPACT (LDS with aliased scratch, the
+//        weights read from the input above 1024 particles, for cells up to
+//        4096), LAYOUT_GLOBAL (per-workgroup global scratch for
 //        cells up to MCC_MAX_CELL; one, four or eight waves per cell, whose
 //        scratch accesses the workgroup barriers order as they do LDS ones,
 //        the waves of a workgroup sharing their CU's L1)
@@ -27,7 +27,7 @@ namespace mcc {
 
 // Where the arrays of a cell live (all cross-thread data is in LDS unless the
 // layout is GLOBAL, whose workgroup is a single wave).
-enum Layout : int { LAYOUT_LDS = 0, LAYOUT_COMPACT = 1, LAYOUT_GLOBAL = 2 };
+enum Layout : int { LAYOUT_COMPACT = 1, LAYOUT_GLOBAL = 2 };
 enum Pairing : int { PAIR_ORDER_N = 0, PAIR_NXN = 1, PAIR_DUPLICITY = 2 };
 
 struct CellMem {
@@ -40,8 +40,8 @@ struct CellMem {
   double *kbuf;           // per-pair K / U of the energy loop (+ h(-mu) for REL)
   uint32_t *slotbuf;      // GLOBAL: per-item bucket slots
   double *bx, *by, *bz;   // GLOBAL: pre-scatter snapshot
-  // tangent form: tangent of the velocities, its pre-scatter snapshot, and
-  // per-pair tangents of K (then of U)
+  // tangent form: tangent of the velocities, its pre-scatter snapshot
+  // (GLOBAL), and per-pair tangents of K (then of U)
   double *tx, *ty, *tz, *btx, *bty, *btz, *kdot;
 };
 
@@ -684,7 +684,7 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
   static_assert(PAIRING == PAIR_ORDER_N || !(TAN || DIAG),
                 "the N x N and duplicity pairings have no tangent or diagnostic form");
   static_assert(!GL || TPC <= 512, "the global layout runs at most 8 waves per cell");
-  static_assert(!TAN || (!REL && sizeof(KR) == 8 && LAY != LAYOUT_COMPACT && !DIAG),
+  static_assert(!TAN || (!REL && sizeof(KR) == 8 && !DIAG),
                 "the tangent form is FP64 non-relativistic, without diagnostics");
   // FP32 kinematics in the compact layout from 1024 particles up: the N97
   // table in LDS as the FP32 values its uses take (room the smaller
@@ -747,38 +747,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
 #endif
 
   CellMem M;
-  double *wdst = nullptr;  // where the load phase copies the weights (LDS layout)
+  double *wdst = nullptr;  // where the load phase copies the weights
   M.cnt = lcnt;
   M.slotbuf = nullptr;
   M.bx = M.by = M.bz = nullptr;
-  if constexpr (LAY == LAYOUT_LDS) {
-    __shared__ double lv[4 * CAP];
-    __shared__ uint64_t lscr[CAP + 1];
-    __shared__ __attribute__((aligned(16))) uint16_t lidx[6 * CAP + 4];
-    M.vx = lv;
-    M.vy = lv + CAP;
-    M.vz = lv + 2 * CAP;
-    wdst = lv + 3 * CAP;
-    M.w = wdst;
-    M.key = reinterpret_cast<uint32_t *>(lscr);
-    M.kbuf = reinterpret_cast<double *>(lscr);
-    M.list0 = lidx;
-    M.list1 = lidx + CAP;
-    M.ord0 = lidx + 2 * CAP;
-    M.ord1 = lidx + 3 * CAP;
-    M.mem = lidx + 4 * CAP;
-    M.word = lidx + 5 * CAP;
-    if constexpr (TAN) {
-      __shared__ double lt[7 * CAP];
-      M.tx = lt;
-      M.ty = lt + CAP;
-      M.tz = lt + 2 * CAP;
-      M.btx = lt + 3 * CAP;
-      M.bty = lt + 4 * CAP;
-      M.btz = lt + 5 * CAP;
-      M.kdot = lt + 6 * CAP;
-    }
-  } else if constexpr (LAY == LAYOUT_COMPACT) {
+  if constexpr (LAY == LAYOUT_COMPACT) {
     __shared__ double lv[(W_LDS ? 4 : 3) * CAP];
     __shared__ __attribute__((aligned(16))) uint16_t lidx[(HAS_WORD ? 6 : 5) * CAP + 4];
     M.vx = lv;
@@ -798,6 +771,15 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
     M.key = reinterpret_cast<uint32_t *>(lidx + 2 * CAP);
     M.kbuf = reinterpret_cast<double *>(lcnt);
     M.word = HAS_WORD ? lidx + 5 * CAP : M.list0;  // (list0: scratch of the plan's weight pass)
+    if constexpr (TAN) {
+      // the tangent and, one per pair, the tangents of the pair energies (the
+      // snapshot of the tangent is in registers, as the velocities' is)
+      __shared__ double lt[3 * CAP + CAP / 2 + 1];
+      M.tx = lt;
+      M.ty = lt + CAP;
+      M.tz = lt + 2 * CAP;
+      M.kdot = lt + 3 * CAP;
+    }
   } else {
     char *base = A.big_scratch + (uint64_t)blockIdx.x * A.big_stride;
     double *dv = reinterpret_cast<double *>(base);
@@ -1062,6 +1044,14 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
       MCC_PHASE(1);  // snapshot and shuffles
       // pre-scatter snapshot (Alg. 1, first step)
       double bx[GL ? 1 : PPT], by[GL ? 1 : PPT], bz[GL ? 1 : PPT];
+      constexpr int TPT = TAN && !GL ? PPT : 1;
+      double btx[TPT], bty[TPT], btz[TPT];  // tangent form: of the tangent
+#define SNAPX(j, e) (BIG ? M.bx[e] : bx[BIG ? 0 : (j)])
+#define SNAPY(j, e) (BIG ? M.by[e] : by[BIG ? 0 : (j)])
+#define SNAPZ(j, e) (BIG ? M.bz[e] : bz[BIG ? 0 : (j)])
+#define SNAPTX(j, e) (BIG ? M.btx[e] : btx[BIG ? 0 : (j)])
+#define SNAPTY(j, e) (BIG ? M.bty[e] : bty[BIG ? 0 : (j)])
+#define SNAPTZ(j, e) (BIG ? M.btz[e] : btz[BIG ? 0 : (j)])
       if constexpr (!GL && !TAN) {
         // every owned slot (those past n hold LDS contents nobody uses)
 #pragma unroll
@@ -1084,15 +1074,12 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             bz[j] = M.vz[e];
           }
           if constexpr (TAN) {
-            M.btx[e] = M.tx[e];
-            M.bty[e] = M.ty[e];
-            M.btz[e] = M.tz[e];
+            SNAPTX(j, e) = M.tx[e];
+            SNAPTY(j, e) = M.ty[e];
+            SNAPTZ(j, e) = M.tz[e];
           }
         }
       });
-#define SNAPX(j, e) (BIG ? M.bx[e] : bx[BIG ? 0 : (j)])
-#define SNAPY(j, e) (BIG ? M.by[e] : by[BIG ? 0 : (j)])
-#define SNAPZ(j, e) (BIG ? M.bz[e] : bz[BIG ? 0 : (j)])
 
       // random binary pairs (Fig. 1)
       // L0, L1: the shuffled lists of species a and b
@@ -1315,9 +1302,9 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             P[4] += to_b ? dy : 0.0;
             P[5] += to_b ? dz : 0.0;
           } else if (ia || ib) {
-            P[3] += mp * (M.tx[e] - M.btx[e]);
-            P[4] += mp * (M.ty[e] - M.bty[e]);
-            P[5] += mp * (M.tz[e] - M.btz[e]);
+            P[3] += mp * (M.tx[e] - SNAPTX(j, e));
+            P[4] += mp * (M.ty[e] - SNAPTY(j, e));
+            P[5] += mp * (M.tz[e] - SNAPTZ(j, e));
           }
         };
         if constexpr (!GL && W_LDS) {
@@ -1413,7 +1400,7 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             if constexpr (TAN) {
               const double tvx = M.tx[e], tvy = M.ty[e], tvz = M.tz[e];
               const double dke = mp * (vx * tvx + vy * tvy + vz * tvz);
-              Ev[2 % NE] += dke - mp * (ox * M.btx[e] + oy * M.bty[e] + oz * M.btz[e]);
+              Ev[2 % NE] += dke - mp * (ox * SNAPTX(j, e) + oy * SNAPTY(j, e) + oz * SNAPTZ(j, e));
               if (isa)
                 Ev[3 % NE] += dke;
               else
@@ -1754,9 +1741,9 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             M.vy[e] = SNAPY(j, e);
             M.vz[e] = SNAPZ(j, e);
             if constexpr (TAN) {
-              M.tx[e] = M.btx[e];
-              M.ty[e] = M.bty[e];
-              M.tz[e] = M.btz[e];
+              M.tx[e] = SNAPTX(j, e);
+              M.ty[e] = SNAPTY(j, e);
+              M.tz[e] = SNAPTZ(j, e);
             }
           }
         });

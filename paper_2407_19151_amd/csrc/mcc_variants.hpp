@@ -28,20 +28,25 @@ enum Mode {
   NMODE = 13
 };
 
-// layout: 0 all in LDS; 1 compact LDS (weights read from the input);
+// layout: 1 LDS (compact: keys and pair energies aliased, above 1024 particles
+// the weights read from the input; 40-42 B per particle of capacity where
+// separate arrays took 56, so more cells are resident per CU: relativistic
+// cells of 576 + 448, 484 us per step of 4096 cells at three waves per SIMD,
+// 593 with separate arrays at two; cells of 3000, 254 us per 400 in LDS, 608
+// in global scratch);
 // 2 per-workgroup global scratch (one wave per cell, or several waves for
 // the plain FP64 and FP32 modes)
 struct Variant {
   int tpc;     // threads per cell (workgroup size)
   int cap;     // largest cell the variant holds
-  int layout;  // 0 LDS, 1 compact LDS, 2 global scratch
+  int layout;  // 1 LDS, 2 global scratch
 };
 
 constexpr int NVARIANT = 16;
 constexpr Variant kVariants[NVARIANT] = {
-    {64, 128, 0},    {64, 256, 0},   {128, 256, 0},  {128, 512, 0},  {256, 512, 0},
-    {256, 1024, 0},  {512, 1024, 0}, {512, 2048, 0}, {1024, 2048, 0}, {1024, 4096, 1},
-    {64, 32768, 2},  {256, 2048, 0}, {512, 4096, 1}, {256, 4096, 1},
+    {64, 128, 1},    {64, 256, 1},   {128, 256, 1},  {128, 512, 1},  {256, 512, 1},
+    {256, 1024, 1},  {512, 1024, 1}, {512, 2048, 1}, {1024, 2048, 1}, {1024, 4096, 1},
+    {64, 32768, 2},  {256, 2048, 1}, {512, 4096, 1}, {256, 4096, 1},
     {256, 32768, 2}, {512, 32768, 2}};
 // the one-wave global variant, which the modes without multi-wave global
 // kernels use in place of variants 14 and 15
@@ -54,12 +59,13 @@ constexpr int kBucketCap[NBUCKET] = {128, 256, 512, 1024, 2048, 4096, 32768};
 // mixes; the autotuner may pick another candidate).  The compact layouts
 // take 256 threads for the 2048 bucket (under the 2-wave register cap the
 // FP64 512-thread kernel holds one workgroup per CU: 0.55 against 0.43 ms on
-// the 65,536-cell mix); the tangent mode, whose cells keep the full LDS
-// layout, has its own large-cell variant.  Cells above 4096 particles take 8 waves in
+// the 65,536-cell mix).  Cells above 4096 particles take 8 waves in
 // global scratch (measured on cells of 4 400 to 8 200 particles: 5.1-5.3x the
-// one-wave variant, 1.5x the 4-wave)
+// one-wave variant, 1.5x the 4-wave).  The tangent form: two waves for cells
+// of 129-256 (3000 of 200: 141 against 147 us) and eight for 1025-2048, whose
+// registers hold twice the snapshot.
 constexpr int kDefaultVariant[NBUCKET] = {0, 1, 3, 5, 11, 12, 15};
-constexpr int kDefaultVariantTan[NBUCKET] = {0, 1, 3, 5, 7, 12, 15};
+constexpr int kDefaultVariantTan[NBUCKET] = {0, 2, 3, 5, 7, 12, 15};
 // With at most as many cells as the device has compute units, every cell has
 // a CU to itself: resident cells per CU no longer matter, the latency of one
 // cell does, and four waves per cell shorten it (16 cells, FP64 N97, kernel
@@ -78,19 +84,12 @@ constexpr int kCandidates[NBUCKET][5] = {
     {0, 1, 2, 5, -1}, {1, 2, 3, 4, 5}, {3, 4, 5, 6, -1}, {5, 6, 7, 11, -1},
     {7, 11, 8, -1, -1}, {12, 13, 9, -1, -1}, {15, 14, 10, -1, -1}};
 
-// the tangent form keeps six more doubles per particle and one per pair: in
-// LDS up to 1024 particles, above that in global scratch
+// the tangent form keeps three more doubles per particle and one per pair: in
+// LDS (compact layout) up to 2048 particles, above that in global scratch.
+// With separate arrays and the tangent's snapshot in LDS it held two cells of
+// 512 per CU instead of four (1024 cells of 512: 139 against 95 us per step)
+// and none above 1024 (400 cells of 1800: 1312 against 204 us).
 constexpr Variant kTanVariantBig = {64, 4096, 2};
-
-// Every mode but the tangent form runs every LDS variant in the compact
-// layout (weights read from HBM, keys and pair energies aliased: 40-42 B of
-// LDS per particle of capacity instead of 56, so more cells are resident per
-// CU; relativistic cells of 576 + 448: 484 us per step of 4096
-// cells at three waves per SIMD, 593 in the full layout at two; cells of 3000:
-// 254 us per 400 in LDS, 608 in global scratch).
-inline constexpr Variant compact_of(Variant V) {
-  return V.layout == 0 ? Variant{V.tpc, V.cap, 1} : V;
-}
 
 // few: no more cells than compute units
 inline constexpr int default_variant(int mode, int bucket, bool few) {
@@ -110,10 +109,9 @@ inline constexpr bool multiwave_global(int m) {
 inline constexpr Variant variant_of(int mode, int v) {
   return (kVariants[v].layout == 2 && kVariants[v].tpc > 64 && !multiwave_global(mode))
              ? kVariants[kGlobalOneWave]
-         : (mode == MODE_TAN && kVariants[v].cap > 1024 && kVariants[v].layout != 2)
+         : (mode == MODE_TAN && kVariants[v].cap > 2048 && kVariants[v].layout != 2)
              ? kTanVariantBig
-         : mode == MODE_TAN ? kVariants[v]
-                            : compact_of(kVariants[v]);
+             : kVariants[v];
 }
 
 // Minimum waves per SIMD the compiler must leave room for (it then caps the
@@ -122,9 +120,13 @@ inline constexpr Variant variant_of(int mode, int v) {
 // waiting on LDS and barriers most of the time.  Cells of 2048 and 4096
 // particles, whose LDS use allows at most 8 waves per CU, ask for 2: an
 // uncapped allocation that reaches 256 registers leaves room for one.
-// 1: no cap (the global-scratch and tangent forms).
+// The tangent form's LDS leaves room for two per SIMD above 256 particles (an
+// uncapped 512 kernel takes 270 registers, one wave: 1024 cells 136 against 96
+// us) and pays for three below (6000 cells of 60: 150, 128 and 150 us at two,
+// three and four).  1: no cap (the global-scratch forms).
 constexpr int min_waves(int tpc, int cap, int layout, bool fp64, bool tangent) {
-  if (tangent || layout == 2) return 1;
+  if (layout == 2) return 1;
+  if (tangent) return cap <= 256 ? 3 : 2;
   if (cap >= 2048) return 2;
   if (tpc == 64 && cap == 128) return 4;
   return 3;
