@@ -144,20 +144,36 @@ const void *const *kernel_table(int mode) {
 
 }  // namespace
 
-// A side stream and two events (default priority, created once) that let the
-// 4096 bucket run on a branch beside the 2048 bucket: its cells take a whole
-// CU's LDS each and drain unevenly, and the 2048 cells fill the CUs it leaves.
-// Every other bucket runs alone: cells of different sizes sharing CUs slowed
-// the step (2-7 %).
-struct Branch {
-  hipStream_t side = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
+// Side streams and events (default priority, created once) on which the
+// kernels of some size buckets run beside those of the others.
+struct Branches {
+  static constexpr int N = 2;
+  hipStream_t side[N] = {};
+  hipEvent_t fork = nullptr, join[N] = {};
+  hipError_t create() {
+    hipError_t e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+    for (int i = 0; i < N && e == hipSuccess; ++i) {
+      e = hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking);
+      if (e == hipSuccess) e = hipEventCreateWithFlags(&join[i], hipEventDisableTiming);
+    }
+    return e;
+  }
+  void release() {
+    for (int i = 0; i < N; ++i) {
+      if (join[i]) (void)hipEventDestroy(join[i]);
+      if (side[i]) (void)hipStreamDestroy(side[i]);
+      join[i] = nullptr;
+      side[i] = nullptr;
+    }
+    if (fork) (void)hipEventDestroy(fork);
+    fork = nullptr;
+  }
 };
 
 struct mcc_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
-  Branch branch;  // the per-call steps' branch (launch_buckets)
+  Branches branches;  // the per-call steps' other streams (launch_buckets)
   int n_cu = 0;
   bool validate = false;
   int32_t *err = nullptr;  // device error word
@@ -409,39 +425,55 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
   return MCC_OK;
 }
 
-constexpr int kSideBucket = 5, kBesideBucket = 4;
-static_assert(kBucketCap[kSideBucket] == 4096 && kBucketCap[kBesideBucket] == 2048,
-              "the branch pairs the 4096 and 2048 buckets");
+// How many streams the buckets' kernels are dealt to, in turn.  A bucket's
+// persistent grid drains unevenly at its end and, in a small population, never
+// fills the GPU; another bucket's cells then take the room.  The fork and join
+// cost about 10 us in a graph, which one shared tail does not pay for (4000
+// cells of 225-275 in two buckets, FP32: 109 against 98 us), so a plan forks
+// from three buckets up.  Three streams up to 2^21 particles, two above, where
+// two grids fill the GPU and a third only mixes cells of mismatched footprints
+// on the CUs.  Lognormal cells, FP64, one, two and three streams: 200 cells of
+// 330 272, 170 and 134 us; 4000 351, 243 and 209; 8000 456, 334 and 349;
+// 16 411 773, 558 and 633; FP32, 65 536: 1640, 1594 and 1702.  A call, whose
+// counts are on the device, takes two (4000 lognormal cells: 538, 390 and 369;
+// 4000 of 100: 272, 252 and 268).
+constexpr int64_t kThreeStreams = 1 << 21;
+
+int branch_streams(int64_t n, int buckets, bool counts_known) {
+  if (!counts_known) return 2;
+  return buckets < 3 ? 1 : n <= kThreeStreams ? 3 : 2;
+}
 
 // enqueue the collide kernels of all buckets, largest cells first
 // (host_counts: the buckets' cell counts when known on the host; empty
-// buckets are then not launched).  With br, the 4096 bucket runs on the
-// branch, unless both kernels use global scratch (they would share the
-// large-cell buffer).
+// buckets are then not launched), with br dealt to its streams and this one.
+// The global-scratch kernels share one scratch, so they stay on this stream.
 mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base, int mode,
                           int32_t n_cells, const int32_t *lists, const uint32_t *counts,
                           const Variants &pick, hipStream_t stream,
-                          const uint32_t *host_counts = nullptr, const Branch *br = nullptr) {
+                          const uint32_t *host_counts = nullptr, const Branches *br = nullptr) {
   auto most = [&](int b) {
     return host_counts ? (int64_t)host_counts[b] : pick.most_cells(base.n, n_cells, b);
   };
-  const bool branch =
-      br && most(kSideBucket) > 0 && most(kBesideBucket) > 0 &&
-      !(variant_of(mode, pick.v[kSideBucket]).layout == 2 &&
-        variant_of(mode, pick.v[kBesideBucket]).layout == 2);
-  if (branch) {
+  int buckets = 0;
+  for (int b = 0; b < NBUCKET; ++b) buckets += most(b) > 0;
+  const int K = br ? std::min(branch_streams(base.n, buckets, host_counts != nullptr), buckets) : 1;
+  if (K > 1) {
     HIP_TRY(hipEventRecord(br->fork, stream));
-    HIP_TRY(hipStreamWaitEvent(br->side, br->fork, 0));
+    for (int i = 0; i < K - 1; ++i) HIP_TRY(hipStreamWaitEvent(br->side[i], br->fork, 0));
   }
+  int turn = 0;
   for (int b = NBUCKET - 1; b >= 0; --b) {
     if (most(b) == 0) continue;
+    const int on = variant_of(mode, pick.v[b]).layout == 2 ? 0 : turn % K;
+    ++turn;
     const mcc_status st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick.v[b],
-                                        most(b), (branch && b == kSideBucket) ? br->side : stream);
+                                        most(b), on ? br->side[on - 1] : stream);
     if (st != MCC_OK) return st;
-    if (branch && b == kBesideBucket) {
-      HIP_TRY(hipEventRecord(br->join, br->side));
-      HIP_TRY(hipStreamWaitEvent(stream, br->join, 0));
-    }
+  }
+  for (int i = 0; i < K - 1; ++i) {
+    HIP_TRY(hipEventRecord(br->join[i], br->side[i]));
+    HIP_TRY(hipStreamWaitEvent(stream, br->join[i], 0));
   }
   return MCC_OK;
 }
@@ -588,9 +620,7 @@ mcc_status mcc_create(mcc_ctx **out, int device, void *hip_stream) {
     e = ctx->work.ensure(sizeof(uint32_t) * WORK_QUEUES * WORK_STRIDE * NBUCKET)
             ? hipSuccess
             : hipErrorOutOfMemory;
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->branch.side, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->branch.fork, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->branch.join, hipEventDisableTiming);
+  if (e == hipSuccess) e = ctx->branches.create();
   if (e == hipSuccess)
     e = hipMemset(ctx->work.p, 0, sizeof(uint32_t) * WORK_QUEUES * WORK_STRIDE * NBUCKET);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -634,10 +664,9 @@ void mcc_destroy(mcc_ctx *ctx) {
                     &ctx->adj_part})
     b->release();
   if (ctx->err) (void)hipFree(ctx->err);
-  if (ctx->branch.side) (void)hipStreamSynchronize(ctx->branch.side);
-  if (ctx->branch.join) (void)hipEventDestroy(ctx->branch.join);
-  if (ctx->branch.fork) (void)hipEventDestroy(ctx->branch.fork);
-  if (ctx->branch.side) (void)hipStreamDestroy(ctx->branch.side);
+  for (hipStream_t side : ctx->branches.side)
+    if (side) (void)hipStreamSynchronize(side);
+  ctx->branches.release();
   delete ctx;
 }
 
@@ -703,11 +732,11 @@ mcc_status mcc_collide_sorted(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t 
   HIP_TRY(launch_front(offsets, n_cells, n_species, n, weights, ctx->lists.as<int32_t>(),
                        ctx->counts.as<uint32_t>(), cell_corr_pairs, stats, nullptr, 0, pick.first,
                        ctx->err, s));
-  // (the branch's event calls cost the host more than the overlap gains when
+  // (the event calls of more streams cost the host more than the overlap gains when
   // every cell has a CU to itself)
   st = launch_buckets(ctx, ctx->big, A, mode, n_cells, ctx->lists.as<int32_t>(),
                       ctx->counts.as<uint32_t>(), pick, s, nullptr,
-                      n_cells > ctx->n_cu ? &ctx->branch : nullptr);
+                      n_cells > ctx->n_cu ? &ctx->branches : nullptr);
   if (st != MCC_OK) return st;
   return finish(ctx);
 }
@@ -798,6 +827,7 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells, int3
                        ctx->counts.as<uint32_t>(), nullptr, stats, nullptr, 0, pick.first,
                        ctx->err, s));
   if (n_cells == 0) return finish(ctx);
+  // (one stream: 1024 cells of 512 in one bucket 96 us, 135 on two)
   st = launch_buckets(ctx, ctx->big, A, MODE_TAN, n_cells, ctx->lists.as<int32_t>(),
                       ctx->counts.as<uint32_t>(), pick, s);
   if (st != MCC_OK) return st;
@@ -1067,9 +1097,9 @@ mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int3
 // ---------------------------------------------------------------------------
 // Batched plan
 // ---------------------------------------------------------------------------
-// One step into the graph being captured on s (the branch of
-// launch_buckets on the capture's side stream and events)
-static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s, const Branch &br) {
+// One step into the graph being captured on s (launch_buckets' other streams
+// on the capture's own)
+static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s, const Branches &br) {
   // counters are reset by kernels (no memset nodes in the graph)
   if (pl->stats) HIP_TRY(launch_zero_stats(pl->stats, s));
   const mcc_status st =
@@ -1257,13 +1287,11 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
     pl->args.prep_word = W.prep_word;
   }
   // capture one step into a graph: stats reset, bucket kernels, step += 1
-  // (default-priority streams; the side stream only carries a branch)
+  // (default-priority streams; the side streams only carry branches)
   hipStream_t cs = nullptr;
-  Branch br;
+  Branches br;
   e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&br.side, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&br.fork, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&br.join, hipEventDisableTiming);
+  if (e == hipSuccess) e = br.create();
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     st = plan_enqueue_step(pl, cs, br);
@@ -1271,9 +1299,7 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
     if (st == MCC_OK && e2 != hipSuccess) st = from_hip(e2);
     if (st == MCC_OK) e = hipGraphInstantiate(&pl->exec, pl->graph, nullptr, nullptr, 0);
   }
-  if (br.join) (void)hipEventDestroy(br.join);
-  if (br.fork) (void)hipEventDestroy(br.fork);
-  if (br.side) (void)hipStreamDestroy(br.side);
+  br.release();
   if (cs) (void)hipStreamDestroy(cs);
   if (e != hipSuccess || st != MCC_OK) {
     mcc_plan_destroy(pl);
