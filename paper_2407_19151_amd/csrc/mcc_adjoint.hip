@@ -396,10 +396,9 @@ __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs 
           }
           const double cf = C.coef * f * nmin_dv;
           if constexpr (sizeof(KR) == 8)
-            scatter_pair_nr_f64<VS, VS>(in_space<VS>(M.vx), in_space<VS>(M.vy),
-                                        in_space<VS>(M.vz), in_space<VS>(M.w), I, J, kp, cf,
-                                        C.fa, C.fb, A.method, (uint32_t)cell, step_lo, c3p, k0,
-                                        k1, A.n97seg);
+            scatter_pair_nr_f64<VS, VS, CAP>(in_space<VS>(M.vx), nullptr, I, J, kp, cf, C.fa,
+                                             C.fb, A.method, (uint32_t)cell, step_lo, c3p, k0,
+                                             k1, A.n97seg);
           else
             scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, C.fa, C.fb, A.method,
                                 (uint32_t)cell, step_lo, c3p, k0, k1, A.n97);

@@ -138,13 +138,21 @@ __device__ __forceinline__ void scatter_pair_hs(VP vx, VP vy, VP vz, WP w, int I
 // code then does not share a register allocation with the rest of the cell
 // kernel, which roughly halves the kernel's registers (measured: the FP64
 // step runs in 0.63x the time); the FP32 form is cheaper inline.
-// VS, WS: the address spaces of the velocities and the weights.
-template <int VS, int WS>
+// VS, WS: the address spaces of the velocities and the weights.  vy, vz and,
+// in the velocities' space, the weights follow vx at strides of CAP, so one
+// pointer is passed: each argument is a register the caller may have to spill
+// (30 -> 27 spills in the 64 x 256 kernel).
+template <int VS, int WS, int CAP>
 __device__ __attribute__((noinline)) void scatter_pair_nr_f64(
-    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
-    SpacePtr<WS, const double> w, int I, int J, uint32_t kp, double coef_f_nmin_dV, double fa,
-    double fb, int method, uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
-    const double *n97tab) {
+    SpacePtr<VS, double> vx, SpacePtr<WS, const double> wsep, int I, int J, uint32_t kp,
+    double coef_f_nmin_dV, double fa, double fb, int method, uint32_t cell, uint32_t step_lo,
+    uint32_t c3, uint32_t k0, uint32_t k1, const double *n97tab) {
+  const SpacePtr<VS, double> vy = vx + CAP, vz = vx + 2 * CAP;
+  SpacePtr<WS, const double> w;
+  if constexpr (VS == WS)
+    w = vx + 3 * CAP;
+  else
+    w = wsep;
   if (method == MCC_HARD_SPHERE)
     scatter_pair_hs(vx, vy, vz, w, I, J, kp, coef_f_nmin_dV, fa, fb, cell, step_lo, c3, k0, k1);
   else
@@ -223,13 +231,18 @@ __device__ __forceinline__ void rot_tangent(int method, double ux, double uy, do
   }
 }
 
-template <int VS, int WS>
+template <int VS, int WS, int CAP>  // (as in scatter_pair_nr_f64)
 __device__ __attribute__((noinline)) void scatter_pair_nr_tan(
-    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
-    SpacePtr<VS, double> tx, SpacePtr<VS, double> ty, SpacePtr<VS, double> tz,
-    SpacePtr<WS, const double> w, int I, int J, uint32_t kp, double coef_f_nmin_dV, double fa, double fb, int method,
-    uint32_t cell, uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1,
-    const double *n97tab, double dlnl) {
+    SpacePtr<VS, double> vx, SpacePtr<VS, double> tx, SpacePtr<WS, const double> wsep, int I,
+    int J, uint32_t kp, double coef_f_nmin_dV, double fa, double fb, int method, uint32_t cell,
+    uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1, const double *n97tab, double dlnl) {
+  const SpacePtr<VS, double> ty = tx + CAP, tz = tx + 2 * CAP;
+  const SpacePtr<VS, double> vy = vx + CAP, vz = vx + 2 * CAP;
+  SpacePtr<WS, const double> w;
+  if constexpr (VS == WS)
+    w = vx + 3 * CAP;
+  else
+    w = wsep;
   using K = KMath<double>;
   const double vix = vx[I], viy = vy[I], viz = vz[I];
   const double vjx = vx[J], vjy = vy[J], vjz = vz[J];
@@ -290,12 +303,17 @@ __device__ __attribute__((noinline)) void scatter_pair_nr_tan(
 // boosted back; s from the invariant rate with the CM deflection.
 // Species (unweighted) masses ma, mb; u = gamma v.  All FP64.
 // ---------------------------------------------------------------------------
-template <int VS, int WS>
+template <int VS, int WS, int CAP>  // (as in scatter_pair_nr_f64)
 __device__ __attribute__((noinline)) void scatter_pair_rel(
-    SpacePtr<VS, double> vx, SpacePtr<VS, double> vy, SpacePtr<VS, double> vz,
-    SpacePtr<WS, const double> w, int I, int J, uint32_t kp,
+    SpacePtr<VS, double> vx, SpacePtr<WS, const double> wsep, int I, int J, uint32_t kp,
     double coef_f_nmin_dV, double ma, double mb, double c, int method, uint32_t cell,
     uint32_t step_lo, uint32_t c3, uint32_t k0, uint32_t k1, const double *n97tab) {
+  const SpacePtr<VS, double> vy = vx + CAP, vz = vx + 2 * CAP;
+  SpacePtr<WS, const double> w;
+  if constexpr (VS == WS)
+    w = vx + 3 * CAP;
+  else
+    w = wsep;
   const double c2 = c * c;
   const double uix = vx[I], uiy = vy[I], uiz = vz[I];
   const double ujx = vx[J], ujy = vy[J], ujz = vz[J];
@@ -884,7 +902,7 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
     // the cell's arrays with their address spaces (the out-of-line pairs)
     constexpr int VS = GL ? SPACE_GLOBAL : SPACE_LDS;
     constexpr int WS = GL || !W_LDS ? SPACE_GLOBAL : SPACE_LDS;
-    const auto pvx = in_space<VS>(M.vx), pvy = in_space<VS>(M.vy), pvz = in_space<VS>(M.vz);
+    const auto pvx = in_space<VS>(M.vx);
     const auto pw = in_space<WS>(M.w);
     const bool prep_read = A.corr && A.prep_mode == PREP_READ;
 
@@ -1160,10 +1178,10 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             const uint32_t kp = (uint32_t)(r * P + i);
             if constexpr (REL) {
               const double mI = sb ? mb : ma;
-              scatter_pair_rel<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+              scatter_pair_rel<VS, WS, CAP>(pvx, VS == WS ? nullptr : pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
                                A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             } else if constexpr (sizeof(KR) == 8)
-              scatter_pair_nr_f64<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+              scatter_pair_nr_f64<VS, WS, CAP>(pvx, VS == WS ? nullptr : pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
                                   (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             else if constexpr (TAB_LDS)
               scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
@@ -1240,14 +1258,14 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
             }
             if constexpr (REL) {
               const double mI = sb ? mb : ma;
-              scatter_pair_rel<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
+              scatter_pair_rel<VS, WS, CAP>(pvx, VS == WS ? nullptr : pw, I, J, kp, cf, mI, intra ? mI : mb, A.c,
                                A.method, (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             } else if constexpr (TAN)
-              scatter_pair_nr_tan<VS, WS>(pvx, pvy, pvz, in_space<VS>(M.tx), in_space<VS>(M.ty),
-                                          in_space<VS>(M.tz), pw, I, J, kp, cf, C.fa, C.fb,
-                                  A.method, (uint32_t)cell, step_lo, c3p, k0, k1, A.n97seg, A.dlnl);
+              scatter_pair_nr_tan<VS, WS, CAP>(pvx, in_space<VS>(M.tx), VS == WS ? nullptr : pw, I,
+                                               J, kp, cf, C.fa, C.fb, A.method, (uint32_t)cell,
+                                               step_lo, c3p, k0, k1, A.n97seg, A.dlnl);
             else if constexpr (sizeof(KR) == 8)
-              scatter_pair_nr_f64<VS, WS>(pvx, pvy, pvz, pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
+              scatter_pair_nr_f64<VS, WS, CAP>(pvx, VS == WS ? nullptr : pw, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
                                   (uint32_t)cell, step_lo, c3s, k0, k1, A.n97seg);
             else if constexpr (TAB_LDS)
               scatter_pair_nr<KR>(M.vx, M.vy, M.vz, M.w, I, J, kp, cf, Cs.fa, Cs.fb, A.method,
