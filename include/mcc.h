@@ -146,8 +146,8 @@ const char *mcc_status_string(mcc_status s);
 
 /* Create a context on `device` enqueuing on `hip_stream` (NULL: the default
  * stream).  The context owns its workspace (cell work lists, error word,
- * large-cell scratch, the collide kernels' cell-queue counters), grown on
- * demand.  Work enqueued through one context must run in order: the calls of
+ * large-cell scratch, the collide kernels' cell-queue counters, 2 B per
+ * particle where cells above 1024 particles may occur), grown on demand.  Work enqueued through one context must run in order: the calls of
  * one context share that workspace, so they must not overlap on the device.
  * The context also creates one side stream (default priority) on which the
  * sorted step runs the kernel of its 2049-4096-particle cells beside the

@@ -994,9 +994,10 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
         int flag = WORDER_EQUAL;
         if (A.sortw && ns >= 2 && lo[0] != hi[0]) {
           flag = WORDER_TIES;
-          // without an LDS home the order is kept only by a plan's weight
-          // pass (M.word is list0 then, free before any collision)
-          if (HAS_WORD || A.prep_mode == PREP_WRITE) {
+          // without an LDS home the order is kept in HBM, by a plan's weight
+          // pass or a call that has room for it (M.word is list0 then, free
+          // before any collision)
+          if (HAS_WORD || A.prep_mode != PREP_NONE) {
             const bool crowded = weight_sort<TPC, PPT, GL>(M, ns, nullptr, o, M.word + o, lo[0],
                                                            hi[0], wsum, &maxocc);
             int tie = 0;
@@ -1017,8 +1018,11 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
         }
       }
       __syncthreads();
-      if (A.prep_mode == PREP_WRITE) {
+      if (HAS_WORD ? A.prep_mode == PREP_WRITE : A.prep_mode != PREP_NONE) {
         for (int e = t; e < n; e += TPC) A.prep_word[cb + e] = M.word[e];
+        // (the collisions overwrite list0 and read the order: the waves of a
+        // workgroup share their CU's L1)
+        if constexpr (!HAS_WORD) __syncthreads();
       }
     }
 
@@ -1489,8 +1493,7 @@ __global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8,
           const int f = s_wflag[sp];
           if (f == WORDER_EQUAL) return L;  // all weights equal: the shuffled order
           if (f == WORDER_DISTINCT) {
-            // (without an LDS home: only a plan marks a species distinct, and
-            // its order is read from HBM)
+            // (without an LDS home: read from HBM)
             if constexpr (HAS_WORD)
               return (const uint16_t *)(M.word + o);
             else

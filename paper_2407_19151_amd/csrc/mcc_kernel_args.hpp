@@ -40,7 +40,7 @@ struct SpeciesPrep {
 };
 
 // prep_mode of CollideArgs
-enum : int32_t { PREP_NONE = 0, PREP_WRITE = 1, PREP_READ = 2 };
+enum : int32_t { PREP_NONE = 0, PREP_WRITE = 1, PREP_READ = 2, PREP_KEEP = 3 };
 
 // the collide kernels hand out cells from up to this many interleaved
 // queues, each with a claim and a finished-workgroup counter at the start of
@@ -80,7 +80,8 @@ struct CollideArgs {
   int32_t write_primal;         // 0: the velocities are read but not written back
   // weight data of a plan: PREP_WRITE computes and stores it (launched with
   // no collisions), PREP_READ uses it (prep[n_cells*S], prep_word[n]:
-  // descending-weight order, cell-local)
+  // descending-weight order, cell-local).  PREP_KEEP (a call without a plan):
+  // variants without an LDS home for the order keep it in prep_word
   int32_t prep_mode;
   SpeciesPrep *prep;
   uint16_t *prep_word;
