@@ -48,3 +48,26 @@ def test_buckets_that_share_the_global_scratch(ctx, pad):  # noqa: F811
     finally:
         for b in variants:
             ctx.set_variant(b, -1)
+
+
+def test_a_captured_call_forks_and_joins(ctx):  # noqa: F811
+    """A call on two streams inside a caller's graph, replayed three times
+    with eager calls between."""
+    import torch
+    from paper_2407_19151_amd import runner
+    wl = custom_workload([(9, 4)] * 400 + MIXED[:5] * 2, seed=19)
+    dw, de, other = (runner.DeviceWorkload(wl) for _ in range(3))
+    start = [x.clone() for x in (dw.vx, dw.vy, dw.vz)]
+    runner.collide_sorted(ctx, de, 1)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        runner.collide_sorted(ctx, dw, 1, with_stats=False)
+    for _ in range(3):
+        runner.collide_sorted(ctx, other, 1)
+        for x, x0 in zip((dw.vx, dw.vy, dw.vz), start):
+            x.copy_(x0)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(dw.velocities(), de.velocities())
+    assert ctx.device_error() == 0
