@@ -405,10 +405,7 @@ __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs 
         }
       }
       __syncthreads();
-      if (!A.corr) {
-        if (rec && t == 0) s_rec[sl].fail = 0;
-        return;
-      }
+      if (!A.corr) return;  // (no correction, no record of one: rev reads none)
       // momentum restore, Eq. (17)
       double P[3] = {0.0, 0.0, 0.0};
       for_owned<TPC, PPT, !GLOB>(n, [&](int j, int e) {
@@ -581,7 +578,8 @@ __global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs 
       const double ma = A.mass[a], mb = A.mass[b];
       auto in_a = [&](int e) { return (unsigned)(e - oa) < (unsigned)na; };
       auto part = [&](int e) { return in_a(e) || (!intra && (unsigned)(e - ob) < (unsigned)nb); };
-      if (Z.fail && !A.keep) return;  // Sec. 6.2 reset: the output is the input
+      // Sec. 6.2 reset: the output is the input (Z is set only with the correction)
+      if (A.corr && Z.fail && !A.keep) return;
       const double *QX = R.q, *QY = R.q + CAP, *QZ = R.q + 2 * CAP;
       for (int e = t; e < n; e += TPC) {
         M.vx[e] = R.b[e];
