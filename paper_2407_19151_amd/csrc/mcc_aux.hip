@@ -839,9 +839,9 @@ hipError_t launch_move_back(int64_t n, int64_t m, uint32_t *const *place, uint16
 // ----------------------------------------------------------------------------
 // The FP64 form's N97 table (N97_SEGMENTS polynomials), computed once per
 // process in extended precision: on each segment the root A of Nanbu's
-// equation at the eight Chebyshev nodes, the polynomial through 1/A and
-// exp(-2A) or expm1(-2A) there by divided differences.  The truncation error
-// is below 2 (1/128)^8 = 3e-17 relative.
+// equation at the Chebyshev nodes, the polynomial through 1/A and exp(-2A) or
+// expm1(-2A) there by divided differences.  The truncation error is below
+// 2 (1/128)^8 = 3e-17 relative, and below 1e-18 on the finer segments.
 // ----------------------------------------------------------------------------
 static long double n97_root_l(long double s) {
   // Newton on 1 - L(A) = -expm1(-s) (A > 1.6) or L(A) = exp(-s), from the
@@ -884,28 +884,32 @@ struct N97Segments {
       v[N + k] = 0.0;
     }
     for (int i = 1; i < N97_SEGMENTS; ++i) {
-      const int e = N97_SEG_E0 + ((i - 1) >> N97_SEG_BITS);
-      const int m = (i - 1) & ((1 << N97_SEG_BITS) - 1);
-      const long double c = ldexpl(1.0L + (m + 0.5L) / (1 << N97_SEG_BITS), e);
-      const long double h = ldexpl(0.5L / (1 << N97_SEG_BITS), e);
+      const bool fine = i >= N97_FINE0;
+      const int bits = fine ? N97_FINE_BITS : N97_SEG_BITS, k0 = i - (fine ? N97_FINE0 : 1);
+      const int e = (fine ? N97_SEG_E1 : N97_SEG_E0) + (k0 >> bits);
+      const int m = k0 & ((1 << bits) - 1);
+      const int M = fine ? N - 1 : N;  // coefficients
+      const long double c = ldexpl(1.0L + (m + 0.5L) / (1 << bits), e);
+      const long double h = ldexpl(0.5L / (1 << bits), e);
       long double z[N], w[2][N];
-      for (int q = 0; q < N; ++q) {
-        z[q] = cosl((2 * q + 1) * 3.14159265358979323846264338L / (2 * N));
+      for (int q = 0; q < M; ++q) {
+        z[q] = cosl((2 * q + 1) * 3.14159265358979323846264338L / (2 * M));
         const long double A = n97_root_l(c + h * z[q]);
         w[0][q] = 1.0L / A;
-        w[1][q] = c < N97_SEG_SPLIT ? expl(-2.0L * A) : expm1l(-2.0L * A);
+        w[1][q] = fine ? expm1l(-2.0L * A) : expl(-2.0L * A);
       }
       for (int f = 0; f < 2; ++f) {
         long double *d = w[f], p[N] = {};
-        for (int o = 1; o < N; ++o)
-          for (int q = N - 1; q >= o; --q) d[q] = (d[q] - d[q - 1]) / (z[q] - z[q - o]);
-        for (int q = N - 1; q >= 0; --q) {  // Newton form to powers of z
-          for (int k = N - 1; k > 0; --k) p[k] = p[k - 1] - z[q] * p[k];
+        for (int o = 1; o < M; ++o)
+          for (int q = M - 1; q >= o; --q) d[q] = (d[q] - d[q - 1]) / (z[q] - z[q - o]);
+        for (int q = M - 1; q >= 0; --q) {  // Newton form to powers of z
+          for (int k = M - 1; k > 0; --k) p[k] = p[k - 1] - z[q] * p[k];
           p[0] = d[q] - z[q] * p[0];
         }
+        double *out = v + i * N97_SEG_DOUBLES + f * N;
         long double hk = 1.0L;
-        for (int k = 0; k < N; ++k, hk *= h)
-          v[i * N97_SEG_DOUBLES + f * N + k] = (double)(p[k] / hk);
+        for (int k = 0; k < M; ++k, hk *= h) out[k] = (double)(p[k] / hk);
+        if (fine) out[M] = (double)(p[0] - (long double)out[0]);
       }
     }
   }

@@ -175,7 +175,7 @@ __device__ __forceinline__ double langevin_prime(double A, double R, const N97Ro
     return dL;
   }
   // 1/sinh^2 A = 4 e^{-2A} / (1 - e^{-2A})^2, finite for every A
-  return R * R - 4.0 * r.F / (r.E * r.E);
+  return R * R - 4.0 * r.F / (r.E() * r.E());
 }
 // d(1 - cos theta)/ds of the N97 angle, with the uniform u0 fixed (0 in the
 // limits, where oc is clamped or does not depend on s)
@@ -184,7 +184,7 @@ __device__ __forceinline__ double n97_oc_s(double s, double u0, double oc, const
   if (!(oc > 0.0 && oc < 2.0) || s > KMath<double>::S_ISO || R == 0.0) return 0.0;
   const double A = 1.0 / R;
   // oc = -log1p(u0 E) / A: d/dA, times dA/ds = -exp(-s) / L'(A)
-  return (2.0 * u0 * r.F / (1.0 + u0 * r.E) - oc) * R * (-exp(-s) / langevin_prime(A, R, r));
+  return (2.0 * u0 * r.F / (1.0 + u0 * r.E()) - oc) * R * (-exp(-s) / langevin_prime(A, R, r));
 }
 
 // Tangent of a pair's velocity change du (the rotation of u = v_I - v_J by

@@ -859,26 +859,34 @@ __device__ __forceinline__ float n97_A_fast(float s, const Tab *tab) {
 }
 
 // Nanbu's root for one pair, FP64, as its uses take it: R = 1/A,
-// E = expm1(-2A) and F = exp(-2A).  Where E is near -1 the table holds F, and
-// E = F - 1 is its rounded value; where F is near 1 it holds E.  R comes as
-// R0 + r (r at most 1/64 of R0), which a product takes with one rounding.
+// E = expm1(-2A) and F = exp(-2A).  Below s = 2, where E is near -1, the table
+// holds F, and E = F - 1 is its rounded value.  From there on E comes as
+// E0 + e as R does as R0 + r: e and r are at most 1/64 of E0 and R0 and carry
+// what those lost to rounding, so that a product takes either with one
+// rounding.  (1 - cos theta) is then no further from its value than with A
+// itself, whose error the quotient cancels (R0 and E0 rounded by themselves:
+// 9.0e-17 to 1.0e-16 on average between 2 and 8, 6.4e-17 like this, 7.5e-17
+// with A; from 8 on 8.8e-17, 6.4e-17 and 7.4e-17).
 // s > 0; above KMath::S_ISO the caller takes the isotropic limit.
-// About 50 instructions where the table, Newton step and expm1 it replaces
+// About 60 instructions where the table, Newton step and expm1 it replaces
 // took 850, several times per wave with every range of s that its lanes hold;
 // R within 2.3e-16 of the root's (before: A within 1.7e-15).
 struct N97Root {
-  double R0, r, E, F;
+  double R0, r, E0, e, F;
   __device__ __forceinline__ double R() const { return R0 + r; }
+  __device__ __forceinline__ double E() const { return E0 + e; }
 };
 __device__ __forceinline__ N97Root n97_root(double s, const double *seg) {
   N97Root r;
   const int hi = __double2hiint(s);
-  constexpr int SH = 20 - N97_SEG_BITS;
-  int i = (hi >> SH) - ((1023 + N97_SEG_E0) << N97_SEG_BITS) + 1;
+  const bool fine = s >= N97_SEG_SPLIT;
+  constexpr int SC = 20 - N97_SEG_BITS, SF = 20 - N97_FINE_BITS;
+  int i = (hi >> (fine ? SF : SC)) - (fine ? ((1023 + N97_SEG_E1) << N97_FINE_BITS) - N97_FINE0
+                                           : ((1023 + N97_SEG_E0) << N97_SEG_BITS) - 1);
   i = i < 0 ? 0 : (i > N97_SEGMENTS - 1 ? N97_SEGMENTS - 1 : i);
   // the segment's centre has the next mantissa bit set and the rest clear
-  const double c =
-      i == 0 ? 0.0 : __hiloint2double((hi & ~((1 << SH) - 1)) | (1 << (SH - 1)), 0);
+  const int hc = (hi & (fine ? -(1 << SF) : -(1 << SC))) | (fine ? 1 << (SF - 1) : 1 << (SC - 1));
+  const double c = i == 0 ? 0.0 : __hiloint2double(hc, 0);
   const double f = s - c;  // exact
   // (global loads: in the out-of-line pair functions the pointer is generic)
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -888,36 +896,40 @@ __device__ __forceinline__ N97Root n97_root(double s, const double *seg) {
   d2 q[H], v[H];
 #pragma unroll
   for (int k = 0; k < H; ++k) q[k] = p[k];
+  // (the eighth entry of the finer segments, 1e-16 of the first, is no
+  // coefficient of f^7, and as one too small to count)
   double R = q[H - 1].y;
 #pragma unroll
   for (int k = H - 1; k >= 0; --k) {
     if (k < H - 1) R = fma(R, f, q[k].y);
     if (k > 0) R = fma(R, f, q[k].x);
   }
-  asm volatile("" : "+v"(R) : : "memory");
+  r.R0 = q[0].x;
+  r.r = fma(R, f, fine ? q[H - 1].y : 0.0);
+  asm volatile("" : "+v"(r.r) : : "memory");
 #pragma unroll
   for (int k = 0; k < H; ++k) v[k] = p[H + k];
   double T = v[H - 1].y;
 #pragma unroll
   for (int k = H - 1; k >= 0; --k) {
     if (k < H - 1) T = fma(T, f, v[k].y);
-    T = fma(T, f, v[k].x);
+    if (k > 0) T = fma(T, f, v[k].x);
   }
-  const bool low = s < N97_SEG_SPLIT;
-  r.R0 = q[0].x;
-  r.r = R * f;
-  r.E = low ? T - 1.0 : T;
-  r.F = low ? T : T + 1.0;
+  const double F = fma(T, f, v[0].x);
+  r.E0 = fine ? v[0].x : F - 1.0;
+  r.e = fine ? fma(T, f, v[H - 1].y) : 0.0;
+  r.F = fine ? 1.0 + r.E() : F;
   if (s >= N97_SEG_TOP) {
     // A = 3y + 9/5 y^3 + 297/175 y^5 + ..., y = exp(-s) < 3.4e-4, and the
     // series of expm1(-2A)
     const double y = exp(-s), y2 = y * y;
     const double A = y * fma(y2, fma(y2, 297.0 / 175.0, 1.8), 3.0);
     r.R0 = 1.0 / A;
-    r.r = 0.0;
-    r.E = -2.0 * A *
-          fma(-A, fma(-A, fma(-A, fma(-A, 2.0 / 15.0, 1.0 / 3.0), 2.0 / 3.0), 1.0), 1.0);
-    r.F = 1.0 + r.E;
+    r.r = r.R0 * fma(-A, r.R0, 1.0);
+    r.E0 = -2.0 * A;
+    r.e = A * A *
+          fma(A, fma(A, fma(A, fma(A, 4.0 / 45.0, -4.0 / 15.0), 2.0 / 3.0), -4.0 / 3.0), 2.0);
+    r.F = 1.0 + r.E();
   }
   return r;
 }
@@ -964,7 +976,7 @@ __device__ __forceinline__ void sample_angle(int method, float s, uint32_t a0, u
 // the N97 angle of a root (FP64)
 __device__ __forceinline__ void n97_angle(double s, double u0, const N97Root &r, double &oc,
                                           double &st) {
-  const double l = -log1p(u0 * r.E);
+  const double l = -log1p(fma(u0, r.E0, u0 * r.e));
   oc = s > KMath<double>::S_ISO ? 2.0 * u0 : fma(l, r.R0, l * r.r);
   oc = oc < 0.0 ? 0.0 : (oc > 2.0 ? 2.0 : oc);
   st = sqrt(oc * (2.0 - oc));

@@ -12,15 +12,19 @@ namespace mcc {
 // knots of the FP32 form's N97 A(s) table (uniform in ln s)
 constexpr int N97_TABLE_SIZE = 256;
 
-// The FP64 form's N97 table: polynomials of degree 7 on 32 segments per
-// binade of s from 2^-6 to 8, and segment 0 for all smaller s.  Per segment
-// the coefficients (about its centre) of 1/A(s) and of exp(-2A) (s < 2) or
-// expm1(-2A) (s >= 2): 128 bytes, one cache line per lookup.
-constexpr int N97_SEG_BITS = 5, N97_SEG_E0 = -6, N97_SEG_E1 = 3, N97_SEG_DEG = 7;
+// The FP64 form's N97 table, 128 bytes (one cache line) per segment of s:
+// polynomials about the segment's centre for 1/A(s) and for exp(-2A) (below
+// s = 2) or expm1(-2A) (from there).  Segment 0 takes all s below 2^-6; from
+// there to 2, 32 segments per binade with polynomials of degree 7; from 2 to
+// 8, 128 per binade with degree 6, whose eighth entry is what the rounding of
+// the constant term lost.
+constexpr int N97_SEG_BITS = 5, N97_SEG_E0 = -6, N97_SEG_E1 = 1, N97_SEG_DEG = 7;
+constexpr int N97_FINE_BITS = 7, N97_FINE_E1 = 3;
 constexpr int N97_SEG_DOUBLES = 2 * (N97_SEG_DEG + 1);
-constexpr int N97_SEGMENTS = 1 + ((N97_SEG_E1 - N97_SEG_E0) << N97_SEG_BITS);
-constexpr double N97_SEG_TOP = 8.0;    // 2^E1
-constexpr double N97_SEG_SPLIT = 2.0;  // below: exp(-2A), above: expm1(-2A)
+constexpr int N97_FINE0 = 1 + ((N97_SEG_E1 - N97_SEG_E0) << N97_SEG_BITS);  // the first from 2 up
+constexpr int N97_SEGMENTS = N97_FINE0 + ((N97_FINE_E1 - N97_SEG_E1) << N97_FINE_BITS);
+constexpr double N97_SEG_SPLIT = 2.0;  // 2^E1
+constexpr double N97_SEG_TOP = 8.0;    // 2^FINE_E1
 
 // Per-collision constants computed on the host in FP64.
 struct CollConst {
