@@ -127,10 +127,12 @@ __device__ __forceinline__ PairBar pair_adjoint(
     vz = -oc * bz;
   }
   if (st != 0.0) ocb += stb * (1.0 - oc) / st;  // st^2 = oc (2 - oc), either sign of st
-  const double sb = ocb * ocs;                  // adjoint of s
-  lbar += sb * s * inv_lnl;
+  // adjoint of ln s (0 where the angle does not depend on s, also where s has
+  // overflowed)
+  const double sb = ocs != 0.0 ? ocb * ocs * s : 0.0;
+  lbar += sb * inv_lnl;
   // |u| through the rotation and through s: ds = -3 s (u . du) / |u|^2
-  const double c = umb / um - 3.0 * s * sb / um2;
+  const double c = umb / um - 3.0 * sb / um2;
   return PairBar{vx + c * ux, vy + c * uy, vz + c * uz};
 }
 

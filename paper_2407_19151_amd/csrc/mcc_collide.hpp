@@ -208,7 +208,9 @@ __device__ __forceinline__ void rot_tangent(int method, double ux, double uy, do
       toc = 2.0 / ((1.0 + d2) * (1.0 + d2)) * d2 * ts / s;
     }
   } else {
-    toc = n97_oc_s(s, u0, oc, root) * ts;
+    // (0 where the angle does not depend on s, also where ts has overflowed with s)
+    const double ocs = n97_oc_s(s, u0, oc, root);
+    toc = ocs != 0.0 ? ocs * ts : 0.0;
   }
   // st^2 = oc (2 - oc) for either sign of st
   const double tst = st != 0.0 ? (1.0 - oc) * toc / st : 0.0;
