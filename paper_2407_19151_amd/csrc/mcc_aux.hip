@@ -622,9 +622,13 @@ __global__ void k_sample_angles(int method, int64_t n, const double *s, const ui
     const T si = (T)s[i];
     double a = 0.0;
     if constexpr (sizeof(T) == 8) {
-      sample_angle(method, si, a0[i], a1[i], o, t, seg);
-      if (method == 1 && !(si > KMath<double>::S_ISO))
-        a = si > 0.0 ? 1.0 / n97_root(si, seg).R() : __builtin_inf();
+      if (method == 1 && !(si > 0.0)) {  // (no pair: the segments take s > 0)
+        o = t = 0.0;
+        a = __builtin_inf();
+      } else {
+        sample_angle(method, si, a0[i], a1[i], o, t, seg);
+        if (method == 1 && !(si > KMath<double>::S_ISO)) a = 1.0 / n97_root(si, seg).R();
+      }
     } else {
       sample_angle(method, si, a0[i], a1[i], o, t, tab);
       if (method == 1) a = (double)n97_A_fast(si, tab);
