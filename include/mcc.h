@@ -178,7 +178,7 @@ mcc_status mcc_device_error(mcc_ctx *ctx, int32_t *code);
  * 9 (1024,4096), 10 (64,32768, one wave with global scratch), 11 (256,2048),
  * 12 (512,4096), 13 (256,4096), 14 (256,32768) and 15 (512,32768) (four and
  * eight waves with global scratch; the diagnostic and tangent forms run them
- * as 10).  -1 restores the default, which depends on
+ * as 10, and the tangent form runs 8 as 7).  -1 restores the default, which depends on
  * the precision mode and on whether n_cells exceeds the device's compute
  * units (built-in tables, the fastest measured on lognormal cell-size mixes
  * and on few cells).  The variant's capacity must hold the bucket's largest cell,
@@ -322,9 +322,9 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells,
  * the pair Jacobians are evaluated in FP64.  A reset (Sec. 6.2) collision
  * passes the adjoint through unchanged.
  * Scratch: per workgroup, the records of up to six collisions (three above
- * 1024 particles per cell) at 80 B per particle of capacity each, longer
+ * 2048 particles per cell) at 80 B per particle of capacity each, longer
  * collision lists being taken in groups: at most 0.5 GB on 256 compute units
- * for cells up to 1024, 0.7 GB for cells up to 4096, 2.7 GB more once a cell
+ * for cells up to 2048, 0.7 GB for cells up to 4096, 2.7 GB more once a cell
  * above 4096 occurs; owned by the context.  The call waits once on the
  * context's stream (to read the cell counts per size bucket) before it
  * enqueues the kernels.

@@ -25,9 +25,9 @@
 // kinematics or FP64) so that it takes the same discrete choices; the pair
 // adjoints are evaluated in FP64 with that form's uniforms.  One workgroup
 // per cell, with the threads per cell of the forward-mode kernels, so the
-// per-cell sums round, and the cut pair falls, as there.
+// per-cell sums are split as there (adjoint_form).
 //
-// Bound by the latency of the cell's phases.  Cells of up to 1024 particles
+// Bound by the latency of the cell's phases.  Cells of up to 2048 particles
 // keep what is accessed through the lists (velocities, weights, adjoints) in
 // LDS, 70 B per particle of capacity, so that eight waves are resident per CU
 // (the registers allow no more), and only stream the records through the
@@ -143,10 +143,10 @@ struct AdjRec {
   int nc0, nc1, fail;
 };
 
-// GLOB: the cell lives in the per-workgroup global scratch (cells above 1024
-// particles), else in LDS
+// GLOB: the cell lives in the per-workgroup global scratch, else in LDS.
+// Cells of 2048 fill a CU's LDS: its one workgroup may take every register.
 template <int TPC, int CAP, typename KR, bool GLOB>
-__global__ void __launch_bounds__(TPC, GLOB ? 1 : 2) adjoint_kernel(AdjointArgs A) {
+__global__ void __launch_bounds__(TPC, GLOB || CAP * 2 / TPC > 8 ? 1 : 2) adjoint_kernel(AdjointArgs A) {
   constexpr int PPT = CAP / TPC;
   constexpr int NW = TPC / WAVE;
   constexpr int VS = GLOB ? SPACE_GLOBAL : SPACE_LDS;  // where the cell lives
@@ -826,42 +826,29 @@ __global__ void __launch_bounds__(1024) k_sum_f64(const double *x, int64_t n, do
   if (threadIdx.x == 0) out[0] = tot[0];
 }
 
-// the kernel of a bucket (largest cell `most`) at the forward-mode variant's
-// threads per cell: in LDS up to 1024 particles, above that in global scratch
+template <typename KR, int TPC, int CAP, bool GLOB>
+const void *adjoint_fn() {
+  return reinterpret_cast<const void *>(&adjoint_kernel<TPC, CAP, KR, GLOB>);
+}
 template <typename KR>
-const void *adjoint_kernel_of(int tpc, int most, int &cap, int &threads) {
-  auto is = [&](int c, int n) {
-    cap = c;
-    threads = n;
-  };
-  if (most > 4096) {
-    is(32768, 64);
-    return reinterpret_cast<const void *>(&adjoint_kernel<64, 32768, KR, true>);
+const void *adjoint_kernel_of(const AdjointForm &f) {
+  switch (f.cap) {
+    case 128: return adjoint_fn<KR, 64, 128, false>();
+    case 256: return adjoint_fn<KR, 64, 256, false>();
+    case 512: return adjoint_fn<KR, 128, 512, false>();
+    case 1024: return adjoint_fn<KR, 256, 1024, false>();
+    case 2048:
+      return f.tpc == 512 ? adjoint_fn<KR, 512, 2048, false>() : adjoint_fn<KR, 256, 2048, false>();
+    case 4096: return adjoint_fn<KR, 64, 4096, true>();
+    default: return adjoint_fn<KR, 64, 32768, true>();
   }
-  if (tpc >= 256 && most <= 1024) {
-    is(1024, 256);
-    return reinterpret_cast<const void *>(&adjoint_kernel<256, 1024, KR, false>);
-  }
-  if (tpc >= 128 && most <= 512) {
-    is(512, 128);
-    return reinterpret_cast<const void *>(&adjoint_kernel<128, 512, KR, false>);
-  }
-  if (tpc == 64 && most <= 128) {
-    is(128, 64);
-    return reinterpret_cast<const void *>(&adjoint_kernel<64, 128, KR, false>);
-  }
-  if (tpc == 64 && most <= 256) {
-    is(256, 64);
-    return reinterpret_cast<const void *>(&adjoint_kernel<64, 256, KR, false>);
-  }
-  is(4096, 64);
-  return reinterpret_cast<const void *>(&adjoint_kernel<64, 4096, KR, true>);
 }
 
+// the kernel of a bucket (largest cell `most`) beside the tangent's of tpc threads
 AdjointKernel adjoint_kernel_for(bool fp32, int tpc, int most) {
   AdjointKernel k;
-  k.fn = fp32 ? adjoint_kernel_of<float>(tpc, most, k.cap, k.tpc)
-              : adjoint_kernel_of<double>(tpc, most, k.cap, k.tpc);
+  k.form = adjoint_form(tpc, most);
+  k.fn = fp32 ? adjoint_kernel_of<float>(k.form) : adjoint_kernel_of<double>(k.form);
   return k;
 }
 
@@ -872,7 +859,7 @@ hipError_t launch_adjoint(const AdjointKernel &k, const AdjointArgs &base, const
   A.cell_list = lists + (int64_t)b * (n_cells > 0 ? n_cells : 1);
   A.cell_count = counts + b;
   void *kargs[] = {&A};
-  return hipLaunchKernel(k.fn, dim3(grid), dim3(k.tpc), kargs, 0, s);
+  return hipLaunchKernel(k.fn, dim3(grid), dim3(k.form.tpc), kargs, 0, s);
 }
 
 hipError_t launch_sum_f64(const double *x, int64_t n, double *out, hipStream_t s) {

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "mcc_kernel_args.hpp"
+#include "mcc_variants.hpp"
 
 namespace mcc {
 
@@ -37,7 +38,7 @@ struct AdjointArgs {
 
 // record slots per workgroup: the collisions a forward pass records before
 // the sweep back over them (longer lists are taken in groups).  Six cover
-// three species; three for the large-cell scratch, whose slots are 2.6 MB.
+// three species; three for the global scratch, whose slots are up to 2.6 MB.
 constexpr int ADJ_MAX_SLOTS = 6, ADJ_BIG_SLOTS = 3;
 
 // one record slot: 9 doubles, half a double, half a u32 and a u16 per
@@ -53,10 +54,41 @@ constexpr unsigned long long adj_stride_bytes(int cap, int slots, bool global) {
                  : 0ull);
 }
 
-// a compiled reverse-mode kernel: its capacity and threads per cell
+// The reverse-mode kernel of a size bucket (largest cell `most`) beside a
+// tangent kernel of tpc threads per cell: as many threads, so that the two
+// split a cell's sums alike (the sums still round by their own expressions: at
+// a switch, where a cell's correction just fails, the two forms' factors f_E
+// differ by a few units in the last place).  In LDS up to 2048 particles,
+// above that, and for one wave above 256, in global scratch.
+struct AdjointForm {
+  int tpc, cap;
+  bool global;
+};
+inline constexpr AdjointForm adjoint_form(int tpc, int most) {
+  if (most > 4096) return {64, 32768, true};
+  if (tpc == 512) return {512, 2048, false};
+  if (tpc == 256) return most <= 1024 ? AdjointForm{256, 1024, false} : AdjointForm{256, 2048, false};
+  if (tpc == 128) return {128, 512, false};
+  if (most <= 128) return {64, 128, false};
+  if (most <= 256) return {64, 256, false};
+  return {64, 4096, true};
+}
+// (every variant that a bucket can run, the caller's included)
+inline constexpr bool adjoint_forms_match() {
+  for (int b = 0; b < NBUCKET; ++b)
+    for (int v = 0; v < NVARIANT; ++v) {
+      if (kVariants[v].cap < kBucketCap[b]) continue;
+      const AdjointForm f = adjoint_form(variant_of(MODE_TAN, v).tpc, kBucketCap[b]);
+      if (f.tpc != variant_of(MODE_TAN, v).tpc || f.cap < kBucketCap[b]) return false;
+    }
+  return true;
+}
+static_assert(adjoint_forms_match(), "the reverse mode takes the tangent's threads per cell");
+
+// a compiled reverse-mode kernel
 struct AdjointKernel {
   const void *fn = nullptr;
-  int cap = 0, tpc = 0;
+  AdjointForm form{};
 };
 
 }  // namespace mcc

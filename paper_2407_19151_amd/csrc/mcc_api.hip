@@ -918,13 +918,12 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
     const bool fp32 = p->precision == MCC_FP32_KINEMATICS;
     for (int b = 0; b < NBUCKET; ++b) {
       if (hc[b] == 0) continue;
-      // threads per cell of the forward-mode variant of the bucket, so the
-      // per-cell sums (and the choices they decide) round as there
+      // (threads per cell of the forward-mode variant of the bucket)
       const AdjointKernel K =
           adjoint_kernel_for(fp32, variant_of(MODE_TAN, pick.v[b]).tpc, kBucketCap[b]);
-      const bool big = K.cap > 4096, global = K.cap > 1024;
+      const bool big = K.form.cap > 4096, global = K.form.global;
       int occ = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, K.fn, K.tpc, 0) != hipSuccess ||
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, K.fn, K.form.tpc, 0) != hipSuccess ||
           occ < 1)
         occ = 1;
       // (as many workgroups of the global form as before the records of a
@@ -933,7 +932,7 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
       const int grid = (int)std::min<uint32_t>(hc[b], (uint32_t)(ctx->n_cu * occ));
       DevBuf &buf = big ? ctx->adj_big : ctx->adj_small;
       A.slots = std::min(std::max(n_coll, 1), global ? ADJ_BIG_SLOTS : ADJ_MAX_SLOTS);
-      A.stride = adj_stride_bytes(K.cap, A.slots, global);
+      A.stride = adj_stride_bytes(K.form.cap, A.slots, global);
       if (!buf.ensure(A.stride * (uint64_t)grid)) return MCC_ERR_OOM;
       A.scratch = buf.as<char>();
       HIP_TRY(launch_adjoint(K, A, ctx->lists.as<int32_t>(), ctx->counts.as<uint32_t>(), n_cells,

@@ -90,6 +90,9 @@ constexpr int kCandidates[NBUCKET][5] = {
 // 512 per CU instead of four (1024 cells of 512: 139 against 95 us per step)
 // and none above 1024 (400 cells of 1800: 1312 against 204 us).
 constexpr Variant kTanVariantBig = {64, 4096, 2};
+// the most threads a tangent kernel takes: the reverse mode, which follows it,
+// would spill half its registers at sixteen waves
+constexpr Variant kTanVariantWide = {512, 2048, 1};
 
 // few: no more cells than compute units
 inline constexpr int default_variant(int mode, int bucket, bool few) {
@@ -111,6 +114,7 @@ inline constexpr Variant variant_of(int mode, int v) {
              ? kVariants[kGlobalOneWave]
          : (mode == MODE_TAN && kVariants[v].cap > 2048 && kVariants[v].layout != 2)
              ? kTanVariantBig
+         : (mode == MODE_TAN && kVariants[v].tpc > 512) ? kTanVariantWide
              : kVariants[v];
 }
 
