@@ -457,26 +457,33 @@ mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base
     return host_counts ? (int64_t)host_counts[b] : pick.most_cells(base.n, n_cells, b);
   };
   int buckets = 0;
-  for (int b = 0; b < NBUCKET; ++b) buckets += most(b) > 0;
+  for (int b = 0; b < NBUCKET; ++b) {
+    if (most(b) == 0) continue;
+    ++buckets;
+    // (scratch before the first launch: an allocation that fails leaves nothing done)
+    if (!ensure_big(ctx, big, mode, pick.v[b])) return MCC_ERR_OOM;
+  }
   const int K = br ? std::min(branch_streams(base.n, buckets, host_counts != nullptr), buckets) : 1;
   if (K > 1) {
     HIP_TRY(hipEventRecord(br->fork, stream));
     for (int i = 0; i < K - 1; ++i) HIP_TRY(hipStreamWaitEvent(br->side[i], br->fork, 0));
   }
   int turn = 0;
-  for (int b = NBUCKET - 1; b >= 0; --b) {
+  mcc_status st = MCC_OK;
+  for (int b = NBUCKET - 1; b >= 0 && st == MCC_OK; --b) {
     if (most(b) == 0) continue;
     const int on = variant_of(mode, pick.v[b]).layout == 2 ? 0 : turn % K;
     ++turn;
-    const mcc_status st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick.v[b],
-                                        most(b), on ? br->side[on - 1] : stream);
-    if (st != MCC_OK) return st;
+    st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick.v[b], most(b),
+                       on ? br->side[on - 1] : stream);
   }
+  // (after an error too: what already runs on the side streams stays ordered
+  // before the caller's next work, and a capture's branches are closed)
   for (int i = 0; i < K - 1; ++i) {
     HIP_TRY(hipEventRecord(br->join[i], br->side[i]));
     HIP_TRY(hipStreamWaitEvent(stream, br->join[i], 0));
   }
-  return MCC_OK;
+  return st;
 }
 
 mcc_status finish(mcc_ctx *ctx) {

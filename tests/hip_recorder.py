@@ -13,7 +13,8 @@ tells streams, events, allocations and launches in order.  The script gets
   ctx()          a new context
   log()          the log since the last call, as a list of dicts
   rt             the stand-in: rt.rec_malloc_limit(bytes) makes larger
-                 allocations fail
+                 allocations fail, rt.rec_fail_launch(k) the k-th launch from
+                 here (from 1)
 
 and what it prints comes back as the result (JSON by its last line)."""
 import json
@@ -44,6 +45,8 @@ static std::map<const void *, std::pair<size_t, void *>> &vars() {
 static std::vector<std::string> lines;
 static std::map<const void *, int> ids;
 static size_t limit = ~(size_t)0;
+static int fail_launch;
+static hipError_t last_error = hipSuccess;
 static int id(const void *p) {
   if (!p) return 0;
   auto it = ids.find(p);
@@ -84,6 +87,7 @@ int rec_log(char *buf, size_t len) {
   return 0;
 }
 void rec_malloc_limit(size_t n) { limit = n; }
+void rec_fail_launch(int k) { fail_launch = k; }
 
 void **__hipRegisterFatBinary(const void *) { static void *m; return &m; }
 void __hipUnregisterFatBinary(void **) {}
@@ -107,6 +111,10 @@ hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *s, hipStream_t *s
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t, hipStream_t s) {
   const std::string n = kernels()[f];
+  if (fail_launch > 0 && --fail_launch == 0) {
+    put(op("failed") + ", \"kernel\": \"" + n + "\"");
+    return last_error = hipErrorInvalidConfiguration;
+  }
   put(op("launch") + ", \"kernel\": \"" + n + "\"" + num("stream", id(s)) + num("grid", g.x) +
       num("block", b.x));
   if (n.find("k_front_one") != std::string::npos) front(a, true);
@@ -141,7 +149,11 @@ hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *p, int) {
   p->multiProcessorCount = 256;
   return hipSuccess;
 }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) {
+  const hipError_t e = last_error;
+  last_error = hipSuccess;
+  return e;
+}
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {

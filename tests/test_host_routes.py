@@ -36,3 +36,47 @@ print(json.dumps(res))
 """ % many)
     assert len(out) > 40
     assert [x for x in out if x[2] != x[3]] == []
+
+
+def _joined(lines):
+    """Every stream that was forked from the caller's (0) and launched on is
+    joined to it afterwards: an event recorded on it after its last launch and
+    waited for by stream 0."""
+    for s in {x["stream"] for x in lines if x["op"] == "wait" and x["stream"] != 0}:
+        last = max((i for i, x in enumerate(lines) if x["op"] in ("launch", "wait")
+                    and x["stream"] == s))
+        rec = [i for i, x in enumerate(lines) if i > last and x["op"] == "record"
+               and x["stream"] == s]
+        if not rec or not any(x["op"] == "wait" and x["stream"] == 0
+                              and x["event"] == lines[rec[0]]["event"] for x in lines[rec[0]:]):
+            return False
+    return True
+
+
+def test_streams_are_joined_after_an_error(lib):
+    """A launch that fails behind the fork, and a scratch allocation that
+    fails: the call reports it, no kernel stays unordered with the caller's
+    stream, and a failed allocation leaves nothing launched."""
+    out = hip_recorder.run(lib, """
+h, res = ctx(), []
+p = Pop([2000] * 10 + [300] * 10 + [50] * 300)
+for k in range(1, 10):
+    sorted_step(h, p); log()
+    rt.rec_fail_launch(k)
+    res.append((sorted_step(h, p), log()))
+    rt.rec_fail_launch(0)
+rt.hipGetLastError()
+h = ctx()
+L.mcc_set_variant(h, 0, 10)        # (700 MB of scratch)
+rt.rec_malloc_limit(1 << 20); log()
+rc = sorted_step(h, p)
+print(json.dumps([res, rc, log()]))
+""")
+    res, rc, lines = out
+    assert [r for r, _ in res] == [-3] * 9  # (two front kernels, seven buckets)
+    for r, x in res:
+        assert _joined(x), (r, x)
+    assert sum(1 for r, x in res if r == -3 and any(y["op"] == "launch" and y["stream"] != 0
+                                                    for y in x)) >= 2
+    assert rc == -2 and not any("collide_kernel" in y.get("kernel", "") for y in lines)
+    assert _joined(lines)
