@@ -116,13 +116,29 @@ struct DevBuf {
 // owns one for its direct calls and every plan owns its own: a plan's graph
 // holds the scratch address, so a buffer the context later grows (and
 // reallocates) must never be the one a plan replays against.
+// One buffer per kernel footprint (the tangent's arrays are larger), so none
+// ever moves: a caller's graph may hold it too.
 struct BigScratch {
-  DevBuf big4k, big32k;
+  DevBuf big32k, tan4k, tan32k;
+  DevBuf &of(const Variant &V, bool tan) { return !tan ? big32k : V.cap > 4096 ? tan32k : tan4k; }
+  const DevBuf &of(const Variant &V, bool tan) const {
+    return const_cast<BigScratch *>(this)->of(V, tan);
+  }
   void release() {
-    big4k.release();
     big32k.release();
+    tan4k.release();
+    tan32k.release();
   }
 };
+// (the step's global variants are all of the largest capacity)
+constexpr bool step_globals_are_32k() {
+  for (int m = 0; m < NMODE; ++m)
+    for (int v = 0; v < NVARIANT; ++v)
+      if (m != MODE_TAN && variant_of(m, v).layout == 2 && variant_of(m, v).cap != MCC_MAX_CELL)
+        return false;
+  return true;
+}
+static_assert(step_globals_are_32k(), "one scratch size per buffer");
 
 const void *const *kernel_table(int mode) {
   switch (mode) {
@@ -369,18 +385,27 @@ int grid_of(mcc_ctx *ctx, int mode, int v) {
   return ctx->grid[mode][v];
 }
 
+// The scratch's size does not depend on the call, so the first allocation also
+// serves a call that is being captured (whose graph then holds it): in relaxed
+// mode for this thread, as a malloc would otherwise end the capture.  A capture
+// must not need larger-celled eager calls before it.
 bool ensure_big(mcc_ctx *ctx, BigScratch &B, int mode, int v) {
   const Variant V = variant_of(mode, v);
   if (V.layout != 2) return true;
-  const uint64_t stride = big_stride_bytes(V.cap, mode == MODE_TAN);
-  if (V.cap > 4096) return B.big32k.ensure(stride * (uint64_t)ctx->n_cu);
-  return B.big4k.ensure(stride * (uint64_t)ctx->n_cu);
+  const uint64_t bytes = big_stride_bytes(V.cap, mode == MODE_TAN) * (uint64_t)ctx->n_cu;
+  DevBuf &buf = B.of(V, mode == MODE_TAN);
+  if (buf.p) return true;
+  hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&m) != hipSuccess) return buf.ensure(bytes);
+  const bool ok = buf.ensure(bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&m);
+  return ok;
 }
 
 void set_big_args(const BigScratch &B, CollideArgs &A, int mode, int v) {
   const Variant V = variant_of(mode, v);
   if (V.layout != 2) return;
-  A.big_scratch = V.cap > 4096 ? B.big32k.as<char>() : B.big4k.as<char>();
+  A.big_scratch = B.of(V, mode == MODE_TAN).as<char>();
   A.big_stride = big_stride_bytes(V.cap, mode == MODE_TAN);
 }
 
