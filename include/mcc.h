@@ -325,7 +325,9 @@ mcc_status mcc_collide_sorted_jvp(mcc_ctx *ctx, int64_t n, int32_t n_cells,
  * 2048 particles per cell) at 80 B per particle of capacity each, longer
  * collision lists being taken in groups: at most 0.5 GB on 256 compute units
  * for cells up to 2048, 0.7 GB for cells up to 4096, 2.7 GB more once a cell
- * above 4096 occurs; owned by the context.  The call waits once on the
+ * above 4096 occurs; owned by the context.  Where that much cannot be
+ * allocated, longer groups are traded for memory, down to one record at a time
+ * (0.4 and 1.4 GB above 2048 and 4096).  The call waits once on the
  * context's stream (to read the cell counts per size bucket) before it
  * enqueues the kernels.
  * Errors: MCC_ERR_UNSUPPORTED for the relativistic form, a pairing other

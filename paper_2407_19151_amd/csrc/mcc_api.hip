@@ -963,9 +963,15 @@ mcc_status mcc_collide_adjoint(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t
       if (global) occ = big ? 1 : 2;
       const int grid = (int)std::min<uint32_t>(hc[b], (uint32_t)(ctx->n_cu * occ));
       DevBuf &buf = big ? ctx->adj_big : ctx->adj_small;
+      // (without memory for a step's records, fewer at a time: with one slot
+      // less than the 228 B per particle that a fixed record took)
       A.slots = std::min(std::max(n_coll, 1), global ? ADJ_BIG_SLOTS : ADJ_MAX_SLOTS);
-      A.stride = adj_stride_bytes(K.form.cap, A.slots, global);
-      if (!buf.ensure(A.stride * (uint64_t)grid)) return MCC_ERR_OOM;
+      for (;; --A.slots) {
+        A.stride = adj_stride_bytes(K.form.cap, A.slots, global);
+        if (buf.ensure(A.stride * (uint64_t)grid)) break;
+        (void)hipGetLastError();
+        if (A.slots == 1) return MCC_ERR_OOM;
+      }
       A.scratch = buf.as<char>();
       HIP_TRY(launch_adjoint(K, A, ctx->lists.as<int32_t>(), ctx->counts.as<uint32_t>(), n_cells,
                              b, grid, s));

@@ -80,3 +80,23 @@ print(json.dumps([res, rc, log()]))
                                                     for y in x)) >= 2
     assert rc == -2 and not any("collide_kernel" in y.get("kernel", "") for y in lines)
     assert _joined(lines)
+
+
+@pytest.mark.parametrize("cell,used_before", [(100, 478e6), (1000, 478e6), (1500, 478e6),
+                                              (4000, 478e6), (8000, 1912e6)])
+def test_adjoint_fits_where_it_fitted(lib, cell, used_before):
+    """Seven collisions with no more memory than 228 B per particle of the 4096
+    (two workgroups per compute unit) or 32768 kernels' capacity: accepted, in
+    smaller groups of records; refused with less than one record's."""
+    out = hip_recorder.run(lib, """
+cell, used = %d, %d
+h, p = ctx(), Pop([cell] * 600, collisions=((0, 0),) * 7)
+rt.rec_malloc_limit(used); log()
+rc = adjoint(h, p)
+big = [x["bytes"] for x in log() if x["op"] == "malloc" and x["ok"] and x["bytes"] > 1e6]
+h2 = ctx()
+rt.rec_malloc_limit(100000)
+print(json.dumps([rc, big, adjoint(h2, p)]))
+""" % (cell, used_before))
+    assert out[0] == 0 and out[1] and max(out[1]) <= used_before
+    assert out[2] == -2
