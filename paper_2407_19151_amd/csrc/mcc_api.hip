@@ -160,19 +160,27 @@ const void *const *kernel_table(int mode) {
 
 }  // namespace
 
-// Side streams and events (default priority, created once) on which the
-// kernels of some size buckets run beside those of the others.
+// Side streams and events (default priority) on which the kernels of some size
+// buckets run beside those of the others.  A context makes one, which calls
+// take; the second, which only plans do, is made when a plan first needs it (25
+// us each, of 75 that creating a context takes).
 struct Branches {
   static constexpr int N = 2;
   hipStream_t side[N] = {};
   hipEvent_t fork = nullptr, join[N] = {};
-  hipError_t create() {
-    hipError_t e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-    for (int i = 0; i < N && e == hipSuccess; ++i) {
-      e = hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking);
-      if (e == hipSuccess) e = hipEventCreateWithFlags(&join[i], hipEventDisableTiming);
+  int ready = 0;  // side streams there are
+  // makes k side streams; false: not to be had (the caller then takes fewer)
+  bool create(int k) {
+    if (ready >= k) return true;
+    hipError_t e = hipSuccess;
+    if (!fork) e = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
+    while (ready < k && e == hipSuccess) {
+      if (!join[ready]) e = hipEventCreateWithFlags(&join[ready], hipEventDisableTiming);
+      if (e == hipSuccess) e = hipStreamCreateWithFlags(&side[ready], hipStreamNonBlocking);
+      if (e == hipSuccess) ++ready;
     }
-    return e;
+    if (e != hipSuccess) (void)hipGetLastError();
+    return ready >= k;
   }
   void release() {
     for (int i = 0; i < N; ++i) {
@@ -183,13 +191,14 @@ struct Branches {
     }
     if (fork) (void)hipEventDestroy(fork);
     fork = nullptr;
+    ready = 0;
   }
 };
 
 struct mcc_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
-  Branches branches;  // the per-call steps' other streams (launch_buckets)
+  Branches branches;  // the steps' other streams (launch_buckets; a plan's capture)
   int n_cu = 0;
   bool validate = false;
   int32_t *err = nullptr;  // device error word
@@ -488,7 +497,8 @@ mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base
     // (scratch before the first launch: an allocation that fails leaves nothing done)
     if (!ensure_big(ctx, big, mode, pick.v[b])) return MCC_ERR_OOM;
   }
-  const int K = br ? std::min(branch_streams(base.n, buckets, host_counts != nullptr), buckets) : 1;
+  int K = br ? std::min(branch_streams(base.n, buckets, host_counts != nullptr), buckets) : 1;
+  if (K > 1) K = 1 + std::min(K - 1, br->ready);
   if (K > 1) {
     HIP_TRY(hipEventRecord(br->fork, stream));
     for (int i = 0; i < K - 1; ++i) HIP_TRY(hipStreamWaitEvent(br->side[i], br->fork, 0));
@@ -653,7 +663,7 @@ mcc_status mcc_create(mcc_ctx **out, int device, void *hip_stream) {
     e = ctx->work.ensure(sizeof(uint32_t) * WORK_QUEUES * WORK_STRIDE * NBUCKET)
             ? hipSuccess
             : hipErrorOutOfMemory;
-  if (e == hipSuccess) e = ctx->branches.create();
+  if (e == hipSuccess && !ctx->branches.create(1)) e = hipErrorUnknown;
   if (e == hipSuccess)
     e = hipMemset(ctx->work.p, 0, sizeof(uint32_t) * WORK_QUEUES * WORK_STRIDE * NBUCKET);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1151,14 +1161,15 @@ mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int3
 // ---------------------------------------------------------------------------
 // Batched plan
 // ---------------------------------------------------------------------------
-// One step into the graph being captured on s (launch_buckets' other streams
-// on the capture's own)
-static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s, const Branches &br) {
+// One step into the graph being captured on s (with launch_buckets' other
+// streams, which only carry its branches)
+static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s) {
   // counters are reset by kernels (no memset nodes in the graph)
   if (pl->stats) HIP_TRY(launch_zero_stats(pl->stats, s));
   const mcc_status st =
       launch_buckets(pl->ctx, pl->big, pl->args, pl->mode, pl->n_cells, pl->lists.as<int32_t>(),
-                     pl->counts.as<uint32_t>(), pl->pick, s, pl->hcount, &br);
+                     pl->counts.as<uint32_t>(), pl->pick, s, pl->hcount,
+                     &pl->ctx->branches);
   if (st != MCC_OK) return st;
   HIP_TRY(launch_inc_u64(pl->step.as<uint64_t>(), s));
   return MCC_OK;
@@ -1341,19 +1352,20 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
     pl->args.prep_word = W.prep_word;
   }
   // capture one step into a graph: stats reset, bucket kernels, step += 1
-  // (default-priority streams; the side streams only carry branches)
+  // (a default-priority stream)
+  int buckets = 0;
+  for (int b = 0; b < NBUCKET; ++b) buckets += pl->hcount[b] > 0;
+  // (without another stream the plan takes those there are)
+  (void)ctx->branches.create(branch_streams(n, buckets, true) - 1);
   hipStream_t cs = nullptr;
-  Branches br;
   e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
-  if (e == hipSuccess) e = br.create();
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
-    st = plan_enqueue_step(pl, cs, br);
+    st = plan_enqueue_step(pl, cs);
     hipError_t e2 = hipStreamEndCapture(cs, &pl->graph);
     if (st == MCC_OK && e2 != hipSuccess) st = from_hip(e2);
     if (st == MCC_OK) e = hipGraphInstantiate(&pl->exec, pl->graph, nullptr, nullptr, 0);
   }
-  br.release();
   if (cs) (void)hipStreamDestroy(cs);
   if (e != hipSuccess || st != MCC_OK) {
     mcc_plan_destroy(pl);

@@ -100,3 +100,27 @@ print(json.dumps([rc, big, adjoint(h2, p)]))
 """ % (cell, used_before))
     assert out[0] == 0 and out[1] and max(out[1]) <= used_before
     assert out[2] == -2
+
+
+def test_streams_are_created_when_first_needed(lib):
+    """A context creates one side stream, calls none, a plan its capture's, and
+    the context's second side stream at the first plan that takes three."""
+    out = hip_recorder.run(lib, """
+def made():
+    x = log()
+    return [sum(y["op"] == o for y in x) for o in ("stream", "event")]
+
+h, res = ctx(), []
+res.append(made())
+sorted_step(h, Pop([50] * 20)); res.append(made())
+a = plan(h, Pop([50] * 20)); res.append(made())
+b = plan(h, Pop([50] * 400 + [200] * 20)); res.append(made())
+sorted_step(h, Pop([50] * 400)); res.append(made())
+sorted_step(h, Pop([50] * 400)); res.append(made())
+c = plan(h, Pop([50] * 400 + [200] * 20 + [400])); res.append(made())
+h = ctx(); made()
+d = plan(h, Pop([50, 200, 400, 1000] * 99)); res.append(made())
+print(json.dumps([res, [x[0] for x in (a, b, c, d)]]))
+""")
+    assert out[0] == [[1, 2], [0, 0], [1, 0], [1, 0], [0, 0], [0, 0], [2, 1], [2, 1]]
+    assert out[1] == [0] * 4
