@@ -465,7 +465,10 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
 // fills the GPU; another bucket's cells then take the room.  The fork and join
 // cost about 10 us in a graph, which one shared tail does not pay for (4000
 // cells of 225-275 in two buckets, FP32: 109 against 98 us), so a plan forks
-// from three buckets up.  Three streams up to 2^21 particles, two above, where
+// from three buckets up, and for the 2048 and 4096 buckets alone, whose cells
+// take a CU's LDS or half of it each and last long (cells of 1100-4000 on one
+// and two streams, FP32: 300 of them 133 and 112 us, 1500 322 and 291; FP64
+// 161 and 135, 402 and 356).  Three streams up to 2^21 particles, two above, where
 // two grids fill the GPU and a third only mixes cells of mismatched footprints
 // on the CUs.  Lognormal cells, FP64, one, two and three streams: 200 cells of
 // 330 272, 170 and 134 us; 4000 351, 243 and 209; 8000 456, 334 and 349;
@@ -473,10 +476,14 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
 // counts are on the device, takes two (4000 lognormal cells: 538, 390 and 369;
 // 4000 of 100: 272, 252 and 268).
 constexpr int64_t kThreeStreams = 1 << 21;
+constexpr unsigned kLargePair = (1u << 4) | (1u << 5);
+static_assert(kBucketCap[4] == 2048 && kBucketCap[5] == 4096, "the pair that forks alone");
 
-int branch_streams(int64_t n, int buckets, bool counts_known) {
+// filled: the buckets that hold cells (bit b)
+int branch_streams(int64_t n, unsigned filled, bool counts_known) {
   if (!counts_known) return 2;
-  return buckets < 3 ? 1 : n <= kThreeStreams ? 3 : 2;
+  if (filled == kLargePair) return 2;
+  return __builtin_popcount(filled) < 3 ? 1 : n <= kThreeStreams ? 3 : 2;
 }
 
 // enqueue the collide kernels of all buckets, largest cells first
@@ -490,14 +497,16 @@ mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base
   auto most = [&](int b) {
     return host_counts ? (int64_t)host_counts[b] : pick.most_cells(base.n, n_cells, b);
   };
-  int buckets = 0;
+  unsigned filled = 0;
   for (int b = 0; b < NBUCKET; ++b) {
     if (most(b) == 0) continue;
-    ++buckets;
+    filled |= 1u << b;
     // (scratch before the first launch: an allocation that fails leaves nothing done)
     if (!ensure_big(ctx, big, mode, pick.v[b])) return MCC_ERR_OOM;
   }
-  int K = br ? std::min(branch_streams(base.n, buckets, host_counts != nullptr), buckets) : 1;
+  int K = br ? std::min(branch_streams(base.n, filled, host_counts != nullptr),
+                        __builtin_popcount(filled))
+             : 1;
   if (K > 1) K = 1 + std::min(K - 1, br->ready);
   if (K > 1) {
     HIP_TRY(hipEventRecord(br->fork, stream));
@@ -1353,10 +1362,10 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   }
   // capture one step into a graph: stats reset, bucket kernels, step += 1
   // (a default-priority stream)
-  int buckets = 0;
-  for (int b = 0; b < NBUCKET; ++b) buckets += pl->hcount[b] > 0;
+  unsigned filled = 0;
+  for (int b = 0; b < NBUCKET; ++b) filled |= pl->hcount[b] > 0 ? 1u << b : 0u;
   // (without another stream the plan takes those there are)
-  (void)ctx->branches.create(branch_streams(n, buckets, true) - 1);
+  (void)ctx->branches.create(branch_streams(n, filled, true) - 1);
   hipStream_t cs = nullptr;
   e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);

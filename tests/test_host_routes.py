@@ -124,3 +124,27 @@ print(json.dumps([res, [x[0] for x in (a, b, c, d)]]))
 """)
     assert out[0] == [[1, 2], [0, 0], [1, 0], [1, 0], [0, 0], [0, 0], [2, 1], [2, 1]]
     assert out[1] == [0] * 4
+
+
+@pytest.mark.parametrize("sizes,streams", [
+    ([1500] * 20 + [3000] * 20, 2), ([1500] * 20 + [900] * 20, 1), ([3000] * 20 + [900] * 20, 1),
+    ([1500] * 20, 1), ([1500] * 20 + [3000] * 20 + [900], 3), ([100] * 400 + [200] * 400, 1),
+    ([1500] * 800 + [3000] * 400 + [900], 2)])
+def test_streams_of_a_plan(lib, sizes, streams):
+    """The streams that a plan's kernels are dealt to: two for cells of
+    1025-2048 and 2049-4096 alone, one for another pair, else by the number of
+    buckets and particles; all joined."""
+    lines = hip_recorder.run(lib, """
+h, p = ctx(), Pop(%r)
+log()
+rc, q = plan(h, p)
+assert rc == 0
+print(json.dumps(log()))
+""" % sizes)
+    start = [i for i, x in enumerate(lines) if x["op"] == "stream"][-1]  # (the capture's)
+    cs = lines[start]["id"]
+    used = {x["stream"] for x in lines[start:] if "collide_kernel" in x.get("kernel", "")}
+    assert len(used) == streams and (streams == 1 or cs in used)
+    for x in lines:
+        x["stream"] = 0 if x.get("stream") == cs else x.get("stream", -1)
+    assert _joined(lines[start:])
