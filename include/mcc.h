@@ -259,8 +259,9 @@ mcc_status mcc_collide_sorted_noalloc(mcc_ctx *ctx, int64_t n, int32_t n_cells,
  * index order inside each group, the sorted step is applied, and the
  * velocities are written back in place.  Same other arguments.  The context
  * grows scratch of 80 bytes per particle for it (the payload in grouped
- * order and between passes, keys, places; 46 up to 511 groups, 86 and 92 where
- * the group numbers have more than 18 and 27 bits), and mcc_bin's 8 B per 4096
+ * order and between passes, keys, places; 46 up to 511 groups; where the group
+ * numbers have more than 18 bits 84, 86 from 2^24 particles up, and 84 where
+ * they have more than 27), and mcc_bin's 8 B per 4096
  * particles and digit bin.
  */
 mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells,

@@ -69,6 +69,10 @@ hipError_t launch_bin_move(int64_t n, const int32_t *cells, const int32_t *speci
 hipError_t launch_move_back(int64_t n, int64_t m, uint32_t *const *place, uint16_t *const *local,
                             double *g, double *rec, int64_t n_pad, double *const *v,
                             hipStream_t s);
+hipError_t launch_gather_rec(int64_t n, const int32_t *perm, const double *const *payload,
+                             double *rec, double *const *g, hipStream_t s);
+hipError_t launch_scatter_back_rec(int64_t n, const int32_t *perm, double *const *g, double *rec,
+                                   double *const *v, hipStream_t s);
 hipError_t launch_gather(int64_t n, const int32_t *perm, const double *w, const double *vx,
                          const double *vy, const double *vz, double *gw, double *gx, double *gy,
                          double *gz, hipStream_t s);
@@ -210,9 +214,10 @@ struct mcc_ctx {
   // counters (zero between launches: each launch resets them at its end, so
   // launches of one context must not overlap)
   DevBuf work;
-  // unsorted entry: the payload in grouped order and between the passes, and
-  // where a pass's items went (mcc_rebin uses `grouped` for its copy)
-  DevBuf tiles, off, grouped, rec, place[3], local;
+  // unsorted entry: the payload in grouped order and between the passes (or in
+  // records), and where a pass's items went, or the permutation (mcc_rebin uses
+  // `grouped` for its copy)
+  DevBuf tiles, off, grouped, rec, place[2], local;
   DevBuf word;  // the calls' weight order of large cells (PREP_KEEP)
   DevBuf bin_k0, bin_k1, bin_v0, bin_v1, bin_hist, bin_pos;  // radix-sort scratch
   // reverse-mode form: per-workgroup scratch (cells up to 4096 particles,
@@ -709,7 +714,7 @@ void mcc_destroy(mcc_ctx *ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   ctx->big.release();
   for (DevBuf *b : {&ctx->lists, &ctx->counts, &ctx->tiles, &ctx->off, &ctx->rec,
-                    &ctx->place[0], &ctx->place[1], &ctx->place[2], &ctx->local, &ctx->word,
+                    &ctx->place[0], &ctx->place[1], &ctx->local, &ctx->word,
                     &ctx->bin_k0, &ctx->bin_k1, &ctx->bin_v0, &ctx->bin_v1, &ctx->bin_hist,
                     &ctx->bin_pos, &ctx->grouped, &ctx->n97,
                     &ctx->work, &ctx->rb, &ctx->adj_small, &ctx->adj_big,
@@ -1114,6 +1119,18 @@ mcc_status mcc_rebin_out(mcc_ctx *ctx, int64_t n, int32_t n_cells, int32_t n_spe
   return finish(ctx);
 }
 
+// How the unsorted entry's payload comes into grouped order and back: moved
+// with the keys by every radix pass, or gathered and scattered as 32-byte
+// records by the permutation.  A pass moves the payload twice over, whatever
+// the order; the records cost two random accesses a particle, cheap while they
+// fit the 256 MB cache.  Whole steps, FP32 without correction, records against
+// moves: two passes, 3e6 particles 433 and 387 us, 1.2e7 1739 and 1401; three,
+// 1.2e6 705 and 718, 4e6 4898 and 5293, 6e6 1591 and 1637, 1.5e7 2485 and 2502,
+// 1.8e7 3232 and 3190; four, 6e6 10 568 and 10 771, 1.8e7 12 422 and 12 738.
+static bool payload_by_record(int64_t n, int passes) {
+  return passes == 3 ? n < (int64_t)1 << 24 : passes > 3;
+}
+
 mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int32_t *species_id,
                        int32_t n_cells, int32_t n_species, const double *weights, double *vx,
                        double *vy, double *vz, const double *cell_volume,
@@ -1130,30 +1147,43 @@ mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int3
   if (m > (int64_t)INT32_MAX) return MCC_ERR_UNSUPPORTED;
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
   const int passes = bin_passes(m);
+  const bool records = payload_by_record(n, passes);
   bool ok = ctx->off.ensure(sizeof(int64_t) * (size_t)(m + 1)) &&
             ctx->grouped.ensure(grouped_bytes(n)) && ensure_passes(ctx, n) &&
-            ctx->local.ensure(2 * nn * (size_t)passes) &&
-            (passes == 1 || ctx->rec.ensure(grouped_bytes(n)));
-  uint32_t *place[4] = {};
-  uint16_t *local[4] = {};
-  for (int p = 0; ok && p < passes; ++p) {
-    local[p] = ctx->local.as<uint16_t>() + (size_t)p * nn;
-    if (p > 0 && p == passes - 1) {  // over the pass's input keys
-      place[p] = ((p - 1) & 1 ? ctx->bin_k1 : ctx->bin_k0).as<uint32_t>();
-    } else {
-      ok = ctx->place[p].ensure(4 * nn);
-      place[p] = ctx->place[p].as<uint32_t>();
+            (passes == 1 || ctx->rec.ensure(grouped_bytes(n)));  // (one pass: no records)
+  uint32_t *place[3] = {};  // (four passes take the records)
+  uint16_t *local[3] = {};
+  if (records) {
+    ok = ok && ctx->place[0].ensure(4 * nn);  // the permutation
+  } else {
+    ok = ok && ctx->local.ensure(2 * nn * (size_t)passes);
+    for (int p = 0; ok && p < passes; ++p) {
+      local[p] = ctx->local.as<uint16_t>() + (size_t)p * nn;
+      if (p > 0 && p == passes - 1) {  // over the pass's input keys
+        place[p] = ((p - 1) & 1 ? ctx->bin_k1 : ctx->bin_k0).as<uint32_t>();
+      } else {
+        ok = ctx->place[p].ensure(4 * nn);
+        place[p] = ctx->place[p].as<uint32_t>();
+      }
     }
   }
   if (!ok) return MCC_ERR_OOM;
   double *g[4];
   grouped_arrays(ctx, n, g);
   const double *const payload[4] = {weights, vx, vy, vz};
-  HIP_TRY(launch_bin_move(n, cells, species_id, n_cells, n_species, ctx->bin_k0.as<uint32_t>(),
-                          ctx->bin_k1.as<uint32_t>(), place, local,
-                          ctx->bin_hist.as<uint32_t>(), ctx->bin_pos.as<uint32_t>(),
-                          ctx->tiles.as<int64_t>(), ctx->off.as<int64_t>(), payload, g[0],
-                          ctx->rec.as<double>(), grouped_pad(n), ctx->err, ctx->stream));
+  double *const v_out[3] = {vx, vy, vz};
+  int32_t *const perm = ctx->place[0].as<int32_t>();
+  if (records) {
+    st = bin_into(ctx, n, cells, species_id, n_cells, n_species, ctx->off.as<int64_t>(), perm);
+    if (st != MCC_OK) return st;
+    HIP_TRY(launch_gather_rec(n, perm, payload, ctx->rec.as<double>(), g, ctx->stream));
+  } else {
+    HIP_TRY(launch_bin_move(n, cells, species_id, n_cells, n_species, ctx->bin_k0.as<uint32_t>(),
+                            ctx->bin_k1.as<uint32_t>(), place, local,
+                            ctx->bin_hist.as<uint32_t>(), ctx->bin_pos.as<uint32_t>(),
+                            ctx->tiles.as<int64_t>(), ctx->off.as<int64_t>(), payload, g[0],
+                            ctx->rec.as<double>(), grouped_pad(n), ctx->err, ctx->stream));
+  }
   const bool v = ctx->validate;
   ctx->validate = false;
   st = mcc_collide_sorted(ctx, n, n_cells, n_species, ctx->off.as<int64_t>(), g[0], g[1], g[2],
@@ -1161,9 +1191,11 @@ mcc_status mcc_collide(mcc_ctx *ctx, int64_t n, const int32_t *cells, const int3
                           coulomb_log, seed, step, p, stats, cell_corr_pairs);
   ctx->validate = v;
   if (st != MCC_OK) return st;
-  double *const v_out[3] = {vx, vy, vz};
-  HIP_TRY(launch_move_back(n, m, place, local, g[0], ctx->rec.as<double>(), grouped_pad(n),
-                           v_out, ctx->stream));
+  if (records)
+    HIP_TRY(launch_scatter_back_rec(n, perm, g, ctx->rec.as<double>(), v_out, ctx->stream));
+  else
+    HIP_TRY(launch_move_back(n, m, place, local, g[0], ctx->rec.as<double>(), grouped_pad(n),
+                             v_out, ctx->stream));
   return finish(ctx);
 }
 

@@ -490,6 +490,57 @@ __global__ void k_gather(int64_t n, const int32_t *perm, const double *w, const 
   }
 }
 
+// The unsorted entry's payload through 32-byte records (w, vx, vy, vz) of a
+// context-owned array in the caller's order, after a binning that gave the
+// permutation: a particle's random access is one aligned record, one memory
+// segment, instead of an 8-byte word in each of four arrays.  Packing and
+// unpacking stream.
+struct alignas(32) Rec4 {
+  double w, x, y, z;
+};
+
+__global__ void k_pack_rec(int64_t n, const double *w, const double *vx, const double *vy,
+                           const double *vz, Rec4 *rec) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    rec[i] = Rec4{w[i], vx[i], vy[i], vz[i]};
+}
+
+__global__ void k_gather_rec(int64_t n, const int32_t *perm, const Rec4 *rec, double *gw,
+                             double *gx, double *gy, double *gz) {
+  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = perm[j];
+    if (i < 0 || i >= n) continue;
+    const Rec4 r = rec[i];
+    gw[j] = r.w;
+    gx[j] = r.x;
+    gy[j] = r.y;
+    gz[j] = r.z;
+  }
+}
+
+// whole records back (the weight unchanged), then the velocities out
+__global__ void k_scatter_rec(int64_t n, const int32_t *perm, const double *gw, const double *gx,
+                              const double *gy, const double *gz, Rec4 *rec) {
+  for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n;
+       j += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = perm[j];
+    if (i < 0 || i >= n) continue;
+    rec[i] = Rec4{gw[j], gx[j], gy[j], gz[j]};
+  }
+}
+
+__global__ void k_unpack_v(int64_t n, const Rec4 *rec, double *vx, double *vy, double *vz) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const Rec4 r = rec[i];
+    vx[i] = r.x;
+    vy[i] = r.y;
+    vz[i] = r.z;
+  }
+}
+
 // The unsorted entry's payload travels with the keys through the radix passes,
 // each of its four arrays staged in LDS in digit order and written as runs of
 // a digit (8 particles at 512 digits and tiles of 4096): neighbouring tiles
@@ -837,6 +888,29 @@ hipError_t launch_move_back(int64_t n, int64_t m, uint32_t *const *place, uint16
     hipLaunchKernelGGL(k_move_back, dim3(xcd_grid(T)), dim3(RADIX_WPB * WAVE), 0, s, n, T,
                        place[p], local[p], P);
   }
+  return hipGetLastError();
+}
+
+// the payload into grouped order and the velocities back by perm, through
+// records (rec: 32 n bytes, 32-byte aligned)
+hipError_t launch_gather_rec(int64_t n, const int32_t *perm, const double *const *payload,
+                             double *rec, double *const *g, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  Rec4 *r = reinterpret_cast<Rec4 *>(rec);
+  hipLaunchKernelGGL(k_pack_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, payload[0],
+                     payload[1], payload[2], payload[3], r);
+  hipLaunchKernelGGL(k_gather_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, perm, r, g[0],
+                     g[1], g[2], g[3]);
+  return hipGetLastError();
+}
+
+hipError_t launch_scatter_back_rec(int64_t n, const int32_t *perm, double *const *g, double *rec,
+                                   double *const *v, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  Rec4 *r = reinterpret_cast<Rec4 *>(rec);
+  hipLaunchKernelGGL(k_scatter_rec, dim3(grid_for(n, 256)), dim3(256), 0, s, n, perm, g[0], g[1],
+                     g[2], g[3], r);
+  hipLaunchKernelGGL(k_unpack_v, dim3(grid_for(n, 256)), dim3(256), 0, s, n, r, v[0], v[1], v[2]);
   return hipGetLastError();
 }
 

@@ -148,3 +148,23 @@ print(json.dumps(log()))
     for x in lines:
         x["stream"] = 0 if x.get("stream") == cs else x.get("stream", -1)
     assert _joined(lines[start:])
+
+
+@pytest.mark.parametrize("n,n_cells,passes,records", [
+    (5000, 511, 1, False), (5000, 512, 2, False), (5000, (1 << 18) - 1, 2, False),
+    (5000, 1 << 18, 3, True), ((1 << 24) - 1, 1 << 18, 3, True), (1 << 24, 1 << 18, 3, False),
+    (5000, (1 << 27) - 1, 3, True), (5000, 1 << 27, 4, True)])
+def test_route_of_the_unsorted_payload(lib, n, n_cells, passes, records):
+    """With the keys through one and two radix passes, as records from three up
+    below 2^24 particles, and with four."""
+    lines = hip_recorder.run(lib, """
+h = ctx()
+log()
+assert collide(h, %d, %d) == 0
+print(json.dumps(log()))
+""" % (n, n_cells))
+    count = lambda k: sum(k in x.get("kernel", "") for x in lines)
+    assert count("k_radix_hist") == passes
+    assert count("k_radix_move") == count("k_move_back") == (0 if records else passes)
+    assert count("k_radix_scatter") == (passes if records else 0)
+    assert count("k_gather_rec") == count("k_scatter_rec") == (1 if records else 0)
