@@ -465,7 +465,7 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
   return MCC_OK;
 }
 
-// How many streams the buckets' kernels are dealt to, in turn.  A bucket's
+// How many streams a plan's bucket kernels are dealt to, in turn.  A bucket's
 // persistent grid drains unevenly at its end and, in a small population, never
 // fills the GPU; another bucket's cells then take the room.  The fork and join
 // cost about 10 us in a graph, which one shared tail does not pay for (4000
@@ -477,18 +477,33 @@ mcc_status launch_bucket(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base,
 // two grids fill the GPU and a third only mixes cells of mismatched footprints
 // on the CUs.  Lognormal cells, FP64, one, two and three streams: 200 cells of
 // 330 272, 170 and 134 us; 4000 351, 243 and 209; 8000 456, 334 and 349;
-// 16 411 773, 558 and 633; FP32, 65 536: 1640, 1594 and 1702.  A call, whose
-// counts are on the device, takes two (4000 lognormal cells: 538, 390 and 369;
-// 4000 of 100: 272, 252 and 268).
+// 16 411 773, 558 and 633; FP32, 65 536: 1640, 1594 and 1702.
 constexpr int64_t kThreeStreams = 1 << 21;
 constexpr unsigned kLargePair = (1u << 4) | (1u << 5);
 static_assert(kBucketCap[4] == 2048 && kBucketCap[5] == 4096, "the pair that forks alone");
 
 // filled: the buckets that hold cells (bit b)
-int branch_streams(int64_t n, unsigned filled, bool counts_known) {
-  if (!counts_known) return 2;
+int plan_streams(int64_t n, unsigned filled) {
   if (filled == kLargePair) return 2;
   return __builtin_popcount(filled) < 3 ? 1 : n <= kThreeStreams ? 3 : 2;
+}
+
+// A call, whose counts are on the device, deals its buckets to two streams in
+// turn, except where that costs more than it gives: with one bucket holding the
+// cells, and as many as keep the GPU full, another stream's tail has nothing to
+// fill, and the empty kernels launched beside the loaded one slow it (FP64
+// cells of 4, 1e6 of them: 7680 us without, 8830 with one beside it) or, where
+// it is the side stream's, delay the next call (16 000 cells of 700, FP32, back
+// to back: 885 and 1178).  So the side stream takes the 2048 and 4096 buckets
+// alone where the mean cell is in the 1024 bucket and there are more than 8
+// cells per compute unit (4000 Poisson cells of 700, FP32: 268 against 362; 1000
+// of 700 115 and 122, but 1000 of 550, in two buckets, 153 and 120), and where
+// it has at most 128 particles and there are more than 160 (45 000 cells of
+// 100, FP64: 465 against 524; 32 000 lognormal cells of 20 488 and 463).
+bool call_large_aside(int64_t n, int32_t n_cells, int n_cu) {
+  if (n <= (int64_t)n_cells * kBucketCap[0]) return n_cells > 160 * n_cu;
+  return n > (int64_t)n_cells * kBucketCap[2] && n <= (int64_t)n_cells * kBucketCap[3] &&
+         n_cells > 8 * n_cu;
 }
 
 // enqueue the collide kernels of all buckets, largest cells first
@@ -509,10 +524,9 @@ mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base
     // (scratch before the first launch: an allocation that fails leaves nothing done)
     if (!ensure_big(ctx, big, mode, pick.v[b])) return MCC_ERR_OOM;
   }
-  int K = br ? std::min(branch_streams(base.n, filled, host_counts != nullptr),
-                        __builtin_popcount(filled))
-             : 1;
-  if (K > 1) K = 1 + std::min(K - 1, br->ready);
+  const bool large_aside = br && !host_counts && call_large_aside(base.n, n_cells, ctx->n_cu);
+  int K = !br ? 1 : host_counts ? plan_streams(base.n, filled) : 2;
+  if (K > 1) K = std::min(K, std::min(__builtin_popcount(filled), 1 + br->ready));
   if (K > 1) {
     HIP_TRY(hipEventRecord(br->fork, stream));
     for (int i = 0; i < K - 1; ++i) HIP_TRY(hipStreamWaitEvent(br->side[i], br->fork, 0));
@@ -521,7 +535,9 @@ mcc_status launch_buckets(mcc_ctx *ctx, BigScratch &big, const CollideArgs &base
   mcc_status st = MCC_OK;
   for (int b = NBUCKET - 1; b >= 0 && st == MCC_OK; --b) {
     if (most(b) == 0) continue;
-    const int on = variant_of(mode, pick.v[b]).layout == 2 ? 0 : turn % K;
+    const int on = variant_of(mode, pick.v[b]).layout == 2 ? 0
+                   : large_aside ? (K > 1 ? (kLargePair >> b) & 1u : 0)
+                                 : turn % K;
     ++turn;
     st = launch_bucket(ctx, big, base, mode, n_cells, lists, counts, b, pick.v[b], most(b),
                        on ? br->side[on - 1] : stream);
@@ -1397,7 +1413,7 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   unsigned filled = 0;
   for (int b = 0; b < NBUCKET; ++b) filled |= pl->hcount[b] > 0 ? 1u << b : 0u;
   // (without another stream the plan takes those there are)
-  (void)ctx->branches.create(branch_streams(n, filled, true) - 1);
+  (void)ctx->branches.create(plan_streams(n, filled) - 1);
   hipStream_t cs = nullptr;
   e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);

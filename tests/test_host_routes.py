@@ -168,3 +168,24 @@ print(json.dumps(log()))
     assert count("k_radix_move") == count("k_move_back") == (0 if records else passes)
     assert count("k_radix_scatter") == (passes if records else 0)
     assert count("k_gather_rec") == count("k_scatter_rec") == (1 if records else 0)
+
+
+@pytest.mark.parametrize("size,cells,aside", [
+    (700, 2048, False), (700, 2049, True), (512, 2049, False), (513, 2049, True),
+    (1024, 2049, True), (1025, 2049, False), (100, 40960, False), (100, 40961, True),
+    (128, 40961, True), (129, 40961, False), (300, 3000, False)])
+def test_side_stream_of_a_call(lib, size, cells, aside):
+    """The buckets that a call puts on its side stream: every other one, or the
+    2048 and 4096 buckets alone for many cells whose mean is in the 1024 bucket
+    or, for very many, in the 128 bucket."""
+    caps = [128, 256, 512, 1024, 2048, 4096, 32768]
+    lines = hip_recorder.run(lib, """
+h, p = ctx(), Pop([%d] * %d)
+log()
+assert sorted_step(h, p) == 0
+print(json.dumps(steps(log())))
+""" % (size, cells))
+    cap = [int(x["kernel"].split("ELi")[1].split("E")[0]) for x in lines]
+    assert cap == sorted(caps, reverse=True)
+    side = {c for c, x in zip(cap, lines) if x["stream"] != 0}
+    assert side == ({2048, 4096} if aside else {4096, 1024, 256})
