@@ -1237,15 +1237,16 @@ static mcc_status plan_enqueue_step(mcc_plan *pl, hipStream_t s) {
 // order, so the last cells claimed are then the smallest and the grid drains
 // evenly.  Cells are independent (their random numbers are keyed by cell),
 // so the order changes no result.
+// largest0: the particles of bucket 0's largest cell.
 static hipError_t order_largest_first(mcc_plan *pl, const int64_t *offsets, int32_t n_cells,
-                                      int32_t S) {
+                                      int32_t S, int64_t &largest0) {
   std::vector<int64_t> off((size_t)n_cells * S + 1);
   hipError_t e = hipMemcpy(off.data(), offsets, sizeof(int64_t) * off.size(),
                            hipMemcpyDeviceToHost);
   std::vector<int32_t> list;
   for (int b = 0; b < NBUCKET && e == hipSuccess; ++b) {
     const uint32_t k = pl->hcount[b];
-    if (k < 2) continue;
+    if (k < (b == 0 ? 1u : 2u)) continue;
     int32_t *dl = pl->lists.as<int32_t>() + (int64_t)b * n_cells;
     list.resize(k);
     e = hipMemcpy(list.data(), dl, sizeof(int32_t) * k, hipMemcpyDeviceToHost);
@@ -1257,6 +1258,7 @@ static hipError_t order_largest_first(mcc_plan *pl, const int64_t *offsets, int3
       const int64_t sx = size(x), sy = size(y);
       return sx > sy || (sx == sy && x < y);
     });
+    if (b == 0) largest0 = size(list[0]);
     e = hipMemcpy(dl, list.data(), sizeof(int32_t) * k, hipMemcpyHostToDevice);
   }
   return e;
@@ -1301,7 +1303,17 @@ mcc_status mcc_plan_create(mcc_ctx *ctx, mcc_plan **plan, int64_t n, int32_t n_c
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess)
     e = hipMemcpy(pl->hcount, pl->counts.p, sizeof(pl->hcount), hipMemcpyDeviceToHost);
-  if (e == hipSuccess && n_cells > 0) e = order_largest_first(pl, offsets, n_cells, n_species);
+  int64_t largest0 = 0;
+  if (e == hipSuccess && n_cells > 0)
+    e = order_largest_first(pl, offsets, n_cells, n_species, largest0);
+  // Few cells, none of the smallest bucket above one wave's lanes: one wave per
+  // cell, whose sums are bit for bit those of the four waves that a call runs
+  // (three of them add zeros).  A call saves launches with the four-wave kernel;
+  // a plan has none to save (200 cells of 60, one wave and four: FP64 34.1 and
+  // 36.7 us, FP32 31.7 and 33.3, TA77 33.4 and 35.9, relativistic 45.4 and 47.7;
+  // N x N FP32 112 and 109, so that form keeps the four).
+  if (n_cells <= ctx->n_cu && largest0 > 0 && largest0 <= 64 && pl->mode != MODE_FP32_NXN)
+    pl->pick.v[0] = kDefaultVariant[0];
   if (e != hipSuccess) {
     mcc_plan_destroy(pl);
     return from_hip(e);

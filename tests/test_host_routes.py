@@ -189,3 +189,19 @@ print(json.dumps(steps(log())))
     assert cap == sorted(caps, reverse=True)
     side = {c for c, x in zip(cap, lines) if x["stream"] != 0}
     assert side == ({2048, 4096} if aside else {4096, 1024, 256})
+
+
+@pytest.mark.parametrize("sizes,form,block", [
+    ([64] * 20, {}, 64), ([65] * 20, {}, 256), ([60] * 20 + [100], {}, 256),
+    ([60] * 20 + [300], {}, 64), ([60] * 257, {}, 64), ([100] * 257, {}, 64),
+    ([64], dict(precision=1), 64), ([60] * 20, dict(precision=1, pairing=1), 256),
+    ([60] * 20, dict(pairing=1), 64)])
+def test_threads_of_a_plan_of_few_small_cells(lib, sizes, form, block):
+    lines = hip_recorder.run(lib, """
+h, p = ctx(), Pop(%r)
+log()
+rc, q = plan(h, p, native.make_params(**%r))
+assert rc == 0
+print(json.dumps(steps(log())))
+""" % (sizes, form))
+    assert lines[-1]["block"] == block  # (the smallest bucket, launched last)
