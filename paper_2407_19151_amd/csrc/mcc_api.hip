@@ -42,7 +42,6 @@ hipError_t launch_front(const int64_t *offsets, int32_t n_cells, int32_t S, int6
                         mcc_stats *stats, double *zero, int64_t nzero, int first_bucket,
                         int32_t *err, hipStream_t s);
 int64_t scan_tiles_needed(int64_t m);
-int64_t bin_tiles(int64_t n);
 int64_t bin_hist_entries(int64_t n);
 hipError_t launch_bin(int64_t n, const int32_t *cells, const int32_t *species, int32_t n_cells,
                       int32_t S, uint32_t *keys0, uint32_t *keys1, int32_t *vals0,
@@ -429,8 +428,8 @@ unsigned long long *g_phase = nullptr;
 #endif
 
 // The caller's variants (mcc_set_variant) or the defaults, which depend on
-// n_cells alone, so a plan and a call of the same cells take the same ones
-// and give the same bits.
+// n_cells alone, so a plan and a call of the same cells take the same ones (or
+// one whose sums are the same) and give the same bits.
 Variants pick_variants(const mcc_ctx *ctx, int mode, int32_t n_cells) {
   Variants r;
   const bool few = n_cells <= ctx->n_cu;

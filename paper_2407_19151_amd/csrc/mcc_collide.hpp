@@ -32,12 +32,12 @@ enum Pairing : int { PAIR_ORDER_N = 0, PAIR_NXN = 1, PAIR_DUPLICITY = 2 };
 
 struct CellMem {
   double *vx, *vy, *vz;
-  const double *w;        // LDS copy, or the read-only input (COMPACT)
+  const double *w;        // LDS copy, or the read-only input (COMPACT above 1024 particles)
   uint16_t *list0, *list1, *ord0, *ord1, *mem;
-  uint16_t *word;         // descending-weight order per species (not kept in the compact layout)
+  uint16_t *word;         // descending-weight order per species (COMPACT above 1024: list0)
   uint32_t *key;          // shuffle keys (CAP)
   uint32_t *cnt;          // CAP+1 bucket counters, always LDS (atomics)
-  double *kbuf;           // per-pair K / U of the energy loop (+ h(-mu) for REL)
+  double *kbuf;           // U of the correction pairs (tangent form: first their K)
   uint32_t *slotbuf;      // GLOBAL: per-item bucket slots
   double *bx, *by, *bz;   // GLOBAL: pre-scatter snapshot
   // tangent form: tangent of the velocities, its pre-scatter snapshot
@@ -682,7 +682,7 @@ __device__ __forceinline__ void for_owned(int n, F &&f) {
 // carry none of their registers
 template <int TPC, int CAP, typename KR, bool REL, int LAY, bool TAN = false, bool DIAG = false,
           int PAIRING = PAIR_ORDER_N>
-__global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, sizeof(KR) == 8, TAN))
+__global__ void __launch_bounds__(TPC, min_waves(TPC, CAP, LAY, TAN))
     collide_kernel(CollideArgs A) {
   constexpr int PPT = CAP / TPC;
   constexpr int NW = TPC / WAVE;

@@ -70,9 +70,10 @@ constexpr int kDefaultVariantTan[NBUCKET] = {0, 2, 3, 5, 7, 12, 15};
 // a CU to itself: resident cells per CU no longer matter, the latency of one
 // cell does, and four waves per cell shorten it (16 cells, FP64 N97, kernel
 // time against the table above: 200 particles 35 against 45 us, 400 37
-// against 47, 60 35 against 31; eight waves for 1500: 63 against 81).  One
-// variant up to 1024 particles also lets a call without a plan launch one
-// kernel for the first four buckets (kFewBucket takes their cells).
+// against 47; eight waves for 1500: 63 against 81).  Cells of 60 are slower
+// (36 against 34), but one variant up to 1024 particles lets a call without a
+// plan launch one kernel for the first four buckets (kFewBucket takes their
+// cells); a plan of such cells takes the one wave (mcc_plan_create).
 constexpr int kFewVariant[NBUCKET] = {5, 5, 5, 5, 7, 12, 15};
 constexpr int kFewBucket = 3;
 static_assert(kFewVariant[0] == kFewVariant[kFewBucket] &&
@@ -128,7 +129,7 @@ inline constexpr Variant variant_of(int mode, int v) {
 // uncapped 512 kernel takes 270 registers, one wave: 1024 cells 136 against 96
 // us) and pays for three below (6000 cells of 60: 150, 128 and 150 us at two,
 // three and four).  1: no cap (the global-scratch forms).
-constexpr int min_waves(int tpc, int cap, int layout, bool fp64, bool tangent) {
+constexpr int min_waves(int tpc, int cap, int layout, bool tangent) {
   if (layout == 2) return 1;
   if (tangent) return cap <= 256 ? 3 : 2;
   if (cap >= 2048) return 2;
